@@ -860,8 +860,7 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
       ProfScope psc(m, "gemm_gate_up");
       launch_gemm_bf16(m, (const f16_t*)m->Xn, (const f16_t*)L.wgu, nullptr, R, 2 * F, d, p, 2, nullptr, (f16_t*)m->Fb);
     } else {
-      project("gemm_gate_up", m->Xn, L.wgu, 2 * F, d, &np, &ps);
-      launch_swiglu(m, R, np, ps);
+      launch_gemm_f32(m, (const float*)m->Xn, (const float*)L.wgu, (float*)m->Fb, R, 2 * F, d, true);
     }
     project("gemm_down", m->Fb, L.wd, d, F, &pending_parts, &pending_stride);
   }

@@ -142,7 +142,6 @@ void launch_repack_tiles(hipStream_t s, const bf16_t* src, f16_t* dst, int N, in
 void launch_embed(ts_model* m, const RowMeta& rm, int R);
 void launch_norm(ts_model* m, int R, const float* gain, int n_parts, size_t part_stride, bool first);
 void launch_rope_kv(ts_model* m, const RowMeta& rm, int R, int layer, int n_parts, size_t part_stride);
-void launch_swiglu(ts_model* m, int R, int n_parts, size_t part_stride);
 void launch_plain_read(ts_model* m, const void* src, size_t bytes, uint32_t* sink);
 void launch_argmax_rows(ts_model* m, int R);
 void launch_walk(ts_model* m, const RowMeta& rm, int R, int n_seqs);
@@ -150,8 +149,8 @@ void launch_sample(ts_model* m, const RowMeta& rm, int R, int n_seqs, float temp
 void launch_commit(ts_kv* kv, int accept_len);
 void launch_kv_import(ts_kv* kv, int pos0, int n_pos, const void* staged_k, const void* staged_v, int layer);
 void launch_kv_export(ts_kv* kv, int pos0, int n_pos, void* staged_k, void* staged_v, int layer);
-// fp32 compute path
-void launch_gemm_f32(ts_model* m, const float* X, const float* W, float* out, int M, int N, int K);
+// fp32 compute path (ts_f32.hip); swiglu: the weights are the fused gate/up tiles, out is the gated product
+void launch_gemm_f32(ts_model* m, const float* X, const float* W, float* out, int M, int N, int K, bool swiglu = false);
 void launch_attn_f32(ts_model* m, const RowMeta& rm, int R, int n_seqs, int layer, int max_keys);
 size_t attn_f32_max_keys();
 // bf16 compute path (ts_gemm_bf16.hip / ts_attn_bf16.hip)

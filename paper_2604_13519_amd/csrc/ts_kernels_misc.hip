@@ -1,4 +1,4 @@
-// Row-wise and bookkeeping kernels of the verify pass, plus the fp32 compute path.
+// Row-wise and bookkeeping kernels of the verify pass.
 //
 // Everything here is bandwidth-trivial next to the weight and K/V streams (a verify
 // pass has at most a few hundred rows); the kernels are written for clarity and for
@@ -7,16 +7,9 @@
 #include "ts_internal.h"
 #include "ts_device_utils.h"
 
-// rotated queries: float, or IEEE half bits for bf16 models (the attention products run in
-// half precision; bf16 K/V entries widen to half exactly)
-__device__ __forceinline__ void st_q(float* p, float v) { *p = v; }
-__device__ __forceinline__ void st_q(bf16_t* p, float v) { *p = f32_to_f16_bits(v); }
-
-// store an activation that feeds a projection: float as is; for bf16 models as a hi and a lo
-// IEEE half in two planes `plane` elements apart (hi saturating)
-__device__ __forceinline__ void st_act(float* p, size_t, float v, unsigned long long*) { *p = v; }
-__device__ __forceinline__ void st_act(f16_t* p, size_t plane, float v, unsigned long long* sat) { st_act_planes(p, plane, v, sat); }
-// four consecutive activations (p 16-byte aligned in float terms): one vector store per plane
+// store four consecutive activations that feed a projection (p 16-byte aligned in float terms):
+// floats as they are; for bf16 models as a hi and a lo IEEE half in two planes `plane` elements
+// apart (hi saturating), one vector store per plane
 __device__ __forceinline__ void st_act4(float* p, size_t, const float4& v, unsigned long long*) { *reinterpret_cast<float4*>(p) = v; }
 __device__ __forceinline__ void st_act4(f16_t* p, size_t plane, const float4& v, unsigned long long* sat) { st_act_planes4(p, plane, v.x, v.y, v.z, v.w, sat); }
 
@@ -284,39 +277,6 @@ void launch_rope_kv(ts_model* m, const RowMeta&, int R, int layer, int n_parts, 
   else
     hipLaunchKernelGGL(k_rope_kv<float>, grid, dim3(256), 0, m->stream, m->part, n_parts, part_stride, m->rope_cs, m->row_dst,
                        (float*)m->Qb, layer, c.n_q_heads, c.n_kv_heads, c.head_dim);
-}
-
-// ---------------------------------------------------------------------------------
-// SwiGLU: Fb[r][f] = T( silu(gate) * up ), gate / up = sums of split-K partials of the
-// fused projection whose 16-column tiles alternate gate, up, gate, up, ...
-// ---------------------------------------------------------------------------------
-template <typename T>
-__global__ void k_swiglu(const float* __restrict__ part, int n_parts, size_t part_stride, T* __restrict__ Fb,
-                         size_t f_plane, int R, int F, unsigned long long* __restrict__ sat) {
-  const size_t total = (size_t)R * F;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const int r = (int)(i / F), f = (int)(i % F);
-    const int cg = (f >> 4) * 32 + (f & 15);
-    const float* p = part + (size_t)r * (2 * F) + cg;
-    float g = 0.f, u = 0.f;
-    for (int s = 0; s < n_parts; ++s) {
-      g += p[(size_t)s * part_stride];
-      u += p[(size_t)s * part_stride + 16];
-    }
-    st_act(Fb + i, f_plane, g / (1.0f + expf(-g)) * u, sat);
-  }
-}
-
-void launch_swiglu(ts_model* m, int R, int n_parts, size_t part_stride) {
-  ProfScope ps(m, "swiglu");
-  const int F = m->cfg.d_ffn;
-  size_t total = (size_t)R * F;
-  int blocks = (int)((total + 255) / 256);
-  if (blocks > 4096) blocks = 4096;
-  if (m->cfg.dtype == TS_DTYPE_BF16)
-    hipLaunchKernelGGL(k_swiglu<f16_t>, dim3(blocks), dim3(256), 0, m->stream, m->part, n_parts, part_stride, (f16_t*)m->Fb, (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * F, R, F, m->sat_count);
-  else
-    hipLaunchKernelGGL(k_swiglu<float>, dim3(blocks), dim3(256), 0, m->stream, m->part, n_parts, part_stride, (float*)m->Fb, (size_t)0, R, F, (unsigned long long*)nullptr);
 }
 
 // ---------------------------------------------------------------------------------
@@ -640,135 +600,6 @@ void launch_kv_import(ts_kv* kv, int pos0, int n_pos, const void* sk, const void
 }
 void launch_kv_export(ts_kv* kv, int pos0, int n_pos, void* sk, void* sv, int layer) {
   kv_xfer<false>(kv, pos0, n_pos, sk, sv, layer);
-}
-
-// =================================================================================
-// fp32 compute path (small models; launch-latency bound, written for exactness)
-// =================================================================================
-
-// out[M][N] = X[M][K] . W[N][K]^T, fp32 FMA in ascending k.  Block = 16 rows x 64 columns.
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ X, const float* __restrict__ W,
-                                                  float* __restrict__ out, int M, int N, int K) {
-  __shared__ float xs[16][33];
-  __shared__ float ws[64][33];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int n0 = blockIdx.x * 64, m0 = blockIdx.y * 16;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    for (int i = threadIdx.x; i < 16 * 32; i += 256) {
-      const int r = i >> 5, c = i & 31;
-      xs[r][c] = (m0 + r < M && k0 + c < K) ? X[(size_t)(m0 + r) * K + k0 + c] : 0.f;
-    }
-    for (int i = threadIdx.x; i < 64 * 32; i += 256) {
-      const int r = i >> 5, c = i & 31;
-      ws[r][c] = (n0 + r < N && k0 + c < K) ? W[(size_t)(n0 + r) * K + k0 + c] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 32; ++c) {
-      const float w = ws[tx][c];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] = fmaf(xs[ty * 4 + i][c], w, acc[i]);
-    }
-    __syncthreads();
-  }
-  for (int i = 0; i < 4; ++i) {
-    const int r = m0 + ty * 4 + i, n = n0 + tx;
-    if (r < M && n < N) out[(size_t)r * N + n] = acc[i];
-  }
-}
-
-void launch_gemm_f32(ts_model* m, const float* X, const float* W, float* out, int M, int N, int K) {
-  ProfScope ps(m, "gemm_f32");
-  hipLaunchKernelGGL(k_gemm_f32, dim3((N + 63) / 64, (M + 15) / 16), dim3(256), 0, m->stream, X, W, out, M, N, K);
-}
-
-// Tree-masked attention, fp32: one block per (row, query head).  Scores for all keys of
-// the row's sequence live in LDS.  Key j < P is context (visible); key P + s is tree row s,
-// visible iff s = 0 (root) or bit s-1 of the row's ancestor mask is set.
-size_t attn_f32_max_keys() { return 15000; }
-
-__global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ Qb, float* __restrict__ Ab,
-                                                  const int32_t* __restrict__ row_seq,
-                                                  const int32_t* __restrict__ row_lrow,
-                                                  const uint64_t* __restrict__ row_anc,
-                                                  const SeqDesc* __restrict__ seqs, int layer, int Hq, int Hkv, int hd,
-                                                  float scale) {
-  extern __shared__ float smem[];
-  __shared__ float red[4];
-  const int r = blockIdx.x, h = blockIdx.y, g = h / (Hq / Hkv);
-  const SeqDesc sd = seqs[row_seq[r]];
-  const uint64_t anc = row_anc[r];
-  const int T = sd.P + sd.M;
-  float* q = smem;          // [hd]
-  float* sc = smem + hd;    // [T]
-  float* acc = sc + T;      // [256]
-  const size_t page_elems = (size_t)Hkv * 16 * hd;
-  const float* kl = (const float*)sd.k_pool + (size_t)layer * sd.n_pages * page_elems;
-  const float* vl = (const float*)sd.v_pool + (size_t)layer * sd.n_pages * page_elems;
-  for (int i = threadIdx.x; i < hd; i += 256) q[i] = Qb[(size_t)r * Hq * hd + h * hd + i];
-  __syncthreads();
-  float mx = -INFINITY;
-  for (int j = threadIdx.x; j < T; j += 256) {
-    bool vis = true;
-    if (j >= sd.P) {
-      const int s = j - sd.P;
-      vis = (s == 0) || ((anc >> (s - 1)) & 1ull);
-    }
-    float v = -INFINITY;
-    if (vis) {
-      const float* kr = kl + (size_t)sd.page_table[j >> 4] * page_elems + ((size_t)g * 16 + (j & 15)) * hd;
-      float a = 0.f;
-      for (int i = 0; i < hd; ++i) a = fmaf(q[i], kr[i], a);
-      v = a * scale;
-    }
-    sc[j] = v;
-    mx = fmaxf(mx, v);
-  }
-  mx = wave_max(mx);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  __syncthreads();
-  float sum = 0.f;
-  for (int j = threadIdx.x; j < T; j += 256) {
-    const float p = expf(sc[j] - mx);
-    sc[j] = p;
-    sum += p;
-  }
-  sum = wave_sum(sum);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
-  __syncthreads();
-  sum = red[0] + red[1] + red[2] + red[3];
-  // P.V: thread (dd, part) accumulates keys part, part + n_parts, ... for head-dim index dd
-  const int n_parts = 256 / hd;
-  const int dd = threadIdx.x % hd, part = threadIdx.x / hd;
-  float a = 0.f;
-  if (part < n_parts) {
-    for (int j = part; j < T; j += n_parts) {
-      const float p = sc[j];
-      if (p != 0.f) {
-        const float* vp = vl + (size_t)sd.page_table[j >> 4] * page_elems + ((size_t)g * hd + dd) * 16 + (j & 15);
-        a = fmaf(p, *vp, a);
-      }
-    }
-  }
-  acc[threadIdx.x] = a;
-  __syncthreads();
-  if (threadIdx.x < hd) {
-    float o = 0.f;
-    for (int p = 0; p < n_parts; ++p) o += acc[p * hd + threadIdx.x];
-    Ab[(size_t)r * Hq * hd + h * hd + threadIdx.x] = o / sum;
-  }
-}
-
-void launch_attn_f32(ts_model* m, const RowMeta& rm, int R, int, int layer, int max_keys) {
-  ProfScope ps(m, "attn_f32");
-  const ts_model_config& c = m->cfg;
-  size_t shmem = (size_t)(c.head_dim + max_keys + 256) * sizeof(float);
-  hipLaunchKernelGGL(k_attn_f32, dim3(R, c.n_q_heads), dim3(256), shmem, m->stream, (const float*)m->Qb, (float*)m->Ab,
-                     rm.seq, rm.lrow, rm.anc, m->seq_dev, layer, c.n_q_heads, c.n_kv_heads, c.head_dim,
-                     1.0f / sqrtf((float)c.head_dim));
 }
 
 // ---------------------------------------------------------------------------------
