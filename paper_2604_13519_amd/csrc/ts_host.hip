@@ -156,13 +156,13 @@ static void free_workspace(ts_model* m) {
   dev_free(m->H); dev_free(m->Xn); dev_free(m->Qb); dev_free(m->Ab); dev_free(m->Fb); dev_free(m->part);
   dev_free(m->attn_part_o); dev_free(m->attn_part_ml); dev_free(m->rope_cs); dev_free(m->row_dst); dev_free(m->amax_val);
   dev_free(m->amax_idx); dev_free(m->logits); dev_free(m->meta_dev); dev_free(m->seq_dev);
-  dev_free(m->samp_lse); dev_free(m->samp_tok);
+  dev_free(m->samp_part); dev_free(m->samp_tok);
   if (m->meta_host) (void)hipHostFree(m->meta_host);
   if (m->res_host) (void)hipHostFree(m->res_host);
   m->H = nullptr; m->Xn = m->Qb = m->Ab = m->Fb = nullptr; m->part = nullptr;
   m->attn_part_o = nullptr; m->attn_part_ml = nullptr; m->rope_cs = nullptr; m->row_dst = nullptr; m->amax_val = nullptr; m->amax_idx = nullptr;
   m->logits = nullptr; m->meta_dev = nullptr; m->seq_dev = nullptr; m->meta_host = nullptr; m->res_host = nullptr;
-  m->samp_lse = nullptr; m->samp_tok = nullptr;
+  m->samp_part = nullptr; m->samp_tok = nullptr;
   m->ws_rows = 0; m->ws_seqs = 0; m->logits_rows = 0; m->attn_max_splits = 0; m->part_elems = 0;
 }
 
@@ -209,7 +209,8 @@ static ts_status ensure_workspace(ts_model* m, int rows, int seqs, bool want_log
     if ((st = dev_alloc_bytes((void**)&m->row_dst, (size_t)alloc_rows * sizeof(RowDst), true))) return st;
     if ((st = dev_alloc_bytes((void**)&m->amax_val, (size_t)alloc_rows * m->amax_parts * 4, true))) return st;
     if ((st = dev_alloc_bytes((void**)&m->amax_idx, (size_t)alloc_rows * m->amax_parts * 4, true))) return st;
-    if ((st = dev_alloc_bytes((void**)&m->samp_lse, (size_t)alloc_rows * 4, true))) return st;
+    // stochastic acceptance takes one sequence per call
+    if ((st = dev_alloc_bytes((void**)&m->samp_part, (size_t)(TS_MAX_NODES + 1) * sample_chunks(c.vocab) * sizeof(float4), true))) return st;
     if ((st = dev_alloc_bytes((void**)&m->samp_tok, (size_t)alloc_rows * 4, true))) return st;
     m->meta_bytes = meta_bytes_for(alloc_rows);
     if ((st = dev_alloc_bytes(&m->meta_dev, m->meta_bytes, true))) return st;
@@ -388,7 +389,7 @@ extern "C" ts_status ts_model_load(const ts_model_config* cfg, const ts_weights*
   m->rope_cs = nullptr; m->row_dst = nullptr; m->amax_val = nullptr; m->amax_idx = nullptr; m->logits = nullptr;
   m->keep_logits = false; m->logits_rows = 0; m->meta_dev = nullptr; m->meta_host = nullptr; m->meta_bytes = 0;
   m->seq_dev = nullptr; m->res_host = nullptr; m->ws_rows = 0; m->ws_seqs = 0;
-  m->samp_lse = nullptr; m->samp_tok = nullptr;
+  m->samp_part = nullptr; m->samp_tok = nullptr;
   m->prof_on = false; m->ev_used = 0; m->last_rows = 0;
   hipError_t e = hipGetDevice(&m->device);
   hipDeviceProp_t prop;

@@ -121,7 +121,8 @@ struct ts_model {
   float* amax_val; int32_t* amax_idx; int amax_parts;   // [rows][parts]
   int amax_used;                // partials per row the last lm_head launch wrote (<= amax_parts)
   float* logits; bool keep_logits; int logits_rows;     // [rows][V] when kept
-  float* samp_lse; int32_t* samp_tok;                   // per-row token (greedy arg-max or residual sample); log-sum-exp for sampling
+  int32_t* samp_tok;                                    // per-row token (greedy arg-max or residual sample)
+  float4* samp_part;                                    // [TS_MAX_NODES + 1][sample_chunks(V)] (max, sum, best score, token)
   // per-call metadata (device + pinned host mirror)
   void* meta_dev; void* meta_host; size_t meta_bytes;
   SeqDesc* seq_dev;
@@ -145,6 +146,7 @@ void launch_rope_kv(ts_model* m, const RowMeta& rm, int R, int layer, int n_part
 void launch_plain_read(ts_model* m, const void* src, size_t bytes, uint32_t* sink);
 void launch_argmax_rows(ts_model* m, int R);
 void launch_walk(ts_model* m, const RowMeta& rm, int R, int n_seqs);
+int sample_chunks(int vocab);
 void launch_sample(ts_model* m, const RowMeta& rm, int R, int n_seqs, float temperature, uint64_t seed);
 void launch_commit(ts_kv* kv, int accept_len);
 void launch_kv_import(ts_kv* kv, int pos0, int n_pos, const void* staged_k, const void* staged_v, int layer);

@@ -393,8 +393,8 @@ void launch_walk(ts_model* m, const RowMeta& rm, int R, int n_seqs) {
 // ---------------------------------------------------------------------------------
 // Stochastic acceptance (speculative sampling with point-mass drafts; App. B.2 names the
 // rule, Leviathan et al. 2023).  Two kernels over the materialised logits of one sequence:
-//  k_sample_rows  per row: log-sum-exp of logits / T, and the residual sample the step would
-//                 end with at this row: arg-max of logits / T + Gumbel noise over all tokens
+//  k_sample_rows  per row, in chunks: log-sum-exp of logits / T, and the residual sample the step
+//                 would end with at this row: arg-max of logits / T + Gumbel noise over all tokens
 //                 except those of the row's children (if the walk stops here, every child was
 //                 rejected and its token removed from the distribution).
 //  k_walk_sample  child c of row r is accepted with probability p_r(x_c) / (1 - mass of the
@@ -411,16 +411,31 @@ __device__ __forceinline__ float gumbel_noise(uint64_t seed, int lrow, int v) {
   return -logf(-logf(u));
 }
 
-__global__ __launch_bounds__(1024) void k_sample_rows(const float* __restrict__ logits, int V, float inv_t, uint64_t seed,
-                                                      const int32_t* __restrict__ tok, const int32_t* __restrict__ par,
-                                                      const int32_t* __restrict__ lrow, const int32_t* __restrict__ row_seq,
-                                                      const SeqDesc* __restrict__ seqs, float* __restrict__ lse,
-                                                      int32_t* __restrict__ samp_tok) {
+// Log-sum-exp and perturbed arg-max of one chunk of kSampChunk tokens of one row: (max, sum of
+// exponentials, best perturbed score, its token).  A row is cut into chunks so that a handful of
+// rows still fills the chip: the work is one exponential and two logarithms per token.
+constexpr int kSampThreads = 256, kSampPerThread = 8, kSampChunk = kSampThreads * kSampPerThread;
+int sample_chunks(int vocab) { return (vocab + kSampChunk - 1) / kSampChunk; }
+
+__device__ __forceinline__ void lse_take(float& m, float& s, float om, float os) {
+  const float mm = fmaxf(m, om);
+  s = (m == -INFINITY ? 0.f : s * expf(m - mm)) + (om == -INFINITY ? 0.f : os * expf(om - mm));
+  m = mm;
+}
+
+__global__ __launch_bounds__(kSampThreads) void k_sample_rows(const float* __restrict__ logits, int V, float inv_t, uint64_t seed,
+                                                              const int32_t* __restrict__ tok, const int32_t* __restrict__ par,
+                                                              const int32_t* __restrict__ lrow, const int32_t* __restrict__ row_seq,
+                                                              const SeqDesc* __restrict__ seqs, float4* __restrict__ partial) {
   __shared__ int excl[TS_MAX_NODES + 1];
   __shared__ int n_excl;
-  __shared__ float sm[16], ss[16], sv[16];
-  __shared__ int si[16];
-  const int row = blockIdx.x, tid = threadIdx.x;
+  __shared__ float sm[kSampThreads / 64], ss[kSampThreads / 64], sv[kSampThreads / 64];
+  __shared__ int si[kSampThreads / 64];
+  const int row = blockIdx.y, tid = threadIdx.x, v0 = blockIdx.x * kSampChunk + tid;
+  const float* p = logits + (size_t)row * V;
+  float z[kSampPerThread];
+#pragma unroll
+  for (int u = 0; u < kSampPerThread; ++u) z[u] = v0 + u * kSampThreads < V ? p[v0 + u * kSampThreads] * inv_t : -INFINITY;
   const SeqDesc sd = seqs[row_seq[row]];
   const int lr = lrow[row];
   if (tid == 0) n_excl = 0;
@@ -428,54 +443,62 @@ __global__ __launch_bounds__(1024) void k_sample_rows(const float* __restrict__ 
   if (tid < sd.M && tid > 0 && par[sd.row0 + tid] == lr) excl[atomicAdd(&n_excl, 1)] = tok[sd.row0 + tid];
   __syncthreads();
   const int ne = n_excl;
-  const float* p = logits + (size_t)row * V;
   float m = -INFINITY, s = 0.f, bv = -INFINITY;
   int bi = 0x7fffffff;
-  for (int v = tid; v < V; v += 1024) {
-    const float z = p[v] * inv_t;
-    if (z > m) { s = s * expf(m - z) + 1.0f; m = z; } else { s += expf(z - m); }
+#pragma unroll
+  for (int u = 0; u < kSampPerThread; ++u) m = fmaxf(m, z[u]);
+#pragma unroll
+  for (int u = 0; u < kSampPerThread; ++u) {
+    const int v = v0 + u * kSampThreads;
+    if (v >= V) break;
+    s += expf(z[u] - m);
     bool ex = false;
     for (int e = 0; e < ne; ++e) ex |= (excl[e] == v);
-    if (!ex) amax_take(bv, bi, z + gumbel_noise(seed, lr, v), v);
+    if (!ex) amax_take(bv, bi, z[u] + gumbel_noise(seed, lr, v), v);
   }
-  // combine (max, sum of exponentials) and the best perturbed score over the wave, then over the block
-  for (int o = 32; o > 0; o >>= 1) {
-    const float om = __shfl_xor(m, o, 64), os = __shfl_xor(s, o, 64);
-    const float mm = fmaxf(m, om);
-    s = (m == -INFINITY ? 0.f : s * expf(m - mm)) + (om == -INFINITY ? 0.f : os * expf(om - mm));
-    m = mm;
-  }
+  // combine over the wave, then over the block
+  for (int o = 32; o > 0; o >>= 1) lse_take(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
   wave_amax(bv, bi);
   if ((tid & 63) == 0) { sm[tid >> 6] = m; ss[tid >> 6] = s; sv[tid >> 6] = bv; si[tid >> 6] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < 16; ++w) {
-      const float mm = fmaxf(m, sm[w]);
-      s = (m == -INFINITY ? 0.f : s * expf(m - mm)) + (sm[w] == -INFINITY ? 0.f : ss[w] * expf(sm[w] - mm));
-      m = mm;
+    for (int w = 1; w < kSampThreads / 64; ++w) {
+      lse_take(m, s, sm[w], ss[w]);
       amax_take(bv, bi, sv[w], si[w]);
     }
-    lse[row] = m + logf(s);
-    samp_tok[row] = bi;
+    partial[(size_t)row * gridDim.x + blockIdx.x] = make_float4(m, s, bv, __int_as_float(bi));
   }
 }
 
-__global__ __launch_bounds__(128) void k_walk_sample(const float* __restrict__ logits, int V, float inv_t,
-                                                     const float* __restrict__ lse, const int32_t* __restrict__ samp_tok,
-                                                     const float* __restrict__ node_u, const int32_t* __restrict__ tok,
-                                                     const int32_t* __restrict__ par, const SeqDesc* __restrict__ seqs) {
-  __shared__ float prob[TS_MAX_NODES + 1], uu[TS_MAX_NODES + 1];
-  __shared__ int s_tok[TS_MAX_NODES + 1], s_par[TS_MAX_NODES + 1];
+// Joins the chunks of every row (a wave per row), then walks the tree.
+__global__ __launch_bounds__(1024) void k_walk_sample(const float* __restrict__ logits, int V, float inv_t,
+                                                      const float4* __restrict__ partial, int chunks, int32_t* __restrict__ samp_tok,
+                                                      const float* __restrict__ node_u, const int32_t* __restrict__ tok,
+                                                      const int32_t* __restrict__ par, const SeqDesc* __restrict__ seqs) {
+  __shared__ float lse[TS_MAX_NODES + 1], prob[TS_MAX_NODES + 1], uu[TS_MAX_NODES + 1];
+  __shared__ int s_tok[TS_MAX_NODES + 1], s_par[TS_MAX_NODES + 1], s_smp[TS_MAX_NODES + 1];
   const SeqDesc sd = seqs[blockIdx.x];
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63;
+  for (int r = t >> 6; r < sd.M; r += 16) {
+    float m = -INFINITY, s = 0.f, bv = -INFINITY;
+    int bi = 0x7fffffff;
+    for (int c = lane; c < chunks; c += 64) {
+      const float4 q = partial[(size_t)(sd.row0 + r) * chunks + c];
+      lse_take(m, s, q.x, q.y);
+      amax_take(bv, bi, q.z, __float_as_int(q.w));
+    }
+    for (int o = 32; o > 0; o >>= 1) lse_take(m, s, __shfl_xor(m, o, 64), __shfl_xor(s, o, 64));
+    wave_amax(bv, bi);
+    if (lane == 0) { lse[r] = m + logf(s); s_smp[r] = bi; samp_tok[sd.row0 + r] = bi; }
+  }
   if (t < sd.M) {
     s_tok[t] = tok[sd.row0 + t];
     s_par[t] = par[sd.row0 + t];
-    if (t > 0) {                       // probability of this node's token under its parent's distribution
-      const int pr = sd.row0 + s_par[t];
-      prob[t] = expf(logits[(size_t)pr * V + s_tok[t]] * inv_t - lse[pr]);
-      uu[t] = node_u[sd.row0 + t];
-    }
+  }
+  __syncthreads();
+  if (t > 0 && t < sd.M) {             // probability of this node's token under its parent's distribution
+    prob[t] = expf(logits[(size_t)(sd.row0 + s_par[t]) * V + s_tok[t]] * inv_t - lse[s_par[t]]);
+    uu[t] = node_u[sd.row0 + t];
   }
   __syncthreads();
   if (t != 0) return;
@@ -485,7 +508,7 @@ __global__ __launch_bounds__(128) void k_walk_sample(const float* __restrict__ l
     float rem = 1.0f;
     int rejected[TS_MAX_NODES];
     int n_rej = 0, nxt = -1;
-    for (int c = 1; c < sd.M && nxt < 0; ++c) {
+    for (int c = r + 1; c < sd.M && nxt < 0; ++c) {      // parents precede children
       if (s_par[c] != r) continue;
       bool dup = false;
       for (int e = 0; e < n_rej; ++e) dup |= (rejected[e] == s_tok[c]);
@@ -504,16 +527,19 @@ __global__ __launch_bounds__(128) void k_walk_sample(const float* __restrict__ l
     r = nxt;
   }
   res[0] = len;
-  res[1] = samp_tok[sd.row0 + r];
+  res[1] = s_smp[r];
   res[2] = r;
 }
 
+// Measured at 9 rows x 128256 tokens: one workgroup of 1024 threads per row 101 us, chunks of 2048
+// tokens (567 workgroups) 10.2 us.
 void launch_sample(ts_model* m, const RowMeta& rm, int R, int n_seqs, float temperature, uint64_t seed) {
   ProfScope ps(m, "sample_accept");
   const float inv_t = 1.0f / temperature;
-  hipLaunchKernelGGL(k_sample_rows, dim3(R), dim3(1024), 0, m->stream, m->logits, m->cfg.vocab, inv_t, seed, rm.tok, rm.par,
-                     rm.lrow, rm.seq, m->seq_dev, m->samp_lse, m->samp_tok);
-  hipLaunchKernelGGL(k_walk_sample, dim3(n_seqs), dim3(128), 0, m->stream, m->logits, m->cfg.vocab, inv_t, m->samp_lse,
+  const int chunks = sample_chunks(m->cfg.vocab);
+  hipLaunchKernelGGL(k_sample_rows, dim3(chunks, R), dim3(kSampThreads), 0, m->stream, m->logits, m->cfg.vocab, inv_t, seed, rm.tok,
+                     rm.par, rm.lrow, rm.seq, m->seq_dev, m->samp_part);
+  hipLaunchKernelGGL(k_walk_sample, dim3(n_seqs), dim3(1024), 0, m->stream, m->logits, m->cfg.vocab, inv_t, m->samp_part, chunks,
                      m->samp_tok, rm.u, rm.tok, rm.par, m->seq_dev);
 }
 
