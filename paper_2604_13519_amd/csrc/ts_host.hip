@@ -157,11 +157,12 @@ static void free_workspace(ts_model* m) {
   dev_free(m->attn_part_o); dev_free(m->attn_part_ml); dev_free(m->rope_cs); dev_free(m->row_dst); dev_free(m->amax_val);
   dev_free(m->amax_idx); dev_free(m->logits); dev_free(m->meta_dev); dev_free(m->seq_dev);
   dev_free(m->samp_part); dev_free(m->samp_tok);
-  if (m->meta_host) (void)hipHostFree(m->meta_host);
+  if (m->rec_host) (void)hipHostFree(m->rec_host);
+  if (m->seq_host) (void)hipHostFree(m->seq_host);
   if (m->res_host) (void)hipHostFree(m->res_host);
   m->H = nullptr; m->Xn = m->Qb = m->Ab = m->Fb = nullptr; m->part = nullptr;
   m->attn_part_o = nullptr; m->attn_part_ml = nullptr; m->rope_cs = nullptr; m->row_dst = nullptr; m->amax_val = nullptr; m->amax_idx = nullptr;
-  m->logits = nullptr; m->meta_dev = nullptr; m->seq_dev = nullptr; m->meta_host = nullptr; m->res_host = nullptr;
+  m->logits = nullptr; m->meta_dev = nullptr; m->seq_dev = nullptr; m->rec_host = nullptr; m->seq_host = nullptr; m->res_host = nullptr;
   m->samp_part = nullptr; m->samp_tok = nullptr;
   m->ws_rows = 0; m->ws_seqs = 0; m->logits_rows = 0; m->attn_max_splits = 0; m->part_elems = 0;
 }
@@ -212,10 +213,11 @@ static ts_status ensure_workspace(ts_model* m, int rows, int seqs, bool want_log
     // stochastic acceptance takes one sequence per call
     if ((st = dev_alloc_bytes((void**)&m->samp_part, (size_t)(TS_MAX_NODES + 1) * sample_chunks(c.vocab) * sizeof(float4), true))) return st;
     if ((st = dev_alloc_bytes((void**)&m->samp_tok, (size_t)alloc_rows * 4, true))) return st;
-    m->meta_bytes = meta_bytes_for(alloc_rows);
-    if ((st = dev_alloc_bytes(&m->meta_dev, m->meta_bytes, true))) return st;
+    if ((st = dev_alloc_bytes(&m->meta_dev, meta_bytes_for(alloc_rows), true))) return st;
     if ((st = dev_alloc_bytes((void**)&m->seq_dev, (size_t)scap * sizeof(SeqDesc), true))) return st;
-    TS_HIP(hipHostMalloc(&m->meta_host, m->meta_bytes + (size_t)scap * sizeof(SeqDesc), hipHostMallocDefault));
+    // pinned and device-visible: the row set-up kernel reads the first two, the walk writes the third
+    TS_HIP(hipHostMalloc((void**)&m->rec_host, (size_t)alloc_rows * sizeof(RowRec), hipHostMallocDefault));
+    TS_HIP(hipHostMalloc((void**)&m->seq_host, (size_t)scap * sizeof(SeqDesc), hipHostMallocDefault));
     TS_HIP(hipHostMalloc((void**)&m->res_host, (size_t)scap * TS_RESULT_INTS * sizeof(int32_t), hipHostMallocDefault));
     m->ws_rows = cap;
     m->ws_seqs = scap;
@@ -387,7 +389,7 @@ extern "C" ts_status ts_model_load(const ts_model_config* cfg, const ts_weights*
   m->H = nullptr; m->Xn = m->Qb = m->Ab = m->Fb = nullptr; m->part = nullptr; m->part_elems = 0;
   m->attn_part_o = nullptr; m->attn_part_ml = nullptr; m->attn_max_splits = 0;
   m->rope_cs = nullptr; m->row_dst = nullptr; m->amax_val = nullptr; m->amax_idx = nullptr; m->logits = nullptr;
-  m->keep_logits = false; m->logits_rows = 0; m->meta_dev = nullptr; m->meta_host = nullptr; m->meta_bytes = 0;
+  m->keep_logits = false; m->logits_rows = 0; m->meta_dev = nullptr; m->rec_host = nullptr; m->seq_host = nullptr;
   m->seq_dev = nullptr; m->res_host = nullptr; m->ws_rows = 0; m->ws_seqs = 0;
   m->samp_part = nullptr; m->samp_tok = nullptr;
   m->prof_on = false; m->ev_used = 0; m->last_rows = 0;
@@ -787,35 +789,37 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
   if ((st = ensure_attn_partials(m, splits, R))) return st;
 
   // ---- per-row bookkeeping (Alg. 1: flattened sequence + tree mask) ------------------
-  const int alloc_rows = m->ws_rows + TS_MROWS_PER_BLOCK;
-  RowMeta hm = carve_meta(m->meta_host, alloc_rows);
-  RowMeta dm = carve_meta(m->meta_dev, alloc_rows);
-  SeqDesc* hseq = (SeqDesc*)((char*)m->meta_host + m->meta_bytes);
+  const RowMeta dm = carve_meta(m->meta_dev, m->ws_rows + TS_MROWS_PER_BLOCK);
+  const size_t page_elems = (size_t)c.n_kv_heads * TS_PAGE_SIZE * c.head_dim;
   int r0 = 0;
   for (int s = 0; s < n_seqs; ++s) {
     ts_kv* kv = kvs[s];
     const int n = offs[s + 1] - offs[s];
     const int P_s = blocks ? blocks->P[s] : kv->P;
-    hm.tok[r0] = blocks ? blocks->root[s] : kv->pending; hm.pos[r0] = P_s; hm.seq[r0] = s; hm.lrow[r0] = 0;
-    hm.par[r0] = -1; hm.depth[r0] = 0; hm.anc[r0] = 0; hm.u[r0] = 0.f;
-    for (int i = 0; i < n; ++i) {
-      const int r = r0 + i + 1;
-      const int prow = pars[offs[s] + i] + 1;             // local parent row
-      hm.tok[r] = toks[offs[s] + i];
-      hm.seq[r] = s; hm.lrow[r] = i + 1; hm.par[r] = prow;
-      hm.depth[r] = hm.depth[r0 + prow] + 1;
-      hm.pos[r] = P_s + hm.depth[r];
-      hm.anc[r] = hm.anc[r0 + prow] | (1ull << i);
-      hm.u[r] = sample ? sample->node_uniform[offs[s] + i] : 0.f;
+    for (int i = 0; i <= n; ++i) {                        // row 0 = root, row i = node i - 1
+      RowRec& q = m->rec_host[r0 + i];
+      const int node = offs[s] + i - 1, prow = i ? pars[node] + 1 : -1;      // local parent row
+      const RowRec& up = m->rec_host[r0 + std::max(prow, 0)];
+      q.anc = i ? up.anc | (1ull << (i - 1)) : 0;
+      q.depth = i ? up.depth + 1 : 0;
+      q.tok = i ? toks[node] : blocks ? blocks->root[s] : kv->pending;
+      q.pos = P_s + q.depth;
+      q.seq = s; q.lrow = i; q.par = prow;
+      q.u = sample && i ? sample->node_uniform[node] : 0.f;
+      // the row's slot in layer 0; a layer adds layer_stride elements, a KV head 16 * head_dim
+      const int slot = P_s + i;
+      const size_t page = (size_t)kv->page_table_host[slot / TS_PAGE_SIZE] * page_elems;
+      q.dst.k = (char*)kv->k_pool + (page + (size_t)(slot % TS_PAGE_SIZE) * c.head_dim) * m->esz;
+      q.dst.v = (char*)kv->v_pool + (page + slot % TS_PAGE_SIZE) * m->esz;
+      q.dst.layer_stride = (size_t)kv->pool_pages * page_elems;
     }
-    SeqDesc& sd = hseq[s];
+    SeqDesc& sd = m->seq_host[s];
     sd.P = P_s; sd.M = n + 1; sd.row0 = r0; sd.n_pages = kv->pool_pages;
     sd.page_table = kv->page_table; sd.k_pool = kv->k_pool; sd.v_pool = kv->v_pool; sd.result = kv->result;
+    sd.host_result = m->res_host + (size_t)s * TS_RESULT_INTS;
     kv->have_result = false;
     r0 += n + 1;
   }
-  TS_HIP(hipMemcpyAsync(m->meta_dev, m->meta_host, m->meta_bytes, hipMemcpyHostToDevice, m->stream));
-  TS_HIP(hipMemcpyAsync(m->seq_dev, hseq, (size_t)n_seqs * sizeof(SeqDesc), hipMemcpyHostToDevice, m->stream));
 
   // ---- the pass ---------------------------------------------------------------------
   m->prof.clear();
@@ -825,7 +829,7 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
   const bool time_pass = m->prof_on && m->prof_filter == "verify_pass";
   if (time_pass) prof_begin(m, "verify_pass");
   const size_t pass_rec = m->prof.size();
-  launch_embed(m, dm, R);       // + rotary table and K/V destinations of the rows
+  launch_embed(m, dm, R, n_seqs);       // + row metadata to the device, rotary table
   int pending_parts = 0;          // split-K partials of the previous projection still to be added to H
   size_t pending_stride = 0;
   auto project = [&](const char* name, const void* X, const void* W, int N, int K, int* n_parts, size_t* stride) {
@@ -887,8 +891,6 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
   else launch_walk(m, dm, R, n_seqs);
   if (time_pass && pass_rec >= 1) TS_HIP(hipEventRecord(m->prof[pass_rec - 1].b, m->stream));
   TS_HIP(hipGetLastError());
-  for (int s = 0; s < n_seqs; ++s)
-    TS_HIP(hipMemcpyAsync(m->res_host + (size_t)s * TS_RESULT_INTS, kvs[s]->result, TS_RESULT_INTS * 4, hipMemcpyDeviceToHost, m->stream));
   TS_HIP(hipStreamSynchronize(m->stream));
   m->last_rows = R;
 

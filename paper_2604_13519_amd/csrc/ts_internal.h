@@ -48,6 +48,7 @@ struct SeqDesc {
   void* k_pool;          // device, K pages  [L][n_pages][Hkv][16][hd]
   void* v_pool;          // device, V pages  [L][n_pages][Hkv][hd][16]  (transposed in-page)
   int32_t* result;       // device, [0]=accept_len [1]=bonus [2]=best_row, [4..4+64) rows, [68..132) tokens
+  int32_t* host_result;  // the same for the caller: pinned host memory, written by the walk itself
 };
 constexpr int TS_RESULT_INTS = 4 + 2 * TS_MAX_NODES;
 
@@ -57,6 +58,17 @@ struct RowDst {
   void* v;                 // V page column of the slot: + layer * layer_stride + g * hd * 16 + dim * 16
   size_t layer_stride;     // elements per layer of the sequence's pools
 };
+
+// What the host writes per row of a pass, in pinned memory: one 64-byte line, fetched over the bus by
+// the row set-up kernel, which spreads it over the device arrays (RowMeta, RowDst).
+struct RowRec {
+  uint64_t anc;
+  RowDst dst;
+  int32_t tok, pos, seq, lrow, par, depth;
+  float u;
+  int32_t pad;
+};
+static_assert(sizeof(RowRec) == 64, "one line per row");
 
 struct ProfRec { const char* name; hipEvent_t a, b; };
 
@@ -123,8 +135,10 @@ struct ts_model {
   float* logits; bool keep_logits; int logits_rows;     // [rows][V] when kept
   int32_t* samp_tok;                                    // per-row token (greedy arg-max or residual sample)
   float4* samp_part;                                    // [TS_MAX_NODES + 1][sample_chunks(V)] (max, sum, best score, token)
-  // per-call metadata (device + pinned host mirror)
-  void* meta_dev; void* meta_host; size_t meta_bytes;
+  // per-call metadata: the host writes records and descriptors into pinned memory, the row set-up
+  // kernel moves them to the device arrays
+  void* meta_dev;               // carved into RowMeta
+  RowRec* rec_host; SeqDesc* seq_host;      // pinned, [rows], [ws_seqs]
   SeqDesc* seq_dev;
   int32_t* res_host;            // pinned, ws_seqs * TS_RESULT_INTS
   // profiling
@@ -140,7 +154,7 @@ struct ts_model {
 // misc kernels (ts_kernels_misc.hip)
 void launch_repack_tiles(hipStream_t s, const bf16_t* src, f16_t* dst, int N, int K, int n_tile0, int n_tile_stride,
                          int* range_flag);
-void launch_embed(ts_model* m, const RowMeta& rm, int R);
+void launch_embed(ts_model* m, const RowMeta& rm, int R, int n_seqs);
 void launch_norm(ts_model* m, int R, const float* gain, int n_parts, size_t part_stride, bool first);
 void launch_rope_kv(ts_model* m, const RowMeta& rm, int R, int layer, int n_parts, size_t part_stride);
 void launch_plain_read(ts_model* m, const void* src, size_t bytes, uint32_t* sink);
