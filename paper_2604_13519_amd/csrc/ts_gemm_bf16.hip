@@ -16,7 +16,7 @@
 //    double-buffered LDS chunk and read as A operands with 16-byte LDS loads.
 //  * K is split two ways.  Inside a workgroup, KW waves share the same output columns and take
 //    alternate k-steps of every chunk; their accumulators are added through LDS in a fixed
-//    order at the end.  Across workgroups (grid.y), partial sums go to a fp32
+//    order at the end.  Across workgroups, partial sums go to a fp32
 //    [split][row][col] buffer that the next row-wise kernel adds up in a fixed order
 //    (deterministic, no atomics).  The in-workgroup split costs no memory traffic, the
 //    cross-workgroup one costs a write and a read of the partial sums, so the planner uses as
@@ -53,6 +53,7 @@ struct GemmArgs {
   int kt_count;        // K / 32
   size_t split_stride; // R * N
   int amax_parts;
+  int groups, splits;  // column groups x K splits workgroups per row block
 };
 
 enum { MODE_PARTIAL = 0, MODE_ARGMAX = 1, MODE_SWIGLU = 2 };
@@ -82,8 +83,17 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l15 = lane & 15, g = lane >> 4;
   const int cs = wave / KW, kq = wave % KW;
-  const int row0 = blockIdx.z * TS_MROWS_PER_BLOCK;
-  const int kbase0 = blockIdx.y * a.kper;
+  // Place: workgroups are dealt to the 8 XCDs round robin by id.  Each XCD takes a contiguous run of the
+  // (split, column group) pairs in split order: it reads neighbouring weight tiles, and only the
+  // activations of one or two K splits pass through its L2 instead of all of them.  Against column
+  // groups dealt round robin (8B shape): 1 row gate/up 42.1 -> 38.4, QKV 12.5 -> 12.8, O + down 32.3 -> 32.0 us;
+  // 17 rows down 21.7 -> 20.8, O 9.9 -> 9.0; 65 rows within 1 us either way.
+  const int units = a.groups * a.splits;
+  const int unit = (blockIdx.x & 7) * ((units + 7) / 8) + (blockIdx.x >> 3);
+  if (unit >= units) return;
+  const int group = unit % a.groups, split = unit / a.groups;
+  const int row0 = blockIdx.y * TS_MROWS_PER_BLOCK;
+  const int kbase0 = split * a.kper;
   const int n_chunks = a.kper / KC;
 
   // Addresses are (uniform 64-bit base) + (32-bit per-lane byte offset that never changes):
@@ -93,7 +103,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   int nt_idx[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    nt_idx[t] = (blockIdx.x * CS + cs_u) * NT + t;
+    nt_idx[t] = (group * CS + cs_u) * NT + t;
     const int c = nt_idx[t] < a.n_tiles ? nt_idx[t] : a.n_tiles - 1;   // idle waves re-read a valid tile
     wbase[t] = reinterpret_cast<const char*>(a.Wt) + ((size_t)c * a.kt_count + kbase0 / 32 + kq_u * KSW) * 1024;
   }
@@ -208,7 +218,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
           st_act_planes(a.act_out + (size_t)row * (a.N / 2) + f, a.act_plane, gv / (1.0f + expf(-gv)) * uv, a.sat);
         }
       } else {
-        float* o = a.out + (size_t)blockIdx.y * a.split_stride;
+        float* o = a.out + (size_t)split * a.split_stride;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           const int col = nt_idx[t] * 16 + l15;
@@ -283,8 +293,8 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
       float bv = rv[0][tid];
       int bi = ri[0][tid];
       for (int wv = 1; wv < WAVES; ++wv) amax_take(bv, bi, rv[wv][tid], ri[wv][tid]);
-      a.aval[(size_t)(row0 + tid) * a.amax_parts + blockIdx.x] = bv;
-      a.aidx[(size_t)(row0 + tid) * a.amax_parts + blockIdx.x] = bi;
+      a.aval[(size_t)(row0 + tid) * a.amax_parts + group] = bv;
+      a.aidx[(size_t)(row0 + tid) * a.amax_parts + group] = bi;
     }
   }
 }
@@ -409,7 +419,8 @@ void launch_gemm_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, 
   const int groups = (N + cols - 1) / cols;
   const int m_blocks = (R + TS_MROWS_PER_BLOCK - 1) / TS_MROWS_PER_BLOCK;
   const int mt = m_blocks > 1 ? 5 : (R + 15) / 16;
-  dim3 grid(groups, splits, m_blocks);
+  a.groups = groups; a.splits = splits;
+  dim3 grid((groups * splits + 7) / 8 * 8, m_blocks);
   if (mode == MODE_ARGMAX) launch_shape<MODE_ARGMAX>(plan.shape, mt, grid, m->stream, a);
   else if (mode == MODE_SWIGLU) launch_shape<MODE_SWIGLU>(plan.shape, mt, grid, m->stream, a);
   else launch_shape<MODE_PARTIAL>(plan.shape, mt, grid, m->stream, a);
