@@ -19,8 +19,7 @@
 // MFMA formulation, chosen so that no operand needs a transpose or a cross-lane shuffle:
 //   S^T[key][query] = K . Q^T     A = K tile from LDS (16 keys x 32 dims per step)
 //                                 B = Q fragments, resident in registers
-//   lane l then holds query (l % 16) and 4 keys of each 16-key tile, so the soft-max
-//   maximum over keys is an in-lane max plus two lane swaps (16, 32), and the exponentials
+//   lane l then holds query (l % 16) and 4 keys of each 16-key tile, and the exponentials
 //   of two 16-key tiles pack straight into the B operand of
 //   O^T[dim][query] += V^T . P^T  A = V^T tile from LDS.  V pages are stored transposed in
 //                                 the cache ([head_dim][16 tokens]) exactly for this.
@@ -39,6 +38,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 namespace {
 
@@ -64,7 +64,17 @@ __device__ __forceinline__ u32x4 to_half8(u32x4 v) {
 // 2^kRefSlack at most (half holds 2^15), every rescale stays an exact power of two, and the O
 // rescale - 32 multiplies per row tile whenever any row of the wave moves its reference - runs a
 // few times per row instead of at most half blocks of a long context.
-constexpr float kRefSlack = 8.f;
+// The probabilities are taken against the reference as it stands, and only their largest is looked
+// at, in packed halves over all row tiles of a wave (4 instructions per tile and 32 keys; the maximum
+// of the scores over a row's lanes, taken before the exponentials, was 20): one above 2^kRefSlack
+// sends the wave through the path that moves references.  A row without a reference yet has kNoRef,
+// which makes any visible score overflow to +inf and any masked one 0.
+// Measured (with the two 32-key halves unrolled): 65 rows x 8 heads per KV head x 32768 keys x 4
+// sequences 514 -> 416 us, 33 rows x 16 sequences 114 -> 106 us, 38 rows x 23011 keys 43.3 -> 40.0 us,
+// 65 rows x 8192 keys 27.0 -> 25.3 us.  What bounds the loop now is the LDS: with the K and V^T fragment
+// reads compiled out the first of these takes 287 us, without the staging 341 us, without the
+// exponentials 398 us.
+constexpr float kRefSlack = 8.f, kRefLimit = 256.f, kNoRef = -1e30f;
 
 union Pack8 {
   f16x8 v;
@@ -187,12 +197,12 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
     anc[mt] = lrow < M ? a.row_anc[sd.row0 + lrow] : 0ull;
   }
 
-  f32x4 o[DT][MT];
-  float m_run[MT], l_run[MT];
+  f32x4 o[DT][MT], l_run[MT];              // l_run: the row sum, the same in all four elements
+  float m_run[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    m_run[mt] = -INFINITY;
-    l_run[mt] = 0.f;
+    m_run[mt] = kNoRef;
+    l_run[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[dt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -225,7 +235,7 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
     // Two sub-blocks of 32 keys (2 pages) each: scores, mask, running soft-max, P.V.
     const int key0 = blk * KB;
     const bool masked = key0 + KB > P;
-#pragma unroll 1   // keeping the two halves rolled holds the register need at 256
+#pragma unroll
     for (int k2 = 0; k2 < 2; ++k2) {
       // ---- S^T = K . Q^T -----------------------------------------------------------
       // With FD > 0 the K fragments come from LDS through a short software pipeline, FD of them
@@ -278,50 +288,46 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
           }
       }
 
-      // ---- running soft-max on raw scores; a.scale = log2(e)/sqrt(hd) folds into the exponent ---
+      // ---- probabilities against the reference as it stands (see kRefSlack); a.scale =
+      //      log2(e)/sqrt(hd) folds into the exponent
       Pack8 pb[MT];
-      float alpha[MT];
-      bool rescale = false;
+      f16x2 top = {(_Float16)0.f, (_Float16)0.f};
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        float mx = -INFINITY;
 #pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[kt][mt][r]);
-        mx = max_over_lane_groups(mx);
-        // the running reference is a whole number (scores in log2 units) that follows the
-        // rounded-up maximum lazily (kRefSlack): every rescale is an exact power of two, which
-        // commutes with the half rounding of the probabilities, so blocking and splitting of the
-        // keys can change a probability only where it falls into half's subnormal range (below
-        // 2^-14 of the reference's scale)
-        const float m_ceil = ceilf(mx * a.scale);
-        const float m_new = (m_ceil > m_run[mt] + kRefSlack) ? m_ceil : m_run[mt];
-        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-        alpha[mt] = __builtin_amdgcn_exp2f(m_run[mt] - m_use);
-        rescale |= (m_new != m_run[mt]);
-        m_run[mt] = m_new;
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-          for (int r = 0; r < 4; r += 2)
-            pb[mt].u[kt * 2 + (r >> 1)] = pack_f16x2(__builtin_amdgcn_exp2f(fmaf(s[kt][mt][r], a.scale, -m_use)),
-                                                      __builtin_amdgcn_exp2f(fmaf(s[kt][mt][r + 1], a.scale, -m_use)));
+        for (int i = 0; i < 4; ++i) {
+          pb[mt].u[i] = pack_f16x2(__builtin_amdgcn_exp2f(fmaf(s[i >> 1][mt][(i & 1) * 2], a.scale, -m_run[mt])),
+                                   __builtin_amdgcn_exp2f(fmaf(s[i >> 1][mt][(i & 1) * 2 + 1], a.scale, -m_run[mt])));
+          top = __builtin_elementwise_max(top, __builtin_bit_cast(f16x2, pb[mt].u[i]));
+        }
       }
-      // the reference moves rarely after the first blocks: skip the O rescale when no row's did
-      if (__builtin_amdgcn_ballot_w64(rescale) != 0ull) {
+      // some score of the wave beyond the slack: move the references of those rows and start over
+      if (__builtin_amdgcn_ballot_w64(fmaxf((float)top[0], (float)top[1]) > kRefLimit) != 0ull) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int mt = 0; mt < MT; ++mt) {
+          float mx = -INFINITY;
 #pragma unroll
-          for (int dt = 0; dt < DT; ++dt) o[dt][mt] *= alpha[mt];
+          for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[kt][mt][r]);
+          const float m_ceil = ceilf(max_over_lane_groups(mx) * a.scale);
+          const float m_new = (m_ceil > m_run[mt] + kRefSlack) ? m_ceil : m_run[mt];
+          const float alpha = __builtin_amdgcn_exp2f(m_run[mt] - m_new);
+          m_run[mt] = m_new;
+#pragma unroll
+          for (int dt = 0; dt < DT; ++dt) o[dt][mt] *= alpha;
+          l_run[mt] *= alpha;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            pb[mt].u[i] = pack_f16x2(__builtin_amdgcn_exp2f(fmaf(s[i >> 1][mt][(i & 1) * 2], a.scale, -m_new)),
+                                     __builtin_amdgcn_exp2f(fmaf(s[i >> 1][mt][(i & 1) * 2 + 1], a.scale, -m_new)));
+        }
       }
 
       // ---- O^T += V^T . P^T ; row sums of the rounded probabilities from an all-ones operand ---
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const f32x4 ps = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones.v, pb[mt].v, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        l_run[mt] = fmaf(l_run[mt], alpha[mt], ps[0]);
-      }
+      for (int mt = 0; mt < MT; ++mt)
+        l_run[mt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones.v, pb[mt].v, l_run[mt], 0, 0, 0);
       if (FD > 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
@@ -345,12 +351,12 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
   // bounds this epilogue and the merge kernel.
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
-    const float l = l_run[mt];     // already the sum over all keys (MFMA reduces over the lane groups)
+    const float l = l_run[mt][0];  // already the sum over all keys (MFMA reduces over the lane groups)
     const int lrow = (tile0 + mt) * 16 + l15;
     if (lrow < M) {
       const size_t base = ((size_t)(sd.row0 + lrow) * a.Hq + h) * a.splits + split;
       if (g4 == 0) {
-        a.part_ml[base * 2 + 0] = m_run[mt];
+        a.part_ml[base * 2 + 0] = m_run[mt] == kNoRef ? -INFINITY : m_run[mt];
         a.part_ml[base * 2 + 1] = l;
       }
       const float inv = l > 0.f ? 1.0f / l : 0.f;
