@@ -80,11 +80,15 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[SMEM_BYTES];
   f16_t (*xs)[PL][MT * 16][XS] = reinterpret_cast<f16_t (*)[PL][MT * 16][XS]>(smem);
 
-  // place: XCD = blockIdx.x % 8; the row blocks of a weight slab follow each other on one XCD
-  const int xcd = blockIdx.x & 7, rest = blockIdx.x >> 3;
-  const int rb = rest % a.n_rblocks;
-  const int unit = (rest / a.n_rblocks) * 8 + xcd;
-  if (unit >= a.n_units) return;
+  // place: XCD = blockIdx.x % 8; each takes an equal, contiguous run of the (weight slab, row block)
+  // pairs, so that the row blocks of a slab follow each other on one XCD (two at a run's ends).  Whole
+  // slabs dealt round robin loaded the XCDs unevenly (12 slabs: 2 on four of them, 1 on the others), and
+  // the planner paid for it with K splits: 2048 rows x 6144 columns 180.4 us and four partial sums to
+  // re-read (20.4 instead of 36.2 us in k_rope_kv now), 178.4 us and one.
+  const int wgs = a.n_units * a.n_rblocks;
+  const int place = (blockIdx.x & 7) * ((wgs + 7) / 8) + (blockIdx.x >> 3);
+  if (place >= wgs) return;
+  const int rb = place % a.n_rblocks, unit = place / a.n_rblocks;
   const int group = unit % a.n_groups, split = unit / a.n_groups;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -359,7 +363,7 @@ bool gemm_rows_plan(const ts_model* m, int R, int N, int K, int mode, size_t max
         if (chunks % s) continue;
         if (mode != MODE_PARTIAL && s > 1) break;
         if (s > 1 && (size_t)s * R * N > max_part_elems) break;
-        const long wgs = (long)((groups * s + 7) / 8) * 8 * n_rblocks;
+        const long wgs = (long)groups * s * n_rblocks;
         // the 4-row-tile kernels with one or two k-waves need half the registers and LDS of a CU:
         // two workgroups share one
         const int wg_per_cu = (cfg <= 1 && mt <= 4) ? 2 : 1;
@@ -399,7 +403,7 @@ void launch_gemm_rows_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* 
   a.n_groups = (N + cols - 1) / cols;
   a.n_units = a.n_groups * splits;
   a.n_rblocks = ((R + 15) / 16 + mt - 1) / mt;
-  dim3 grid((unsigned)((a.n_units + 7) / 8) * 8 * a.n_rblocks);
+  dim3 grid((unsigned)(a.n_units * a.n_rblocks + 7) / 8 * 8);
   if (mode == MODE_ARGMAX) m->amax_used = a.n_groups;       // partials the combine kernel has to look at
   if (mode == MODE_SWIGLU) launch_mt<MODE_SWIGLU>(mt, cfg, grid, m->stream, a);
   else if (mode == MODE_ARGMAX) launch_mt<MODE_ARGMAX>(mt, cfg, grid, m->stream, a);
