@@ -29,6 +29,7 @@
 //    never have to reach memory.
 #include "ts_internal.h"
 #include "ts_device_utils.h"
+#include <algorithm>
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -65,7 +66,6 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   constexpr int KSTEPS = KC / 32;           // MFMA k-steps per chunk
   constexpr int KSW = KSTEPS / KW;          // ... of which this wave multiplies KSW
   static_assert(KSTEPS % KW == 0 && KSW >= 1, "k-steps of a chunk must divide among the k-waves");
-  static_assert(!(ARGMAX && KW != 1), "the arg-max epilogue expects one wave per column set");
   static_assert(MODE != MODE_SWIGLU || NT == 2, "gate and up tiles alternate");
   constexpr int XS = KC + XPAD;             // LDS row stride in elements (+16 B: bank spread, keeps alignment)
   constexpr int NTHR = 64 * WAVES;
@@ -206,93 +206,89 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   for (int b = 0; b < NBUF - 1; ++b)
     if (c0 + b < n_chunks) step(w[b], w[(b + PF) % NBUF], xr[(b + PF) % NBUF], xr[(b + 1) % NBUF], c0 + b);
 
-  if (!ARGMAX) {
-    // value of output (row tile mt, row r of the lane group, tile t) goes to memory
-    auto emit = [&](int mt, int r, const float (&v)[NT]) {
-      const int row = row0 + mt * 16 + g * 4 + r;
-      if (row >= a.R) return;
-      if (MODE == MODE_SWIGLU) {
-        const int f = (nt_idx[0] >> 1) * 16 + l15;           // tiles 2j / 2j+1 = gate / up of features 16j..
-        if (nt_idx[1] < a.n_tiles) {
-          const float gv = v[0], uv = v[NT - 1];
-          st_act_planes(a.act_out + (size_t)row * (a.N / 2) + f, a.act_plane, gv / (1.0f + expf(-gv)) * uv, a.sat);
-        }
-      } else {
-        float* o = a.out + (size_t)split * a.split_stride;
+  // ARGMAX: best (value, column) of every row over the columns of each column set
+  __shared__ float rv[ARGMAX ? CS : 1][ARGMAX ? MT * 16 : 1];
+  __shared__ int ri[ARGMAX ? CS : 1][ARGMAX ? MT * 16 : 1];
+  // value of output (row tile mt, row r of the lane group, tile t) goes to memory
+  auto emit = [&](int mt, int r, const float (&v)[NT]) {
+    const int lrow = mt * 16 + g * 4 + r, row = row0 + lrow;
+    if (ARGMAX) {
+      float bv = -INFINITY;
+      int bi = 0x7fffffff;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int col = nt_idx[t] * 16 + l15;
-          if (nt_idx[t] < a.n_tiles && col < a.N) o[(size_t)row * a.N + col] = v[t];
+      for (int t = 0; t < NT; ++t) {
+        const int col = nt_idx[t] * 16 + l15;
+        if (nt_idx[t] < a.n_tiles && col < a.N) {
+          if (a.logits != nullptr && row < a.R) a.logits[(size_t)row * a.N + col] = v[t];
+          amax_take(bv, bi, v[t], col);
         }
       }
-    };
-    if (KW == 1) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float v[NT];
-#pragma unroll
-          for (int t = 0; t < NT; ++t) v[t] = acc[mt][t][r];
-          emit(mt, r, v);
-        }
+      for (int o = 8; o > 0; o >>= 1) {       // reduce over the 16 lanes that hold this row
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        amax_take(bv, bi, ov, oi);
+      }
+      if (l15 == 0) { rv[cs][lrow] = bv; ri[cs][lrow] = bi; }
+      return;
+    }
+    if (row >= a.R) return;
+    if (MODE == MODE_SWIGLU) {
+      const int f = (nt_idx[0] >> 1) * 16 + l15;           // tiles 2j / 2j+1 = gate / up of features 16j..
+      if (nt_idx[NT - 1] < a.n_tiles) {
+        const float gv = v[0], uv = v[NT - 1];
+        st_act_planes(a.act_out + (size_t)row * (a.N / 2) + f, a.act_plane, gv / (1.0f + expf(-gv)) * uv, a.sat);
+      }
     } else {
-      // add the KW accumulators of a column set through LDS (the activation buffers are free
-      // after the loop's last barrier), one row tile at a time, always in the order kq = 0, 1, ...
-      float* red = reinterpret_cast<float*>(smem);
+      float* o = a.out + (size_t)split * a.split_stride;
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int t = 0; t < NT; ++t) red[((wave * 4 + r) * NT + t) * 64 + lane] = acc[mt][t][r];
-        __syncthreads();
-        for (int r = kq; r < 4; r += KW) {                 // this wave finishes rows r of the tile
-          float v[NT];
-#pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            float sum = 0.f;
-#pragma unroll
-            for (int k = 0; k < KW; ++k) sum += red[(((cs * KW + k) * 4 + r) * NT + t) * 64 + lane];
-            v[t] = sum;
-          }
-          emit(mt, r, v);
-        }
-        __syncthreads();
+      for (int t = 0; t < NT; ++t) {
+        const int col = nt_idx[t] * 16 + l15;
+        if (nt_idx[t] < a.n_tiles && col < a.N) o[(size_t)row * a.N + col] = v[t];
       }
     }
-  } else {
-    __shared__ float rv[WAVES][MT * 16];
-    __shared__ int ri[WAVES][MT * 16];
+  };
+  if (KW == 1) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int row = row0 + mt * 16 + g * 4 + r;
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
+        float v[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) v[t] = acc[mt][t][r];
+        emit(mt, r, v);
+      }
+  } else {
+    // add the KW accumulators of a column set through LDS (the activation buffers are free
+    // after the loop's last barrier), one row tile at a time, always in the order kq = 0, 1, ...
+    float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) red[((wave * 4 + r) * NT + t) * 64 + lane] = acc[mt][t][r];
+      __syncthreads();
+      for (int r = kq; r < 4; r += KW) {                 // this wave finishes rows r of the tile
+        float v[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const int col = nt_idx[t] * 16 + l15;
-          if (nt_idx[t] < a.n_tiles && col < a.N) {
-            const float v = acc[mt][t][r];
-            if (a.logits != nullptr && row < a.R) a.logits[(size_t)row * a.N + col] = v;
-            amax_take(bv, bi, v, col);
-          }
-        }
+          float sum = 0.f;
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {       // reduce over the 16 lanes that hold this row
-          const float ov = __shfl_xor(bv, o, 64);
-          const int oi = __shfl_xor(bi, o, 64);
-          amax_take(bv, bi, ov, oi);
+          for (int k = 0; k < KW; ++k) sum += red[(((cs * KW + k) * 4 + r) * NT + t) * 64 + lane];
+          v[t] = sum;
         }
-        if (l15 == 0) { rv[wave][mt * 16 + g * 4 + r] = bv; ri[wave][mt * 16 + g * 4 + r] = bi; }
+        emit(mt, r, v);
       }
+      __syncthreads();
+    }
+  }
+  if (ARGMAX) {
     __syncthreads();
     if (tid < MT * 16 && row0 + tid < a.R) {
       float bv = rv[0][tid];
       int bi = ri[0][tid];
-      for (int wv = 1; wv < WAVES; ++wv) amax_take(bv, bi, rv[wv][tid], ri[wv][tid]);
+      for (int c = 1; c < CS; ++c) amax_take(bv, bi, rv[c][tid], ri[c][tid]);
       a.aval[(size_t)(row0 + tid) * a.amax_parts + group] = bv;
       a.aidx[(size_t)(row0 + tid) * a.amax_parts + group] = bi;
     }
@@ -315,11 +311,11 @@ void launch_mt(int mt, dim3 grid, hipStream_t s, const GemmArgs& a) {
 // k-waves per workgroup.  All use chunks of 128 k (the LDS holds two buffers of the
 // activation chunk, 43 KiB for 80 rows).  The k-wave shapes hold fewer weight registers
 // per chunk and prefetch two chunks ahead instead of one.
-constexpr int kNumShapes = 5;
-const int kShapeNT[kNumShapes] = {1, 2, 1, 2, 2};
-const int kShapeCS[kNumShapes] = {4, 4, 8, 8, 4};
-const int kShapeKW[kNumShapes] = {1, 1, 1, 1, 2};
-const int kShapeKC[kNumShapes] = {128, 128, 128, 128, 128};
+constexpr int kNumShapes = 6;
+const int kShapeNT[kNumShapes] = {1, 2, 1, 2, 2, 1};
+const int kShapeCS[kNumShapes] = {4, 4, 8, 8, 4, 2};
+const int kShapeKW[kNumShapes] = {1, 1, 1, 1, 2, 4};
+const int kShapeKC[kNumShapes] = {128, 128, 128, 128, 128, 128};
 
 template <int MODE>
 void launch_shape(int shape, int mt, dim3 grid, hipStream_t s, const GemmArgs& a) {
@@ -328,13 +324,14 @@ void launch_shape(int shape, int mt, dim3 grid, hipStream_t s, const GemmArgs& a
     case 1: launch_mt<2, 4, 1, 128, 1, MODE>(mt, grid, s, a); break;
     case 2: if (MODE != MODE_SWIGLU) launch_mt<1, 8, 1, 128, 1, MODE == MODE_SWIGLU ? MODE_PARTIAL : MODE>(mt, grid, s, a); break;
     case 3: launch_mt<2, 8, 1, 128, 1, MODE>(mt, grid, s, a); break;
-    case 4: if (MODE != MODE_ARGMAX) launch_mt<2, 4, 2, 128, 2, MODE == MODE_ARGMAX ? MODE_PARTIAL : MODE>(mt, grid, s, a); break;
+    case 4: launch_mt<2, 4, 2, 128, 2, MODE>(mt, grid, s, a); break;
+    case 5: if (MODE == MODE_ARGMAX) launch_mt<1, 2, 4, 128, 4, MODE_ARGMAX>(mt, grid, s, a); break;
     default: break;
   }
 }
 
 bool shape_supports(int shape, int mode) {
-  if (mode == MODE_ARGMAX) return kShapeKW[shape] == 1;
+  if (shape == 5) return mode == MODE_ARGMAX;          // 32 columns a workgroup: the others split K further instead
   if (mode == MODE_SWIGLU) return kShapeNT[shape] == 2;
   return true;
 }
@@ -349,12 +346,18 @@ int gemm_bf16_cols_per_group(int shape) { return kShapeNT[shape] * kShapeCS[shap
 int gemm_bf16_chunk(int shape) { return shape >= kRowsShape0 ? gemm_rows_chunk((shape - kRowsShape0) % 4) : kShapeKC[shape]; }
 
 // Tile shape and cross-workgroup K splits, from a byte count per CU:
-//   rounds x (weight bytes one workgroup streams)         rounds = ceil(workgroups / CUs)
-// + write and read of the fp32 partial sums, shared by all CUs (only if splits > 1)
-// + a quarter of the activation bytes (both planes) a workgroup stages from L2 per round.
+//   rounds x (weight bytes one workgroup streams + 72 KB)     rounds = ceil(workgroups / CUs); start and finish
+//                                                             of a round cost what 72 KB of streaming do (3 us)
+// + write and read of the fp32 partial sums, shared by all CUs and 15 % dearer (only if splits > 1), at least 5 KB a split:
+//   with few rows the kernel that adds them up pays for their number, not their bytes
+// + 0.3 of the activation bytes (both planes) a workgroup stages from L2 per round.
 // Measured on MI355X, a second round of workgroups costs a full round (the tail does not
 // overlap), which the round count models.  mode: 0 partial sums, 1 arg-max (no split),
 // 2 SwiGLU epilogue (no split).
+// The constants come from a sweep of every (shape, splits) pair of the 8B projections, each with the change
+// of the kernel behind it, between events.  One row, before the two fixed costs and with them: QKV 16 splits
+// in three rounds 14.8 us, 4 splits in one 12.1 us; O 16 splits 14.9 us, 4 splits 8.3 us; down 21.9 and 20.2 us.
+// 17 rows: QKV 17.5 and 14.1 us, down 22.9 and 22.0 us.  65 rows: unchanged plans.
 GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
   if (R > TS_MROWS_PER_BLOCK) {   // batches: the many-row kernel
     int mt, cfg, splits;
@@ -379,14 +382,17 @@ GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
       const long rounds = (wgs + m->n_cu - 1) / m->n_cu;
       const double kper = (double)K / s;
       double cost = rounds * cols * kper * 2.0;
-      if (s > 1) cost += 2.0 * s * R * (double)N * 4.0 / m->n_cu;
-      cost += 0.25 * rounds * rows * kper * 2.0 * TS_ACT_PLANES;
-      // Measured (8B shape, 65 rows): over a long K range the k-wave shape wins by its deeper prefetch
-      // (gate/up, 32 chunks: 56.2 us against 58.1 us for the 4-wave shape of the same columns); over
-      // the short ranges of the split projections its longer prologue and the cross-wave reduction
-      // are not amortised (O, 4 chunks: 17.0 against 15.2 us; QKV, 8 chunks: 21.9 against 21.2 us).
-      if (kper / kc >= 16 ? kShapeCS[shape] * kShapeKW[shape] < 6 : kShapeKW[shape] > 1) cost *= 1.05;
+      if (s > 1) cost += std::max(2.3 * s * R * (double)N * 4.0 / m->n_cu, 5120.0 * s);
+      cost += 0.3 * rounds * rows * kper * 2.0 * TS_ACT_PLANES;
+      // Measured (8B shape): over a long K range the k-wave shape wins by its deeper prefetch (gate/up, 32
+      // chunks, 65 rows: 55.5 us against 57.7 us for the 4-wave shape of the same columns; down, 14 chunks, 1 to
+      // 17 rows 21.7 - 22.9 against 22.2 - 23.8 us, from 38 rows on no more); over the short ranges of the split
+      // projections its longer prologue and the cross-wave reduction are not amortised (O, 4 chunks, 65 rows:
+      // 16.1 against 14.4 us; QKV, 8 chunks: 22.4 against 20.4 us).
+      const bool long_k = kper / kc >= 16 || (kper / kc >= 12 && rows <= 32);
+      if (long_k ? kShapeCS[shape] * kShapeKW[shape] < 6 : kShapeKW[shape] > 1) cost *= 1.05;
       if (kShapeNT[shape] < 2) cost *= 1.05;                     // one tile per wave reads twice the LDS per weight byte
+      cost += rounds * 73728.0;
       if (cost < best_cost) { best_cost = cost; best.shape = shape; best.splits = s; }
     }
   }
