@@ -183,8 +183,9 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
     // LDS operand fragments requested ahead of the MFMAs that consume them; 0 leaves the order to
     // the compiler (which requests a pair, waits, multiplies).  The explicit pipeline pays in the
     // 8-wave variants with two row splits (65 rows: -4 % with 4 query heads per KV head, -9 %
-    // with 8) and loses elsewhere (+8 % at 33 rows with one row split), measured.
-    constexpr int FD = (RS == 2 && HB == 4) ? 3 : 0;
+    // with 8) and with two tiles a wave (17 rows: 11.4 -> 10.7 us); three tiles in 4 waves have no
+    // registers left for it (33 rows: 107 -> 144 us), measured.
+    constexpr int FD = HB == 4 && (RS == 2 || MT0 == 2) ? 3 : 0;
   // resident query fragments and ancestor masks of this wave's head
   f16x8 qf[MT][KSQ];
   uint64_t anc[MT];
