@@ -1,0 +1,72 @@
+"""Projection shapes at the edges of what the planner picks from: inner sizes of one and two 128-wide
+chunks (shorter than every prefetch ring), column counts that leave a column group nearly empty,
+row counts around the 16-row tiles (their padding rows come from a spare row) - and passes of more
+than 80 rows over odd models, whose merge and cache write take the many-row kernels.  Against
+the oracle, with the tolerances of the other parity tests."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from oracle import toolspec_oracle as O
+from paper_2604_13519_amd import binding as B
+import gpu_utils as U
+
+pytestmark = pytest.mark.gpu
+
+
+def _load(**kw):
+    cfg = wl.get_config("small_bf16").with_(name="shape_edges", **kw)
+    w = wl.gen_weights(cfg, 21)
+    model = B.ts_model_load(cfg, w)
+    B.ts_model_keep_logits(model, True)
+    return cfg, w, model, O.OracleModel(cfg, w, cache=True)
+
+
+@pytest.mark.parametrize("kw", [
+    dict(n_layers=2, d_model=128, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=128, vocab=31),     # every K one chunk
+    dict(n_layers=2, d_model=256, n_q_heads=2, n_kv_heads=2, head_dim=128, d_ffn=384, vocab=2081),  # 2 and 3 chunks, one column past 65 groups
+    dict(n_layers=1, d_model=640, n_q_heads=8, n_kv_heads=1, head_dim=64, d_ffn=1152, vocab=97),    # 5 and 9 chunks, 8 heads per KV head
+])
+def test_projection_shapes(kw):
+    cfg, w, model, om = _load(**kw)
+    rng = np.random.default_rng(3)
+    for n, P in ((0, 33), (15, 16), (16, 130), (48, 64), (64, 65)):
+        K, V = wl.gen_context_kv(cfg, P, seed=70 + n)
+        kv, okv = U.make_pair(cfg, model, K, V, int(rng.integers(cfg.vocab)))
+        tok, par = wl.random_tree(n, cfg.vocab, rng)
+        U.check_verify(cfg, model, om, kv, okv, tok, par, label="d%d n%d P%d" % (cfg.d_model, n, P))
+        B.ts_kv_free(kv)
+    B.ts_model_free(model)
+
+
+@pytest.mark.parametrize("hd,hq,hkv,n_seqs", [(64, 16, 4, 5), (128, 16, 2, 9)])
+def test_many_rows_equal_single_passes(hd, hq, hkv, n_seqs):
+    """Batches past 80 rows (and past 4096 (row, head) slots): rows of a ragged batch against the same
+    requests alone, logits within the canary and cache rows within one-step flips."""
+    cfg, w, model, om = _load(n_layers=2, d_model=256, n_q_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ffn=512, vocab=515)
+    rng = np.random.default_rng(hd)
+    nodes = [64 - (i % 3) for i in range(n_seqs)]
+    lens = [3 + 61 * i for i in range(n_seqs)]
+    trees = [wl.random_tree(n, cfg.vocab, rng) for n in nodes]
+    kvs, ctx = [], []
+    for i in range(n_seqs):
+        K, V = wl.gen_context_kv(cfg, lens[i], seed=300 + i)
+        kv = B.ts_kv_alloc(model, lens[i] + 70)
+        B.ts_kv_import(kv, K, V)
+        B.ts_set_pending(kv, i)
+        kvs.append(kv)
+    B.ts_verify_batch(model, kvs, trees)
+    rows = sum(nodes) + n_seqs
+    both = B.ts_get_logits(model, 0, rows, cfg.vocab)
+    cache = [B.ts_kv_export(kv, lens[i], nodes[i] + 1, cfg) for i, kv in enumerate(kvs)]
+    r0 = 0
+    for i, kv in enumerate(kvs):
+        B.ts_verify(model, kv, *trees[i])
+        one = B.ts_get_logits(model, 0, nodes[i] + 1, cfg.vocab)
+        assert U.rel_l2(both[r0:r0 + nodes[i] + 1], one) <= U.TOL_BF16_R
+        k1, v1 = B.ts_kv_export(kv, lens[i], nodes[i] + 1, cfg)
+        for a, b in ((cache[i][0], k1), (cache[i][1], v1)):
+            assert U.rel_l2(wl.bf16_bits_to_f32(a), wl.bf16_bits_to_f32(b)) <= U.TOL_BF16_R
+        r0 += nodes[i] + 1
+        B.ts_kv_free(kv)
+    B.ts_model_free(model)
