@@ -55,7 +55,7 @@ def _gemm_mode(name):
 
 
 def _load(db):
-    """{kernel (split projections: name + ' grid GxS'): {counter: [values]}}"""
+    """{kernel (split projections: name + ' grid WxB'): {counter: [values]}}"""
     cur = sqlite3.connect(db).cursor()
     agg = collections.defaultdict(lambda: collections.defaultdict(list))
     for k, c, v, gx, gy, wx in cur.execute(
@@ -78,7 +78,7 @@ def kernel_kind(name):
         return "gemm_lm_head_argmax"
     if mode == 0:
         grid = name.split(" grid ")[1] if " grid " in name else ""
-        return "gemm_qkv" if grid.startswith("48x") else "gemm_o+gemm_down"
+        return "gemm_qkv" if grid.startswith("192x") else "gemm_o+gemm_down"
     return {"k_attn_bf16": "attn_bf16", "k_attn_merge": "attn_merge", "k_norm": "residual_rmsnorm",
             "k_rope_kv": "rope_kv_write", "k_plain_read": "plain_read"}.get(name.split("<")[0])
 
@@ -142,7 +142,8 @@ def trace_summary(db, workload, command, bench_json=None):
         f.write("`python -m paper_2604_13519_amd.counters trace <results.db> --workload %s`:\n\n    %s\n\n" % (workload, command))
         f.write("Durations are kernel begin-to-end times from the trace; the run also holds model load (k_repack_tiles, k_kv_xfer)\n"
                 "and bench.py's untimed passes.  Template arguments of `k_gemm_bf16`: row tiles, tiles per wave, column sets, k-waves,\n"
-                "chunk, prefetch depth, mode (0 partial sums, 1 arg-max, 2 SwiGLU), LDS pad; `grid GxS` = column groups x K splits.\n\n")
+                "chunk, prefetch depth, mode (0 partial sums, 1 arg-max, 2 SwiGLU), LDS pad; `grid WxB` = workgroups (column groups x K\n"
+                "splits) x row blocks.\n\n")
         f.write("| kernel | calls | total us | avg us | % |\n|---|---:|---:|---:|---:|\n")
         for k, (n, t) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
             if t / total < 0.0005:

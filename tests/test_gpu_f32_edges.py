@@ -33,3 +33,18 @@ def test_f32_tiles(d_model, hq, hkv, hd, ffn, vocab):
         U.check_verify(cfg, model, om, kv, okv, tok, par, label="f32 d%d hd%d n%d P%d" % (d_model, hd, n, P))
         B.ts_kv_free(kv)
     B.ts_model_free(model)
+
+
+def test_f32_attention_at_its_largest_context():
+    """15000 keys, the most the fp32 path takes (scores and page table of a row fill the LDS): the same
+    tree one key further is refused."""
+    cfg, w, model, om = U.get_model("micro_fp32")
+    n, P = 9, 14990
+    K, V = wl.gen_context_kv(cfg, P, seed=8)
+    kv, okv = U.make_pair(cfg, model, K, V, 3, capacity=P + 20)
+    tok, par = wl.random_tree(n, cfg.vocab, np.random.default_rng(1))
+    U.check_verify(cfg, model, om, kv, okv, tok, par, label="f32 15000 keys")
+    with pytest.raises(B.TsError) as e:
+        B.ts_verify(model, kv, np.append(tok, 1), np.append(par, -1))
+    assert e.value.status == B.TS_ERR_KV_CAPACITY
+    B.ts_kv_free(kv)
