@@ -88,7 +88,8 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   // (split, column group) pairs in split order: it reads neighbouring weight tiles, and only the
   // activations of one or two K splits pass through its L2 instead of all of them.  Against column
   // groups dealt round robin (8B shape): 1 row gate/up 42.1 -> 38.4, QKV 12.5 -> 12.8, O + down 32.3 -> 32.0 us;
-  // 17 rows down 21.7 -> 20.8, O 9.9 -> 9.0; 65 rows within 1 us either way.
+  // 17 rows down 21.7 -> 20.8, O 9.9 -> 9.0; 65 rows QKV 17.6 -> 19.0, O 12.9 -> 12.4, down 28.4 -> 28.0, gate/up the
+  // same (column-group-major runs instead: 19.1 for QKV).
   const int units = a.groups * a.splits;
   const int unit = (blockIdx.x & 7) * ((units + 7) / 8) + (blockIdx.x >> 3);
   if (unit >= units) return;
