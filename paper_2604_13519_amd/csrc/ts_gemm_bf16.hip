@@ -54,8 +54,8 @@ struct GemmArgs {
   int kt_count;        // K / 32
   size_t split_stride; // R * N
   int amax_parts;
-  int zero_row;        // a row of X that is never written (the spare rows start there)
-  int groups, splits;  // column groups x K splits workgroups per row block
+  int zero_row;        // where the rows past the last come from (see x_off)
+  int groups, splits;  // column groups x K splits workgroups
 };
 
 enum { MODE_PARTIAL = 0, MODE_ARGMAX = 1, MODE_SWIGLU = 2 };
@@ -94,7 +94,6 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   const int unit = (blockIdx.x & 7) * ((units + 7) / 8) + (blockIdx.x >> 3);
   if (unit >= units) return;
   const int group = unit % a.groups, split = unit / a.groups;
-  const int row0 = blockIdx.y * TS_MROWS_PER_BLOCK;
   const int kbase0 = split * a.kper;
   const int n_chunks = a.kper / KC;
 
@@ -110,17 +109,24 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
     wbase[t] = reinterpret_cast<const char*>(a.Wt) + ((size_t)c * a.kt_count + kbase0 / 32 + kq_u * KSW) * 1024;
   }
   const uint32_t w_lane = lane * 16;
-  const char* xbase = reinterpret_cast<const char*>(a.X) + ((size_t)row0 * a.K + kbase0) * 2;
-  uint32_t x_off[XPT];                      // byte offset of each staged vector within a chunk
+  // The workspace only grows, and a plane of one that held a very large batch passes 4 GiB: the plane is in the
+  // base (a wave's 64 vectors lie in one plane), the lane offset covers the rows of this pass.
+  static_assert(XVP % 64 == 0, "a wave stages from one plane");
+  constexpr int XPP = XVP % NTHR == 0 ? XVP / NTHR : 0;     // staging rounds per plane; 0: a round holds vectors of both
+  const char* xbase = reinterpret_cast<const char*>(a.X) + (size_t)kbase0 * 2;
+  const size_t plane_bytes = a.x_plane * 2;
+  bool x_lo[XPT];                           // which plane (uniform in a wave)
+  uint32_t x_off[XPT];                      // byte offset of each staged vector within its plane and chunk
 #pragma unroll
   for (int p = 0; p < XPT; ++p) {
-    const int v = min(tid + p * NTHR, XV - 1);      // surplus threads re-read the last vector
-    const int pl = v / XVP, rl = (v % XVP) / (KC / 8), cv = v % (KC / 8);
+    const int v = XPP ? tid + (p < XPP ? p : p - XPP) * NTHR : min(tid + p * NTHR, XV - 1);      // surplus threads re-read the last vector
+    const int rl = (v % XVP) / (KC / 8), cv = v % (KC / 8);
     // rows past the last come from one spare row, which is zero: their lines are fetched once (the activations
     // enter a CU through the same port as the weights), and zeros cost the matrix pipes little power.  17 rows
     // (32 before): head of 8192 columns 19.4 -> 16.3 us, gate/up 40.6 -> 39.7 us, O 9.2 -> 8.8 us
-    const int row = row0 + rl < a.R ? rl : a.zero_row - row0;
-    x_off[p] = (uint32_t)((pl * a.x_plane + (size_t)row * a.K + cv * 8) * 2);
+    const int row = rl < a.R ? rl : a.zero_row;
+    x_lo[p] = XPP ? p >= XPP : __builtin_amdgcn_readfirstlane(v / XVP) != 0;
+    x_off[p] = ((uint32_t)row * (uint32_t)a.K + cv * 8) * 2;
   }
 
   f32x4 acc[MT][NT];
@@ -141,9 +147,10 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
             reinterpret_cast<const f16x8*>(wbase[t] + (size_t)chunk * (KSTEPS * 1024) + w_lane + j * 1024));
   };
   auto load_x = [&](u32x4 (&dst)[XPT], int chunk) {
-    const char* xb = xbase + (size_t)chunk * (KC * 2);
+    const char* hi = xbase + (size_t)chunk * (KC * 2);
+    const char* lo = hi + plane_bytes;
 #pragma unroll
-    for (int p = 0; p < XPT; ++p) dst[p] = *reinterpret_cast<const u32x4*>(xb + x_off[p]);   // never predicated, see below
+    for (int p = 0; p < XPT; ++p) dst[p] = *reinterpret_cast<const u32x4*>((x_lo[p] ? lo : hi) + x_off[p]);   // never predicated, see below
   };
   auto store_x = [&](const u32x4 (&src)[XPT], int buf) {
 #pragma unroll
@@ -217,7 +224,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   __shared__ int ri[ARGMAX ? CS : 1][ARGMAX ? MT * 16 : 1];
   // value of output (row tile mt, row r of the lane group, tile t) goes to memory
   auto emit = [&](int mt, int r, const float (&v)[NT]) {
-    const int lrow = mt * 16 + g * 4 + r, row = row0 + lrow;
+    const int row = mt * 16 + g * 4 + r;
     if (ARGMAX) {
       float bv = -INFINITY;
       int bi = 0x7fffffff;
@@ -235,7 +242,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
         const int oi = __shfl_xor(bi, o, 64);
         amax_take(bv, bi, ov, oi);
       }
-      if (l15 == 0) { rv[cs][lrow] = bv; ri[cs][lrow] = bi; }
+      if (l15 == 0) { rv[cs][row] = bv; ri[cs][row] = bi; }
       return;
     }
     if (row >= a.R) return;
@@ -291,12 +298,12 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   }
   if (ARGMAX) {
     __syncthreads();
-    if (tid < MT * 16 && row0 + tid < a.R) {
+    if (tid < MT * 16 && tid < a.R) {
       float bv = rv[0][tid];
       int bi = ri[0][tid];
       for (int c = 1; c < CS; ++c) amax_take(bv, bi, rv[c][tid], ri[c][tid]);
-      a.aval[(size_t)(row0 + tid) * a.amax_parts + group] = bv;
-      a.aidx[(size_t)(row0 + tid) * a.amax_parts + group] = bi;
+      a.aval[(size_t)tid * a.amax_parts + group] = bv;
+      a.aidx[(size_t)tid * a.amax_parts + group] = bi;
     }
   }
 }
@@ -371,12 +378,12 @@ GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
   if (R > TS_MROWS_PER_BLOCK) {   // batches: the many-row kernel
     int mt, cfg, splits;
     const size_t max_part = m->part_elems ? m->part_elems : kRowsPartCap;
-    if (gemm_rows_plan(m, R, N, K, mode, max_part, &mt, &cfg, &splits)) return GemmPlan{kRowsShape0 + mt * 4 + cfg, splits};
+    gemm_rows_plan(m, R, N, K, mode, max_part, &mt, &cfg, &splits);
+    return GemmPlan{kRowsShape0 + mt * 4 + cfg, splits};
   }
   GemmPlan best{mode == MODE_SWIGLU ? 1 : 0, 1};
   double best_cost = 1e300;
-  const int rows = R > TS_MROWS_PER_BLOCK ? TS_MROWS_PER_BLOCK : ((R + 15) / 16) * 16;
-  const int m_blocks = (R + TS_MROWS_PER_BLOCK - 1) / TS_MROWS_PER_BLOCK;   // each streams the weights again
+  const int rows = ((R + 15) / 16) * 16;
   for (int shape = 0; shape < kNumShapes; ++shape) {
     if (!shape_supports(shape, mode)) continue;
     const int kc = kShapeKC[shape];
@@ -387,7 +394,7 @@ GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
     for (int s = 1; s <= chunks && s <= 16; ++s) {
       if (chunks % s) continue;
       if (mode != MODE_PARTIAL && s > 1) break;
-      const long wgs = (long)groups * s * m_blocks;
+      const long wgs = (long)groups * s;
       const long rounds = (wgs + m->n_cu - 1) / m->n_cu;
       const double kper = (double)K / s;
       double cost = rounds * cols * kper * 2.0;
@@ -423,7 +430,9 @@ void launch_gemm_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, 
   a.act_out = act_out;
   a.sat = m->sat_count;
   a.R = R; a.N = N; a.K = K;
-  a.zero_row = m->ws_rows;
+  // the first spare row, which nothing writes; the last real row where 32 bits do not reach the spare ones (those
+  // outputs are not used, a row of zeros is only the cheaper one)
+  a.zero_row = ((size_t)m->ws_rows + 1) * K * 2 < ((size_t)1 << 32) ? m->ws_rows : R - 1;
   const int splits = mode == MODE_PARTIAL ? plan.splits : 1;
   a.kper = K / splits;
   a.n_tiles = (N + 15) / 16;
@@ -433,10 +442,9 @@ void launch_gemm_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, 
   if (mode == MODE_ARGMAX) m->amax_used = (N + gemm_bf16_cols_per_group(plan.shape) - 1) / gemm_bf16_cols_per_group(plan.shape);
   const int cols = gemm_bf16_cols_per_group(plan.shape);
   const int groups = (N + cols - 1) / cols;
-  const int m_blocks = (R + TS_MROWS_PER_BLOCK - 1) / TS_MROWS_PER_BLOCK;
-  const int mt = m_blocks > 1 ? 5 : (R + 15) / 16;
+  const int mt = (R + 15) / 16;
   a.groups = groups; a.splits = splits;
-  dim3 grid((groups * splits + 7) / 8 * 8, m_blocks);
+  dim3 grid((groups * splits + 7) / 8 * 8);
   if (mode == MODE_ARGMAX) launch_shape<MODE_ARGMAX>(plan.shape, mt, grid, m->stream, a);
   else if (mode == MODE_SWIGLU) launch_shape<MODE_SWIGLU>(plan.shape, mt, grid, m->stream, a);
   else launch_shape<MODE_PARTIAL>(plan.shape, mt, grid, m->stream, a);

@@ -108,13 +108,20 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
     wbase[t] = reinterpret_cast<const char*>(a.Wt) + ((size_t)c * a.kt_count + kbase0 / 32 + kq_u * KSW) * 1024;
   }
   const uint32_t w_lane = lane * 16;
-  const char* xbase = reinterpret_cast<const char*>(a.X) + (size_t)kbase0 * 2;
-  uint32_t x_off[XPT];                      // byte offset of each staged vector within a chunk
+  // plane and row block are in the base (a wave's 64 vectors lie in one plane): both can be past 4 GiB in the
+  // workspace of a very large batch; the lane offset covers the 64 to 128 rows of a block
+  static_assert(XVP % 64 == 0, "a wave stages from one plane");
+  constexpr int XPP = XVP % NTHR == 0 ? XVP / NTHR : 0;     // staging rounds per plane; 0: a round holds vectors of both
+  const char* xbase = reinterpret_cast<const char*>(a.X) + ((size_t)row0 * a.K + kbase0) * 2;
+  const size_t plane_bytes = a.x_plane * 2;
+  bool x_lo[XPT];                           // which plane (uniform in a wave)
+  uint32_t x_off[XPT];                      // byte offset of each staged vector within its plane and chunk
 #pragma unroll
   for (int p = 0; p < XPT; ++p) {
-    const int v = min(tid + p * NTHR, XV - 1);
-    const int pl = v / XVP, row = min(row0 + (v % XVP) / (KC / 8), a.x_rows - 1), cv = v % (KC / 8);
-    x_off[p] = (uint32_t)((pl * a.x_plane + (size_t)row * a.K + cv * 8) * 2);
+    const int v = XPP ? tid + (p < XPP ? p : p - XPP) * NTHR : min(tid + p * NTHR, XV - 1);
+    const int row = min((v % XVP) / (KC / 8), a.x_rows - 1 - row0), cv = v % (KC / 8);
+    x_lo[p] = XPP ? p >= XPP : __builtin_amdgcn_readfirstlane(v / XVP) != 0;
+    x_off[p] = ((uint32_t)row * (uint32_t)a.K + cv * 8) * 2;
   }
 
   f32x4 acc[MT][NT];
@@ -134,19 +141,31 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
   const int last_chunk = n_chunks - 1;
 
   // loads are never predicated (a load under an `if` would make every later wait a wait for
-  // everything): past the end they re-request the last chunk
+  // everything): past the end they re-request the last chunk.
+  // The empty asm statements keep the lane offsets 32 bits wide up to the load, which then adds them to the
+  // uniform base itself; left alone the compiler hoists 64-bit lane addresses, a register pair per load, out of
+  // the loop, and with the planes in the base the largest tiles spill around them.  8 tiles x 4 k-waves: 37 -> 1
+  // registers spilled, 2000 rows x 2048 columns x K 2048 78 -> 47 us; the 8B shape at 264 rows: gate/up 133 -> 127 us,
+  // down 68.5 -> 64.0 us, QKV of 130 rows 29.8 -> 26.1 us.
   auto load_w = [&](f16x8 (&dst)[NT][KSW], int chunk) {
     const size_t off = (size_t)min(chunk, last_chunk) * (KSTEPS * 1024);
+    uint32_t wl = w_lane;
+    asm("" : "+v"(wl));
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int j = 0; j < KSW; ++j)
-        dst[t][j] = *reinterpret_cast<const f16x8*>(wbase[t] + off + w_lane + j * 1024);
+        dst[t][j] = *reinterpret_cast<const f16x8*>(wbase[t] + off + wl + j * 1024);
   };
   auto load_x = [&](u32x4 (&dst)[XPT], int chunk) {
-    const char* xb = xbase + (size_t)min(chunk, last_chunk) * (KC * 2);
+    const char* hi = xbase + (size_t)min(chunk, last_chunk) * (KC * 2);
+    const char* lo = hi + plane_bytes;
 #pragma unroll
-    for (int p = 0; p < XPT; ++p) dst[p] = *reinterpret_cast<const u32x4*>(xb + x_off[p]);
+    for (int p = 0; p < XPT; ++p) {
+      uint32_t o = x_off[p];
+      asm("" : "+v"(o));
+      dst[p] = *reinterpret_cast<const u32x4*>((x_lo[p] ? lo : hi) + o);
+    }
   };
   auto store_x = [&](const u32x4 (&src)[XPT], int buf) {
 #pragma unroll
@@ -342,21 +361,17 @@ int gemm_rows_chunk(int cfg) { return kCfgKC[cfg]; }
 // Row tiles per workgroup (4..8: the rows are cut into equal blocks), configuration and K
 // splits with the least modelled time: rounds of workgroups over the CUs x (matrix-core time of
 // a workgroup + a fixed start/finish cost) + traffic of the partial sums.  max_part_elems
-// bounds splits x R x N.  Returns false if K fits no compiled chunk length.
-bool gemm_rows_plan(const ts_model* m, int R, int N, int K, int mode, size_t max_part_elems, int* mt_out, int* cfg_out,
+// bounds splits x R x N.  K is a multiple of 128 (check_config), so every chunk length fits.
+void gemm_rows_plan(const ts_model* m, int R, int N, int K, int mode, size_t max_part_elems, int* mt_out, int* cfg_out,
                     int* splits_out) {
   const int tiles = (R + 15) / 16;
   double best = 1e300;
-  bool found = false;
-  if ((size_t)TS_ACT_PLANES * (R + 2 * TS_MROWS_PER_BLOCK) * K * 2 >= ((size_t)1 << 32)) return false;   // 32-bit activation offsets
   for (int mt = kMinMT; mt <= kMaxMT; ++mt) {
     const int n_rblocks = (tiles + mt - 1) / mt;
     if (mt > kMinMT && n_rblocks == (tiles + mt - 2) / (mt - 1)) continue;   // same blocks, more idle rows
     for (int cfg = 0; cfg < kNumCfg; ++cfg) {
       if (mode == MODE_ARGMAX && cfg != 0) break;
-      const int kc = kCfgKC[cfg];
-      if (K % kc) continue;
-      const int chunks = K / kc;
+      const int chunks = K / kCfgKC[cfg];
       const int cols = kCfgCS[cfg] * NT * 16;
       const int groups = (N + cols - 1) / cols;
       for (int s = 1; s <= chunks && s <= 8; ++s) {
@@ -376,11 +391,10 @@ bool gemm_rows_plan(const ts_model* m, int R, int N, int K, int mode, size_t max
         const double mfma_us = 2.0 * (K / s / 32 / kCfgKW[cfg]) * mt * NT * 16 / 2400.0;
         double cost = rounds * (wg_per_cu * mfma_us / eff + 6.0);
         if (s > 1) cost += s * R * (double)N * 4.0 / 12.0e6;        // partial sums, mostly overlapped with the products
-        if (cost < best) { best = cost; found = true; *mt_out = mt; *cfg_out = cfg; *splits_out = s; }
+        if (cost < best) { best = cost; *mt_out = mt; *cfg_out = cfg; *splits_out = s; }
       }
     }
   }
-  return found;
 }
 
 void launch_gemm_rows_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, int R, int N, int K, int mt, int cfg,

@@ -178,7 +178,7 @@ int gemm_bf16_chunk(int shape);
 void launch_gemm_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, int R, int N, int K,
                       GemmPlan plan, int mode, float* logits, f16_t* act_out);
 // many-row projection (ts_gemm_rows_bf16.hip), reached through gemm_bf16_plan / launch_gemm_bf16 when R > 80
-bool gemm_rows_plan(const ts_model* m, int R, int N, int K, int mode, size_t max_part_elems, int* mt, int* cfg, int* splits);
+void gemm_rows_plan(const ts_model* m, int R, int N, int K, int mode, size_t max_part_elems, int* mt, int* cfg, int* splits);
 int gemm_rows_chunk(int cfg);
 void launch_gemm_rows_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, int R, int N, int K, int mt, int cfg,
                            int splits, int mode, f16_t* act_out, float* logits);

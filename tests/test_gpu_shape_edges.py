@@ -70,3 +70,39 @@ def test_many_rows_equal_single_passes(hd, hq, hkv, n_seqs):
         r0 += nodes[i] + 1
         B.ts_kv_free(kv)
     B.ts_model_free(model)
+
+
+def test_workspace_of_a_very_large_batch():
+    """253 requests of 65 rows under a feed-forward of 131072 grow the workspace until a plane of the
+    projection inputs (16480 + 80 rows, 4.3 GB) passes 32-bit offsets, and the batch's last row blocks lie beyond
+    them as well.  Every request of the batch is the same, so its rows have to be the same to the bit; a single
+    request afterwards runs the kernels it ran before, so its rows have to be what they were."""
+    cfg = wl.get_config("small_bf16").with_(name="wide_ffn", n_layers=1, d_model=128, n_q_heads=1, n_kv_heads=1, head_dim=128,
+                                            d_ffn=131072, vocab=64)
+    model = B.ts_model_load(cfg, wl.gen_weights(cfg, 5))
+    B.ts_model_keep_logits(model, True)
+    n_seqs, nodes, P = 253, 64, 16
+    assert (n_seqs * (nodes + 1) // 80 * 80 + 160) * cfg.d_ffn * 2 > 1 << 32
+    tok, par = wl.random_tree(nodes, cfg.vocab, np.random.default_rng(9))
+    K, V = wl.gen_context_kv(cfg, P, seed=31)
+    pool = B.ts_kv_pool_create(model, n_seqs * ((P + nodes + 16) // 16))
+    kvs = [B.ts_kv_alloc_pooled(pool, P + nodes + 1) for _ in range(n_seqs)]
+    for kv in kvs:
+        B.ts_kv_import(kv, K, V)
+        B.ts_set_pending(kv, 3)
+
+    def single():
+        res = B.ts_verify(model, kvs[0], tok, par)
+        return res, B.ts_get_logits(model, 0, nodes + 1, cfg.vocab)
+
+    res, before = single()
+    batch = B.ts_verify_batch(model, kvs, [(tok, par)] * n_seqs)
+    rows = B.ts_get_logits(model, 0, n_seqs * (nodes + 1), cfg.vocab).reshape(n_seqs, nodes + 1, cfg.vocab)
+    assert all(np.array_equal(rows[0], r) for r in rows[1:]) and all(b == batch[0] for b in batch)
+    assert U.rel_l2(rows[0], before) <= U.TOL_BF16_R
+    res_after, after = single()
+    assert np.array_equal(before, after) and res_after == res
+    for kv in kvs:
+        B.ts_kv_free(kv)
+    B.ts_kv_pool_free(pool)
+    B.ts_model_free(model)
