@@ -155,7 +155,10 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
         if (VPG % NTHR == 0 || tid + j * NTHR < VPG) stage[p * JP + j] = *reinterpret_cast<const TS_GLOBAL u32x4*>(my_src[j] + pg);
     }
   };
-  auto store_block = [&](int buf) {
+  // always inline: with one head per workgroup (64 threads, eight vectors a thread and page) the compiler left it
+  // a function, which kept `stage` in scratch memory and moved every live register around its calls.  17 rows x
+  // 8192 keys, 16 KV heads of one query head: 64 us, 115 us with the unrolled halves around the call, 25 us inline.
+  auto store_block = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int p = 0; p < 4; ++p)
 #pragma unroll
@@ -186,6 +189,16 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
     // with 8) and with two tiles a wave (17 rows: 11.4 -> 10.7 us); three tiles in 4 waves have no
     // registers left for it (33 rows: 107 -> 144 us), measured.
     constexpr int FD = HB == 4 && (RS == 2 || MT0 == 2) ? 3 : 0;
+    // The two 32-key halves of a block are unrolled, except where one wave holds three tiles of 128 dims: there
+    // the copies cost registers that the kernel does not have.  One head per KV head (245 accumulation registers
+    // instead of 256 and 24 spilled): 33 rows x 8192 keys 37.9 -> 29.3 us, 33 rows x 8 sequences 88.8 -> 65.0 us; four
+    // heads (8 instead of 9 spilled, 36 B of scratch a lane; none before the probabilities took the standing
+    // reference, and that was the slower kernel): 33 rows x 8 sequences of 8192 99 -> 98 us, before 102 us.
+    // Unrolled against rolled elsewhere: 8 heads, 65 rows x 32768 keys 98.5 and 102 us; 64 dims, 48 rows 15.6 and
+    // 16.1 us, ingestion 64.7 and 66.9 us (three or two waves per SIMD fit there instead of four or three: the
+    // launches of one sequence place one workgroup per CU, and the batches are faster all the same: 65 rows x
+    // 8 sequences 68.5 rolled, 67.2 us).
+    constexpr int K2U = HD == 128 && RS == 1 && MT == 3 ? 1 : 2;
   // resident query fragments and ancestor masks of this wave's head
   f16x8 qf[MT][KSQ];
   uint64_t anc[MT];
@@ -236,7 +249,7 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
     // Two sub-blocks of 32 keys (2 pages) each: scores, mask, running soft-max, P.V.
     const int key0 = blk * KB;
     const bool masked = key0 + KB > P;
-#pragma unroll
+#pragma unroll K2U
     for (int k2 = 0; k2 < 2; ++k2) {
       // ---- S^T = K . Q^T -----------------------------------------------------------
       // With FD > 0 the K fragments come from LDS through a short software pipeline, FD of them

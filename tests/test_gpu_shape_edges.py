@@ -72,6 +72,22 @@ def test_many_rows_equal_single_passes(hd, hq, hkv, n_seqs):
     B.ts_model_free(model)
 
 
+@pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (8, 2)])
+def test_row_tiles_of_one_wave(hq, hkv):
+    """One, two and three 16-row tiles in a wave (more rows take two waves) with one, two and four query heads per
+    KV head, which is one wave each: the smallest workgroups stage the most vectors per thread, and three tiles walk a
+    block's halves in a loop.  Contexts of one block, of several splits, and ending inside a half."""
+    cfg, w, model, om = _load(n_layers=1, d_model=256, n_q_heads=hq, n_kv_heads=hkv, head_dim=128, d_ffn=256, vocab=97)
+    rng = np.random.default_rng(hq)
+    for n, P in ((5, 700), (31, 20), (32, 333), (40, 1500), (47, 96)):
+        K, V = wl.gen_context_kv(cfg, P, seed=500 + n)
+        kv, okv = U.make_pair(cfg, model, K, V, int(rng.integers(cfg.vocab)))
+        tok, par = wl.random_tree(n, cfg.vocab, rng)
+        U.check_verify(cfg, model, om, kv, okv, tok, par, label="hq%d n%d P%d" % (hq, n, P))
+        B.ts_kv_free(kv)
+    B.ts_model_free(model)
+
+
 def test_workspace_of_a_very_large_batch():
     """253 requests of 65 rows under a feed-forward of 131072 grow the workspace until a plane of the
     projection inputs (16480 + 80 rows, 4.3 GB) passes 32-bit offsets, and the batch's last row blocks lie beyond
