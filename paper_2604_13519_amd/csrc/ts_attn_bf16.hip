@@ -387,16 +387,20 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
 
 // Combine the splits: out = sum_s w_s (O_s / l_s) / sum_s w_s with w_s = 2^(m_s - m*) l_s, stored as IEEE half.
 // Two kernels, by the number of slots and splits:
-//  * from kMergeSlots (row, head) slots and up to kMergeFew splits (batches and context ingestion): a
-//    thread owns 8 dims of a slot and has all its splits in flight at once; no LDS.  One workgroup per
-//    slot is mostly the cost of dispatching workgroups there: 65536 slots x 3 - 4 splits 66 -> 21.5 us,
-//    16896 x 7 22.0 -> 12.0 us, 10656 x 10 14.7 -> 9.1 us.  Few slots want the other kernel, which spreads
-//    them over more CUs: 208 slots x 12 splits cost a pass of three layers 14 us more here.
+//  * many (row, head) slots and up to kMergeFew splits (batches and context ingestion): a thread owns
+//    8 dims of a slot and requests its splits eight at a time; no LDS.  One workgroup per slot is mostly
+//    the cost of dispatching workgroups there: 65536 slots x 3 - 4 splits 66 -> 21.5 us, 16896 x 7 22.0 -> 12.0 us,
+//    10656 x 10 14.7 -> 9.1 us.  Few slots want the other kernel, which spreads them over more CUs: 208 slots x
+//    12 splits cost a pass of three layers 14 us more here.  The line, one workgroup per slot against a thread
+//    per 8 dims: 4160 slots x 3 / 8 / 9 / 12 / 16 splits 8.6 : 6.6, 9.3 : 7.8, 8.8 : 8.5, 10.0 : 11.2, 9.2 : 11.8 us (past
+//    eight splits a thread needs a second round of loads); with 9 - 16 splits 4224 slots 9.6 : 10.2, 5120 10.7 : 10.5,
+//    5280 10.9 : 10.6, 6336 12.1 : 10.9, 8448 13.6 : 11.0 us; 2304 slots x 8 7.2 : 8.1 us.
 //  * otherwise (one sequence over many workgroups: few slots, many splits): one workgroup per slot; its
 //    256 threads form 256/(HD/4) groups, group j takes splits j, j+groups, ... so that every partial of
 //    the slot is requested at once (the kernel is a single round of memory latency plus the
 //    transfer); the groups' sums are then added through LDS in a fixed order.
-constexpr int kMergeFew = 16, kMergeSlots = 4096;
+constexpr int kMergeFew = 16;
+bool merge_few(int slots, int splits) { return splits <= kMergeFew && slots >= (splits <= 8 ? 4096 : 5120); }
 
 __global__ __launch_bounds__(256) void k_attn_merge_few(const uint16_t* __restrict__ part_o, const float* __restrict__ part_ml,
                                                         f16_t* __restrict__ Ab, size_t a_plane, int slots, int HD, int splits,
@@ -576,7 +580,7 @@ void launch_attn_merge(ts_model* m, int R, int splits) {
   const ts_model_config& c = m->cfg;
   const size_t plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * m->q_dim;
   const int slots = R * c.n_q_heads;
-  if (splits <= kMergeFew && slots >= kMergeSlots) {
+  if (merge_few(slots, splits)) {
     const int per_wg = 256 / (c.head_dim / 8);
     hipLaunchKernelGGL(k_attn_merge_few, dim3((slots + per_wg - 1) / per_wg), dim3(256), 0, m->stream, m->attn_part_o, m->attn_part_ml,
                        (f16_t*)m->Ab, plane, slots, c.head_dim, splits, m->sat_count);

@@ -72,6 +72,28 @@ def test_many_rows_equal_single_passes(hd, hq, hkv, n_seqs):
     B.ts_model_free(model)
 
 
+@pytest.mark.parametrize("n_seqs,P", [(4, 400), (4, 1950), (5, 1950)])
+def test_merge_of_a_batch(n_seqs, P):
+    """Joining key splits at both sides of the rule: 4160 (row, head) slots with up to eight splits and 5200
+    with sixteen take a thread per 8 dims, 4160 with sixteen a workgroup per slot.  Against single passes."""
+    cfg, w, model, om = _load(n_layers=1, d_model=256, n_q_heads=16, n_kv_heads=2, head_dim=128, d_ffn=256, vocab=97)
+    rng = np.random.default_rng(P + n_seqs)
+    trees, kvs = [wl.random_tree(64, cfg.vocab, rng) for _ in range(n_seqs)], []
+    for i in range(n_seqs):
+        K, V = wl.gen_context_kv(cfg, P + i, seed=700 + i)
+        kvs.append(B.ts_kv_alloc(model, P + i + 65))
+        B.ts_kv_import(kvs[i], K, V)
+        B.ts_set_pending(kvs[i], i)
+    B.ts_verify_batch(model, kvs, trees)
+    both = B.ts_get_logits(model, 0, 65 * n_seqs, cfg.vocab).reshape(n_seqs, 65, cfg.vocab)
+    for i, kv in enumerate(kvs):
+        B.ts_verify(model, kv, *trees[i])
+        one = B.ts_get_logits(model, 0, 65, cfg.vocab)
+        assert max(U.rel_l2(a, b) for a, b in zip(both[i], one)) <= U.TOL_BF16_R
+        B.ts_kv_free(kv)
+    B.ts_model_free(model)
+
+
 @pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (8, 2)])
 def test_row_tiles_of_one_wave(hq, hkv):
     """One, two and three 16-row tiles in a wave (more rows take two waves) with one, two and four query heads per
