@@ -56,6 +56,7 @@ struct GemmArgs {
   int amax_parts;
   int zero_row;        // where the rows past the last come from (see x_off)
   int groups, splits;  // column groups x K splits workgroups
+  int runs;            // their place on the XCDs
 };
 
 enum { MODE_PARTIAL = 0, MODE_ARGMAX = 1, MODE_SWIGLU = 2 };
@@ -84,14 +85,10 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l15 = lane & 15, g = lane >> 4;
   const int cs = wave / KW, kq = wave % KW;
-  // Place: workgroups are dealt to the 8 XCDs round robin by id.  Each XCD takes a contiguous run of the
-  // (split, column group) pairs in split order: it reads neighbouring weight tiles, and only the
-  // activations of one or two K splits pass through its L2 instead of all of them.  Against column
-  // groups dealt round robin (8B shape): 1 row gate/up 42.1 -> 38.4, QKV 12.5 -> 12.8, O + down 32.3 -> 32.0 us;
-  // 17 rows down 21.7 -> 20.8, O 9.9 -> 9.0; 65 rows QKV 17.6 -> 19.0, O 12.9 -> 12.4, down 28.4 -> 28.0, gate/up the
-  // same (column-group-major runs instead: 19.1 for QKV).
+  // Place: workgroups are dealt to the 8 XCDs round robin by id.  With a.runs each XCD takes a contiguous run of
+  // the (split, column group) pairs in split order, else the pairs go round robin as they come (use_runs).
   const int units = a.groups * a.splits;
-  const int unit = (blockIdx.x & 7) * ((units + 7) / 8) + (blockIdx.x >> 3);
+  const int unit = a.runs ? (int)((blockIdx.x & 7) * ((units + 7) / 8) + (blockIdx.x >> 3)) : (int)blockIdx.x;
   if (unit >= units) return;
   const int group = unit % a.groups, split = unit / a.groups;
   const int kbase0 = split * a.kper;
@@ -356,6 +353,19 @@ bool shape_supports(int shape, int mode) {
 constexpr int kRowsShape0 = 100;
 constexpr size_t kRowsPartCap = (size_t)64 << 20;   // partial-sum elements a plan may use before a workspace exists
 
+// Place of the workgroups on the XCDs.  In runs an XCD reads neighbouring weight tiles, and only the activations of
+// one or two K splits pass through its L2 instead of all of them.  That pays (8B shape, round robin : runs, us between
+// events): 1 row gate/up 44.4 : 40.0, QKV 14.3 : 12.7, O 11.9 : 9.8, down 22.1 : 21.5; 17 rows 45.3 : 41.7, 14.8 : 13.8,
+// 12.0 : 11.0, 23.6 : 22.9; 65 rows O 15.2 : 14.3, down 29.8 : 29.1, gate/up the same.  Except where five row tiles meet a
+// shape with one k-wave (one chunk in flight) and an XCD's run is a part of one K range of eight chunks or more,
+// presumably because its workgroups then ask its L2 for the same activation lines at the same time, 40 KB a chunk each.  65 rows, from
+// a trace: QKV (48 groups x 4 splits) 17.6 : 18.5, head of 128256 columns (501 groups) 204 : 211; half the K range
+// (2048) 15.7 : 14.7, four row tiles 16.0 : 16.2 and 193 : 192, and two k-waves (head of 151936 columns) 324 : 316.
+// The SwiGLU shapes stay in runs (51200 columns, one k-wave 101.4 : 100.2).
+bool use_runs(int shape, int mode, int R, int chunks_per_split, int groups, int splits) {
+  return !(R > 64 && mode != MODE_SWIGLU && kShapeKW[shape] == 1 && chunks_per_split >= 8 && (groups * splits + 7) / 8 < groups);
+}
+
 }  // namespace
 
 int gemm_bf16_cols_per_group(int shape) { return kShapeNT[shape] * kShapeCS[shape] * 16; }
@@ -444,6 +454,7 @@ void launch_gemm_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, 
   const int groups = (N + cols - 1) / cols;
   const int mt = (R + 15) / 16;
   a.groups = groups; a.splits = splits;
+  a.runs = use_runs(plan.shape, mode, R, a.kper / kShapeKC[plan.shape], groups, splits);
   dim3 grid((groups * splits + 7) / 8 * 8);
   if (mode == MODE_ARGMAX) launch_shape<MODE_ARGMAX>(plan.shape, mt, grid, m->stream, a);
   else if (mode == MODE_SWIGLU) launch_shape<MODE_SWIGLU>(plan.shape, mt, grid, m->stream, a);

@@ -72,6 +72,22 @@ def test_many_rows_equal_single_passes(hd, hq, hkv, n_seqs):
     B.ts_model_free(model)
 
 
+@pytest.mark.parametrize("kw", [
+    dict(d_model=1024, n_q_heads=8, n_kv_heads=2, vocab=32003),    # the head: 251 column groups, not a multiple of the XCDs
+    dict(d_model=2048, n_q_heads=64, n_kv_heads=16, vocab=97),     # QKV: 96 column groups x 2 splits of eight chunks
+])
+def test_places_of_five_row_tiles(kw):
+    """65 rows, one k-wave and a long K range: these launches leave the runs per XCD for round robin."""
+    cfg, w, model, om = _load(n_layers=1, head_dim=128, d_ffn=256, **kw)
+    rng = np.random.default_rng(kw["vocab"])
+    K, V = wl.gen_context_kv(cfg, 40, seed=41)
+    kv, okv = U.make_pair(cfg, model, K, V, 5)
+    tok, par = wl.random_tree(64, cfg.vocab, rng)
+    U.check_verify(cfg, model, om, kv, okv, tok, par, label="d%d" % cfg.d_model)
+    B.ts_kv_free(kv)
+    B.ts_model_free(model)
+
+
 @pytest.mark.parametrize("n_seqs,P", [(4, 400), (4, 1950), (5, 1950)])
 def test_merge_of_a_batch(n_seqs, P):
     """Joining key splits at both sides of the rule: 4160 (row, head) slots with up to eight splits and 5200
