@@ -375,7 +375,8 @@ int gemm_bf16_chunk(int shape) { return shape >= kRowsShape0 ? gemm_rows_chunk((
 //   rounds x (weight bytes one workgroup streams + 72 KB)     rounds = ceil(workgroups / CUs); start and finish
 //                                                             of a round cost what 72 KB of streaming do (3 us)
 // + write and read of the fp32 partial sums, shared by all CUs and 15 % dearer (only if splits > 1), at least 5 KB a split:
-//   with few rows the kernel that adds them up pays for their number, not their bytes
+//   with few rows the kernel that adds them up pays for their number, not their bytes.  Rows of under 1024 columns
+//   (512-wide models) pay that in proportion: K 1536 to 512 columns, 38 rows, 6 splits 7.3 us, 12 splits 6.4 us
 // + 0.3 of the activation bytes (both planes) a workgroup stages from L2 per round.
 // Measured on MI355X, a second round of workgroups costs a full round (the tail does not
 // overlap), which the round count models.  mode: 0 partial sums, 1 arg-max (no split),
@@ -408,7 +409,7 @@ GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
       const long rounds = (wgs + m->n_cu - 1) / m->n_cu;
       const double kper = (double)K / s;
       double cost = rounds * cols * kper * 2.0;
-      if (s > 1) cost += std::max(2.3 * s * R * (double)N * 4.0 / m->n_cu, 5120.0 * s);
+      if (s > 1) cost += std::max(2.3 * s * R * (double)N * 4.0 / m->n_cu, 5.0 * std::min(N, 1024) * s);
       cost += 0.3 * rounds * rows * kper * 2.0 * TS_ACT_PLANES;
       // Measured (8B shape): over a long K range the k-wave shape wins by its deeper prefetch (gate/up, 32
       // chunks, 65 rows: 55.5 us against 57.7 us for the 4-wave shape of the same columns; down, 14 chunks, 1 to
