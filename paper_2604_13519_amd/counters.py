@@ -2,8 +2,8 @@
 
     python -m paper_2604_13519_amd.counters trace <kernel_trace.db> [--workload w3] [--command "..."] [--bench line.json]
 
-writes profiles/verify_<workload>_kernel_trace.md: per kernel (the split projections told apart by
-their grids) calls, total and average duration, and the launches, span and gaps of one timed step.
+writes profiles/verify_<workload>_kernel_trace.md: per kernel (the projections told apart by their place
+in the layer) calls, total and average duration, and the launches, span and gaps of one timed step.
 
     python -m paper_2604_13519_amd.counters sq <w3_pass.db> <w4_pass.db> [--out file] [--commit hash]
 
@@ -50,37 +50,39 @@ def _short(k):
 
 
 def _gemm_mode(name):
-    m = re.match(r"k_gemm_bf16<(\d+), (\d+), (\d+), (\d+), (\d+), (\d+), (\d+), (\d+)>", name)
-    return int(m.group(7)) if m else None
+    """Epilogue of a projection (0 partial sums, 1 arg-max, 2 SwiGLU); None: not a projection of a bf16 model."""
+    m = re.match(r"k_gemm_bf16<(?:\d+, ){6}(\d+), \d+>|k_gemm_rows_bf16<(?:\d+, ){3}(\d+)>", name)
+    return int(m.group(1) or m.group(2)) if m else None
+
+
+_KINDS = {"k_embed_rope": "embed_rope_table", "k_norm": "residual_rmsnorm", "k_rope_kv": "rope_kv_write", "k_attn_bf16": "attn_bf16",
+          "k_attn_merge": "attn_merge", "k_attn_merge_few": "attn_merge", "k_walk": "accept_walk", "k_plain_read": "plain_read"}
+# QKV, O and down are one kernel with whatever shape and splits the planner took: what ran before tells them apart
+_PROJECTION_AFTER = {"residual_rmsnorm": "gemm_qkv", "attn_merge": "gemm_o", "gemm_gate_up": "gemm_down"}
+
+
+def kernel_kinds(names):
+    """Kernel names in launch order -> the kinds bench.py reports them under (None: not one of a verify pass)."""
+    kinds, before = [], None
+    for name in names:
+        mode = _gemm_mode(name)
+        kind = _KINDS.get(name.split("<")[0]) if mode is None else \
+            "gemm_lm_head_argmax" if mode == 1 else "gemm_gate_up" if mode == 2 else _PROJECTION_AFTER.get(before)
+        kinds.append(kind)
+        before = kind or before
+    return kinds
 
 
 def _load(db):
-    """{kernel (split projections: name + ' grid WxB'): {counter: [values]}}"""
-    cur = sqlite3.connect(db).cursor()
+    """{(kind, kernel name): {counter: [values]}} of a counter pass"""
+    rows = list(sqlite3.connect(db).cursor().execute(
+        "select dispatch_id, kernel_name, counter_name, sum(value) from counters_collection group by dispatch_id, kernel_name, counter_name"))
+    order = sorted({(d, _short(k)) for d, k, _, _ in rows})
+    kind = dict(zip(order, kernel_kinds([k for _, k in order])))
     agg = collections.defaultdict(lambda: collections.defaultdict(list))
-    for k, c, v, gx, gy, wx in cur.execute(
-            "select kernel_name, counter_name, value, grid_size_x, grid_size_y, workgroup_size_x from counters_collection"):
-        k = _short(k)
-        if _gemm_mode(k) == 0:
-            k += " grid %dx%d" % (gx // wx, gy)
-        agg[k][c].append(v)
+    for d, k, c, v in rows:
+        agg[kind[d, _short(k)], _short(k)][c].append(v)
     return agg
-
-
-def kernel_kind(name):
-    """Kernel name of the library -> the kind bench.py reports it under (None: not one of ours).
-    The split projections share one kernel; on the 8B shape the QKV projection is the launch with
-    48 column groups, the O and down projections both run 32 groups x 8 splits."""
-    mode = _gemm_mode(name.split(" grid ")[0])
-    if mode == 2:
-        return "gemm_gate_up"
-    if mode == 1:
-        return "gemm_lm_head_argmax"
-    if mode == 0:
-        grid = name.split(" grid ")[1] if " grid " in name else ""
-        return "gemm_qkv" if grid.startswith("192x") else "gemm_o+gemm_down"
-    return {"k_attn_bf16": "attn_bf16", "k_attn_merge": "attn_merge", "k_norm": "residual_rmsnorm",
-            "k_rope_kv": "rope_kv_write", "k_plain_read": "plain_read"}.get(name.split("<")[0])
 
 
 def sq_summary(dbs, out_path, commit):
@@ -95,24 +97,14 @@ def sq_summary(dbs, out_path, commit):
                 "(4 x SQ_BUSY_CU_CYCLES)\n(four SIMDs per CU), LDS active = SQ_LDS_IDX_ACTIVE / SQ_BUSY_CU_CYCLES, LDS conflict = "
                 "SQ_LDS_BANK_CONFLICT / SQ_BUSY_CU_CYCLES,\nwaves waiting = SQ_WAIT_ANY / SQ_WAVE_CYCLES.\n")
         for title, db in dbs:
-            cur = sqlite3.connect(db).cursor()
-            per = collections.defaultdict(lambda: collections.defaultdict(list))
-            q = ("select kernel_name, grid_size_x, grid_size_y, workgroup_size_x, dispatch_id, counter_name, sum(value) "
-                 "from counters_collection group by kernel_name, dispatch_id, counter_name")
-            for k, gx, gy, wx, _, c, v in cur.execute(q):
-                k = _short(k)
-                if not (k.startswith("k_gemm") or k.startswith("k_attn_bf16")):
-                    continue
-                if _gemm_mode(k) == 0 or k.startswith("k_gemm_rows_bf16"):
-                    k += " grid %dx%d" % (gx // wx, gy)
-                per[k][c].append(v)
-            f.write("\n## %s\n\n| kernel | launches | MFMAs / launch | matrix pipe busy | LDS active | LDS conflict | waves waiting |\n"
-                    "|---|---:|---:|---:|---:|---:|---:|\n" % title)
+            per = {k: v for k, v in _load(db).items() if k[1].startswith("k_gemm") or k[1].startswith("k_attn_bf16")}
+            f.write("\n## %s\n\n| kind | kernel | launches | MFMAs / launch | matrix pipe busy | LDS active | LDS conflict | waves waiting |\n"
+                    "|---|---|---:|---:|---:|---:|---:|---:|\n" % title)
             mean = lambda k, c: sum(per[k][c]) / max(len(per[k][c]), 1)
             for k in sorted(per, key=lambda k: -mean(k, "SQ_BUSY_CU_CYCLES") * len(per[k]["SQ_BUSY_CU_CYCLES"])):
                 busy = max(mean(k, "SQ_BUSY_CU_CYCLES"), 1.0)
-                f.write("| `%s` | %d | %.0f | %.1f %% | %.1f %% | %.1f %% | %.1f %% |\n" % (
-                    k, len(per[k]["SQ_BUSY_CU_CYCLES"]), mean(k, "SQ_INSTS_MFMA"), 100 * mean(k, "SQ_VALU_MFMA_BUSY_CYCLES") / (4 * busy),
+                f.write("| %s | `%s` | %d | %.0f | %.1f %% | %.1f %% | %.1f %% | %.1f %% |\n" % (
+                    k[0], k[1], len(per[k]["SQ_BUSY_CU_CYCLES"]), mean(k, "SQ_INSTS_MFMA"), 100 * mean(k, "SQ_VALU_MFMA_BUSY_CYCLES") / (4 * busy),
                     100 * mean(k, "SQ_LDS_IDX_ACTIVE") / busy, 100 * mean(k, "SQ_LDS_BANK_CONFLICT") / busy,
                     100 * mean(k, "SQ_WAIT_ANY") / max(mean(k, "SQ_WAVE_CYCLES"), 1.0)))
     print("wrote", out_path)
@@ -124,13 +116,11 @@ def trace_summary(db, workload, command, bench_json=None):
     cur = sqlite3.connect(db).cursor()
     rows = list(cur.execute("select name, start, end, grid_x, grid_y, workgroup_x from kernels order by start"))
     agg = collections.OrderedDict()
-    names = []
-    for name, st, en, gx, gy, wx in rows:
-        k = _short(name)
-        if _gemm_mode(k) == 0 or k.startswith("k_gemm_rows_bf16"):
+    names = [_short(r[0]) for r in rows]
+    for (_, st, en, gx, gy, wx), k, kind in zip(rows, names, kernel_kinds(names)):
+        if k.startswith("k_gemm"):
             k += " grid %dx%d" % (gx // wx, gy)
-        names.append(k)
-        a = agg.setdefault(k, [0, 0.0])
+        a = agg.setdefault((kind, k), [0, 0.0])
         a[0] += 1
         a[1] += (en - st) / 1e3
     total = sum(a[1] for a in agg.values())
@@ -142,13 +132,13 @@ def trace_summary(db, workload, command, bench_json=None):
         f.write("`python -m paper_2604_13519_amd.counters trace <results.db> --workload %s`:\n\n    %s\n\n" % (workload, command))
         f.write("Durations are kernel begin-to-end times from the trace; the run also holds model load (k_repack_tiles, k_kv_xfer)\n"
                 "and bench.py's untimed passes.  Template arguments of `k_gemm_bf16`: row tiles, tiles per wave, column sets, k-waves,\n"
-                "chunk, prefetch depth, mode (0 partial sums, 1 arg-max, 2 SwiGLU), LDS pad; `grid WxB` = workgroups (column groups x K\n"
-                "splits) x row blocks.\n\n")
-        f.write("| kernel | calls | total us | avg us | % |\n|---|---:|---:|---:|---:|\n")
-        for k, (n, t) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
+                "chunk, prefetch depth, mode (0 partial sums, 1 arg-max, 2 SwiGLU), LDS pad; of `k_gemm_rows_bf16`: row tiles, column sets,\n"
+                "k-waves, mode; grids in workgroups.\n\n")
+        f.write("| kind | kernel | calls | total us | avg us | % |\n|---|---|---:|---:|---:|---:|\n")
+        for (kind, k), (n, t) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
             if t / total < 0.0005:
                 continue
-            f.write("| `%s` | %d | %.1f | %.2f | %.1f |\n" % (k, n, t, t / n, 100.0 * t / total))
+            f.write("| %s | `%s` | %d | %.1f | %.2f | %.1f |\n" % (kind or "", k, n, t, t / n, 100.0 * t / total))
         # one step in the middle of the run: from one row set-up kernel to the next
         starts = [i for i, k in enumerate(names) if k.startswith("k_embed")]
         if len(starts) >= 3:
@@ -163,10 +153,9 @@ def trace_summary(db, workload, command, bench_json=None):
         if bench_json:
             d = json.loads(open(bench_json).read().strip().splitlines()[-1])
             rf = d["roofline"]
-            kname = [k for k in agg if _gemm_mode(k.split(" grid ")[0]) == (2 if rf["kernel"] == "gemm_gate_up" else -1) or
-                     (rf["kernel"] == "gemm_gate_up" and k.startswith("k_gemm_rows_bf16") and k.split(",")[-1].startswith(" 2>"))]
-            if kname:
-                n, t = agg[kname[0]]
+            times = [v for k, v in agg.items() if k[0] == rf["kernel"]]
+            if times:
+                n, t = sum(v[0] for v in times), sum(v[1] for v in times)
                 f.write("\nRoofline kernel of bench.py's line for this build (`%s`): trace average %.2f us per launch; bench.py's HIP-event "
                         "bracket around the same launches reads %.2f us (each bracket carries 2 - 3 us of event overhead), i.e. %s %.0f from the "
                         "trace against %.0f reported.\n" % (rf["kernel"], t / n, rf["avg_us"], rf["unit"],
@@ -207,20 +196,19 @@ def main(argv):
         return trace_summary(argv[1], workload, command, argv[argv.index("--bench") + 1] if "--bench" in argv else None)
     rd, wr = argv[0], argv[1]
     R, W = _load(rd), _load(wr)
-    copy_rd = max(R[[k for k in R if "copyBuffer" in k][0]]["TCC_EA0_RDREQ_128B_sum"]) * 128
-    copy_wr = max(W[[k for k in W if "copyBuffer" in k][0]]["WRITE_SIZE"]) * 1024
+    copy = next(k for k in R if "copyBuffer" in k[1])
+    copy_rd, copy_wr = max(R[copy]["TCC_EA0_RDREQ_128B_sum"]) * 128, max(W[copy]["WRITE_SIZE"]) * 1024
     out, rows = {}, []
-    for k in R:
-        kd = kernel_kind(k)
-        if not kd:
+    for k in sorted(R, key=lambda k: len(R[k]["TCC_EA0_RDREQ_sum"])):     # a kind with several kernels: the most frequent one stays
+        if k[0] in (None, "embed_rope_table", "accept_walk"):
             continue
         mean = lambda d, c: sum(d[k][c]) / max(len(d[k][c]), 1)
         rb = 128 * mean(R, "TCC_EA0_RDREQ_128B_sum") + 64 * mean(R, "TCC_EA0_RDREQ_64B_sum") + 32 * mean(R, "TCC_EA0_RDREQ_32B_sum")
         wb = 1024 * mean(W, "WRITE_SIZE")
         rb *= GIB / copy_rd
         wb *= GIB / copy_wr
-        out[kd] = {"read_bytes": rb, "write_bytes": wb, "bytes": rb + wb}
-        rows.append((kd, k, len(R[k]["TCC_EA0_RDREQ_sum"]), rb, wb))
+        out[k[0]] = {"read_bytes": rb, "write_bytes": wb, "bytes": rb + wb}
+        rows.append((k[0], k[1], len(R[k]["TCC_EA0_RDREQ_sum"]), rb, wb))
     commit = _commit()
     out["_measured_on"] = {"commit": commit, "workload": workload,
                            "scale_read": GIB / copy_rd, "scale_write": GIB / copy_wr}
