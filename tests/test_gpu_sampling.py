@@ -113,3 +113,40 @@ def test_sampling_error_paths():
         assert B.ts_kv_len(kv) == 20
     finally:
         B.ts_kv_free(kv)
+
+
+@pytest.mark.parametrize("vocab", [131072, 140001])
+def test_sampled_walk_over_many_chunks(vocab):
+    """Rows are cut into chunks of 2048 tokens and joined 64 at a time: exactly 64 chunks, and 69 of which the last
+    is ragged.  The head's last 3000 rows are larger, so likely, drafted and sampled tokens lie in the last chunks."""
+    cfg = wl.get_config("micro_fp32").with_(name="many_chunks", n_layers=1, vocab=vocab)
+    w = wl.gen_weights(cfg, 8)
+    w["lm_head"][-3000:] *= 20.0
+    model = B.ts_model_load(cfg, w)
+    omodel = O.OracleModel(cfg, w, cache=True)
+    K, V = wl.gen_context_kv(cfg, 33, seed=94)
+    kv, okv = U.make_pair(cfg, model, K, V, 11)
+    rng = np.random.default_rng(vocab)
+    tok, par = wl.random_tree(12, vocab, rng)
+    for _ in range(2):                     # the first pass finds likely tokens, the second's tree drafts them
+        rows = O.tree_rows(okv.pending, tok, par)
+        ologits, _, _ = O.forward_tree(omodel, okv, rows[0], rows[2], rows[3], "E")
+        for i in range(0, len(tok), 2):
+            tok[i] = int(np.argsort(ologits[rows[1][i + 1]])[-1 - i % 3])
+    rows = O.tree_rows(okv.pending, tok, par)
+    ologits, _, _ = O.forward_tree(omodel, okv, rows[0], rows[2], rows[3], "E")
+    exact, last = 0, 0
+    for T in (0.3, 1.0):
+        for _ in range(12):
+            u = rng.random(len(tok)).astype(np.float32)
+            seed = int(rng.integers(1 << 62))
+            got = B.ts_verify_sample(model, kv, tok, par, T, u, seed)
+            want = SO.sample_walk(ologits, rows[0], rows[1], T, u, seed)
+            last += want.bonus_token >= vocab - 3000
+            if want.decision_gap > 1e-4 and want.bonus_gap > 1e-4:
+                exact += 1
+                assert got == (want.accept_len, want.accepted_tokens, want.accepted_nodes, want.bonus_token)
+    print("vocab %d: %d of 24 compared exactly, %d end in the last 3000 tokens" % (vocab, exact, last))
+    assert exact >= 15 and 4 <= last
+    B.ts_kv_free(kv)
+    B.ts_model_free(model)
