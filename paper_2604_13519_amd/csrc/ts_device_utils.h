@@ -21,15 +21,8 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   return (bf16_t)(b >> 16);
 }
 
-// two floats -> packed bf16 pair (low half = a), round to nearest even, one v_cvt_pk_bf16_f32
-typedef __bf16 ts_bf16x2 __attribute__((ext_vector_type(2)));
-typedef float ts_f32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-  const ts_f32x2 v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, ts_bf16x2));
-}
-
 // two floats -> packed IEEE half pair (low half = a), round to nearest even
+typedef float ts_f32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 ts_f16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack_f16x2(float a, float b) {
   const ts_f32x2 v = {a, b};
@@ -42,10 +35,8 @@ __device__ __forceinline__ uint32_t bf16x2_to_f16x2(uint32_t w) {
 __device__ __forceinline__ uint16_t f32_to_f16_bits(float f) {
   return __builtin_bit_cast(uint16_t, (_Float16)f);
 }
-// activation -> IEEE half, round to nearest even, saturating at the largest finite half (NaN stays NaN)
+// saturates at the largest finite half (NaN stays NaN)
 __device__ __forceinline__ float sat_f16_range(float f) { return f == f ? fminf(fmaxf(f, -65504.f), 65504.f) : f; }
-__device__ __forceinline__ uint16_t f32_to_f16_sat(float f) { return f32_to_f16_bits(sat_f16_range(f)); }
-__device__ __forceinline__ uint32_t pack_f16x2_sat(float a, float b) { return pack_f16x2(sat_f16_range(a), sat_f16_range(b)); }
 
 // An activation that enters a weight projection of a bf16 model is carried as TWO halves,
 // x = hi + lo with hi = half(x) (saturating) and lo = half(x - hi): about 22 significant bits, so
@@ -86,8 +77,6 @@ __device__ __forceinline__ void st_act_planes4(f16_t* p, size_t plane, float x0,
   *reinterpret_cast<uint2*>(p + plane) = make_uint2(__builtin_bit_cast(uint32_t, l01), __builtin_bit_cast(uint32_t, l23));
 }
 
-__device__ __forceinline__ float ld_f32(const float* p) { return *p; }
-__device__ __forceinline__ float ld_f32(const bf16_t* p) { return bf16_to_f32(*p); }
 __device__ __forceinline__ void st_from_f32(float* p, float v) { *p = v; }
 __device__ __forceinline__ void st_from_f32(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 

@@ -4,8 +4,8 @@
 // used once, so the kernel is organised around the HBM read of W and nothing else.
 //  * Arithmetic: IEEE half x IEEE half -> fp32 (v_mfma_f32_16x16x32_f16).  The bf16 weights are
 //    re-encoded as half at model load (exact: half has more significand bits; the load rejects
-//    magnitudes beyond half's range) and the activations arrive rounded to half - 11
-//    significant bits where bf16 has 8, with one MFMA per weight fragment.
+//    magnitudes beyond half's range) and an activation arrives as the sum of two halves, about
+//    22 significant bits, with two MFMAs per weight fragment and row tile.
 //  * W is pre-tiled at model load into MFMA operand order (see k_repack_tiles): a wave's
 //    16-byte-per-lane global load is one contiguous 1 KiB tile that feeds the MFMA directly as
 //    the B operand - no LDS, no shuffles for weights.
@@ -319,7 +319,7 @@ void launch_mt(int mt, dim3 grid, hipStream_t s, const GemmArgs& a) {
 
 // The compiled tile shapes.  shape id -> (NT, CS, KW): tiles per wave, column sets and
 // k-waves per workgroup.  All use chunks of 128 k (the LDS holds two buffers of the
-// activation chunk, 43 KiB for 80 rows).  The k-wave shapes hold fewer weight registers
+// activation chunk in both planes, 85 KiB for 80 rows).  The k-wave shapes hold fewer weight registers
 // per chunk and prefetch two to four chunks ahead instead of one.
 constexpr int kNumShapes = 7;
 const int kShapeNT[kNumShapes] = {1, 2, 1, 2, 2, 1, 2};

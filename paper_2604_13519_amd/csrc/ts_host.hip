@@ -167,7 +167,7 @@ static void free_workspace(ts_model* m) {
   m->ws_rows = 0; m->ws_seqs = 0; m->logits_rows = 0; m->attn_max_splits = 0; m->part_elems = 0;
 }
 
-static size_t meta_bytes_for(int rows) { return (size_t)rows * (6 * sizeof(int32_t) + sizeof(uint64_t) + sizeof(float)); }
+static size_t meta_bytes_for(int rows) { return (size_t)rows * (5 * sizeof(int32_t) + sizeof(uint64_t) + sizeof(float)); }
 
 // Row buffers carry TS_MROWS_PER_BLOCK spare rows: tile-granular kernels read (never use)
 // rows past the last real one.
@@ -202,7 +202,7 @@ static ts_status ensure_workspace(ts_model* m, int rows, int seqs, bool want_log
         if (cap > TS_MROWS_PER_BLOCK && i != 2) pe = std::max(pe, std::min((size_t)8 * cap * Ns[i], (size_t)64 << 20));
       }
     } else {
-      pe = (size_t)cap * std::max(std::max(m->qkv_dim, 2 * c.d_ffn), c.d_model);
+      pe = (size_t)cap * std::max(m->qkv_dim, c.d_model);     // gate/up stores its product, not sums
     }
     m->part_elems = pe;
     if ((st = dev_alloc_bytes((void**)&m->part, pe * 4, true))) return st;
@@ -729,7 +729,6 @@ static RowMeta carve_meta(void* base, int rows) {
   char* p = (char*)base;
   rm.anc = (uint64_t*)p; p += (size_t)rows * sizeof(uint64_t);
   rm.tok = (int32_t*)p;  p += (size_t)rows * 4;
-  rm.pos = (int32_t*)p;  p += (size_t)rows * 4;
   rm.seq = (int32_t*)p;  p += (size_t)rows * 4;
   rm.lrow = (int32_t*)p; p += (size_t)rows * 4;
   rm.par = (int32_t*)p;  p += (size_t)rows * 4;

@@ -23,13 +23,11 @@ ts_status ts_fail(ts_status code, const char* fmt, ...);
 
 // ---- geometry constants ---------------------------------------------------------
 constexpr int TS_MROWS_PER_BLOCK = 80;  // rows one GEMM pass covers (5 MFMA tiles of 16)
-constexpr int TS_GEMM_KC = 128;         // k elements per staged chunk
 constexpr int TS_ATTN_KB = 64;          // keys per attention block (4 pages)
 
 // Per-row metadata of one verify pass, structure of arrays in one device buffer.
 struct RowMeta {
   int32_t* tok;      // token id
-  int32_t* pos;      // absolute position = committed length + depth
   int32_t* seq;      // sequence index within the batch
   int32_t* lrow;     // row index within its sequence (0 = root)
   int32_t* par;      // parent row within its sequence (-1 for the root)

@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void k_embed_rope(const RowRec* __restrict__ r
     cs[(size_t)r * half + j] = make_float2((float)cos(ang), (float)sin(ang));
   }
   if (threadIdx.x == blockDim.x - 1) {
-    rm.anc[r] = s_rec.anc; rm.tok[r] = s_rec.tok; rm.pos[r] = s_rec.pos; rm.seq[r] = s_rec.seq; rm.lrow[r] = s_rec.lrow;
+    rm.anc[r] = s_rec.anc; rm.tok[r] = s_rec.tok; rm.seq[r] = s_rec.seq; rm.lrow[r] = s_rec.lrow;
     rm.par[r] = s_rec.par; rm.depth[r] = s_rec.depth; rm.u[r] = s_rec.u;
     dst[r] = s_rec.dst;
   }
