@@ -94,8 +94,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   const int kbase0 = split * a.kper;
   const int n_chunks = a.kper / KC;
 
-  // Addresses are (uniform 64-bit base) + (32-bit per-lane byte offset that never changes):
-  // the loads then need no vector address arithmetic inside the loop.
+  // Addresses are (uniform 64-bit base) + (32-bit per-lane byte offset that never changes).
   const int cs_u = __builtin_amdgcn_readfirstlane(cs), kq_u = __builtin_amdgcn_readfirstlane(kq);
   const char* wbase[NT];                    // start of this wave's k range in each owned tile row
   int nt_idx[NT];
@@ -118,9 +117,9 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   for (int p = 0; p < XPT; ++p) {
     const int v = XPP ? tid + (p < XPP ? p : p - XPP) * NTHR : min(tid + p * NTHR, XV - 1);      // surplus threads re-read the last vector
     const int rl = (v % XVP) / (KC / 8), cv = v % (KC / 8);
-    // rows past the last come from one spare row, which is zero: their lines are fetched once (the activations
-    // enter a CU through the same port as the weights), and zeros cost the matrix pipes little power.  17 rows
-    // (32 before): head of 8192 columns 19.4 -> 16.3 us, gate/up 40.6 -> 39.7 us, O 9.2 -> 8.8 us
+    // rows past the last come from one spare row, which is zero: their lines are fetched once, and zeros cost the
+    // matrix pipes little power.  17 rows (32 before): head of 8192 columns 19.4 -> 16.3 us, gate/up 40.6 -> 39.7 us,
+    // O 9.2 -> 8.8 us
     const int row = rl < a.R ? rl : a.zero_row;
     x_lo[p] = XPP ? p >= XPP : __builtin_amdgcn_readfirstlane(v / XVP) != 0;
     x_off[p] = ((uint32_t)row * (uint32_t)a.K + cv * 8) * 2;
@@ -385,6 +384,10 @@ int gemm_bf16_chunk(int shape) { return shape >= kRowsShape0 ? gemm_rows_chunk((
 // of the kernel behind it, between events.  One row, before the two fixed costs and with them: QKV 16 splits
 // in three rounds 14.8 us, 4 splits in one 12.1 us; O 16 splits 14.9 us, 4 splits 8.3 us; down 21.9 and 20.2 us.
 // 17 rows: QKV 17.5 and 14.1 us, down 22.9 and 22.0 us.  65 rows: unchanged plans.
+// On the 32B-class shape, which set none of them (one request, events): 1 row QKV 19.7 -> 20.9 us (1280 workgroups
+// that overlap on their CUs beat 200 there, which the round count does not see), O 20.1 -> 18.6 us, each norm behind
+// a split 7.9 -> 7.0 us; 65 rows O 33.0 -> 27.5 us, head of 151936 columns 363 -> 316 us, the rest alike.  Two layers and a
+// head of 8192 columns, 1 / 9 / 17 / 38 / 65 rows: 445 -> 418, 453 -> 427, 501 -> 450, 546 -> 509, 659 -> 603 us a call.
 GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
   if (R > TS_MROWS_PER_BLOCK) {   // batches: the many-row kernel
     int mt, cfg, splits;

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
   // pairs, so that the row blocks of a slab follow each other on one XCD (two at a run's ends).  Whole
   // slabs dealt round robin loaded the XCDs unevenly (12 slabs: 2 on four of them, 1 on the others), and
   // the planner paid for it with K splits: 2048 rows x 6144 columns 180.4 us and four partial sums to
-  // re-read (20.4 instead of 36.2 us in k_rope_kv now), 178.4 us and one.
+  // re-read (20.4 instead of 36.2 us in k_rope_kv now), 178.4 us and one (170 us with 32-bit lane offsets, below).
   const int wgs = a.n_units * a.n_rblocks;
   const int place = (blockIdx.x & 7) * ((wgs + 7) / 8) + (blockIdx.x >> 3);
   if (place >= wgs) return;
