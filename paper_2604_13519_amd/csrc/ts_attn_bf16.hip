@@ -403,7 +403,7 @@ constexpr int kMergeFew = 16;
 bool merge_few(int slots, int splits) { return splits <= kMergeFew && slots >= (splits <= 8 ? 4096 : 5120); }
 
 __global__ __launch_bounds__(256) void k_attn_merge_few(const uint16_t* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                        f16_t* __restrict__ Ab, size_t a_plane, int slots, int HD, int splits,
+                                                        f16_t* __restrict__ Ab, size_t a_plane, int slots, int Hq, int HD, int splits,
                                                         unsigned long long* __restrict__ sat) {
   const int tps = HD / 8;                  // threads per slot
   const int slot = blockIdx.x * (256 / tps) + threadIdx.x / tps, d8 = threadIdx.x % tps;
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(256) void k_attn_merge_few(const uint16_t* __restri
     }
   }
   // the attention output feeds the O projection as a hi and a lo half
-  f16_t* dst = Ab + (size_t)slot * HD + d8 * 8;
+  f16_t* dst = Ab + (size_t)(slot / Hq) * act_ld(Hq * HD) + slot % Hq * HD + d8 * 8;
   st_act_planes4(dst, a_plane, num[0] / den, num[1] / den, num[2] / den, num[3] / den, sat);
   st_act_planes4(dst + 4, a_plane, num[4] / den, num[5] / den, num[6] / den, num[7] / den, sat);
 }
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__
     den += r_den[k * tpp + d4];
   }
   // the attention output feeds the O projection as a hi and a lo half
-  st_act_planes4(Ab + slot * HD + d4 * 4, a_plane, num.x / den, num.y / den, num.z / den, num.w / den, sat);
+  st_act_planes4(Ab + slot / Hq * act_ld(Hq * HD) + slot % Hq * HD + d4 * 4, a_plane, num.x / den, num.y / den, num.z / den, num.w / den, sat);
 }
 
 // Rows are covered by RS waves per head, MT tiles of 16 rows each: (tiles -> RS x MT)
@@ -578,12 +578,12 @@ void launch_attn_bf16(ts_model* m, const RowMeta& rm, int R, int n_seqs, int lay
 void launch_attn_merge(ts_model* m, int R, int splits) {
   ProfScope ps(m, "attn_merge");
   const ts_model_config& c = m->cfg;
-  const size_t plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * m->q_dim;
+  const size_t plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * act_ld(m->q_dim);
   const int slots = R * c.n_q_heads;
   if (merge_few(slots, splits)) {
     const int per_wg = 256 / (c.head_dim / 8);
     hipLaunchKernelGGL(k_attn_merge_few, dim3((slots + per_wg - 1) / per_wg), dim3(256), 0, m->stream, m->attn_part_o, m->attn_part_ml,
-                       (f16_t*)m->Ab, plane, slots, c.head_dim, splits, m->sat_count);
+                       (f16_t*)m->Ab, plane, slots, c.n_q_heads, c.head_dim, splits, m->sat_count);
     return;
   }
   hipLaunchKernelGGL(k_attn_merge, dim3(R * c.n_q_heads), dim3(256), 0, m->stream, m->attn_part_o, m->attn_part_ml,

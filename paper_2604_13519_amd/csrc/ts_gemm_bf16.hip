@@ -38,14 +38,14 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 struct GemmArgs {
-  const f16_t* X;      // [2 planes][rows][K] IEEE half (x = hi + lo), rows padded in memory
+  const f16_t* X;      // [2 planes][rows][act_ld(K)] IEEE half (x = hi + lo)
   size_t x_plane;      // elements between the hi and the lo plane
   const f16_t* Wt;     // tiled weights, IEEE half
   float* out;          // [split][R][N] partial sums (nullptr for ARGMAX)
   float* logits;       // [R][N] or nullptr (ARGMAX only)
   float* aval;         // [R][amax_parts]
   int32_t* aidx;
-  f16_t* act_out;      // SWIGLU: [2 planes][rows][N/2] gated product, IEEE half hi + lo
+  f16_t* act_out;      // SWIGLU: [2 planes][rows][act_ld(N/2)] gated product, IEEE half hi + lo
   size_t act_plane;    // elements between its planes
   unsigned long long* sat;   // counts gated products beyond half's range
   int R, N, K;
@@ -61,7 +61,7 @@ struct GemmArgs {
 
 enum { MODE_PARTIAL = 0, MODE_ARGMAX = 1, MODE_SWIGLU = 2 };
 
-template <int MT, int NT, int CS, int KW, int KC, int PF, int MODE, int XPAD = 8>
+template <int MT, int NT, int CS, int KW, int KC, int PF, int MODE, int XPAD = 16>
 __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   constexpr int WAVES = CS * KW;            // CS column sets x KW k-step owners
   constexpr bool ARGMAX = MODE == MODE_ARGMAX;
@@ -69,7 +69,11 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   constexpr int KSW = KSTEPS / KW;          // ... of which this wave multiplies KSW
   static_assert(KSTEPS % KW == 0 && KSW >= 1, "k-steps of a chunk must divide among the k-waves");
   static_assert(MODE != MODE_SWIGLU || NT == 2, "gate and up tiles alternate");
-  constexpr int XS = KC + XPAD;             // LDS row stride in elements (+16 B: bank spread, keeps alignment)
+  // LDS row stride in elements.  A 16-byte read is served in four groups of 16 lanes that are not consecutive (lanes
+  // 0-3, 12-15, 20-27 make the first): with rows 16 (2 mod 4) bytes apart, as with 32 more than KC, their 16-byte
+  // vectors fall into 16 different bank groups.  16 bytes more left a conflict in every read, half of the LDS cycles
+  // (counters: gate/up 65 rows 11.8 -> 7.2 M cycles).
+  constexpr int XS = KC + XPAD;
   constexpr int NTHR = 64 * WAVES;
   constexpr int NBUF = PF + 1;              // weight register ring
   constexpr int PL = TS_ACT_PLANES;         // an activation is the sum of a hi and a lo half
@@ -122,7 +126,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
     // O 9.2 -> 8.8 us
     const int row = rl < a.R ? rl : a.zero_row;
     x_lo[p] = XPP ? p >= XPP : __builtin_amdgcn_readfirstlane(v / XVP) != 0;
-    x_off[p] = ((uint32_t)row * (uint32_t)a.K + cv * 8) * 2;
+    x_off[p] = ((uint32_t)row * (uint32_t)act_ld(a.K) + cv * 8) * 2;
   }
 
   f32x4 acc[MT][NT];
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
       const int f = (nt_idx[0] >> 1) * 16 + l15;           // tiles 2j / 2j+1 = gate / up of features 16j..
       if (nt_idx[NT - 1] < a.n_tiles) {
         const float gv = v[0], uv = v[NT - 1];
-        st_act_planes(a.act_out + (size_t)row * (a.N / 2) + f, a.act_plane, gv / (1.0f + expf(-gv)) * uv, a.sat);
+        st_act_planes(a.act_out + (size_t)row * act_ld(a.N / 2) + f, a.act_plane, gv / (1.0f + expf(-gv)) * uv, a.sat);
       }
     } else {
       float* o = a.out + (size_t)split * a.split_stride;
@@ -318,7 +322,7 @@ void launch_mt(int mt, dim3 grid, hipStream_t s, const GemmArgs& a) {
 
 // The compiled tile shapes.  shape id -> (NT, CS, KW): tiles per wave, column sets and
 // k-waves per workgroup.  All use chunks of 128 k (the LDS holds two buffers of the
-// activation chunk in both planes, 85 KiB for 80 rows).  The k-wave shapes hold fewer weight registers
+// activation chunk in both planes, 90 KiB for 80 rows).  The k-wave shapes hold fewer weight registers
 // per chunk and prefetch two to four chunks ahead instead of one.
 constexpr int kNumShapes = 7;
 const int kShapeNT[kNumShapes] = {1, 2, 1, 2, 2, 1, 2};
@@ -438,15 +442,15 @@ void launch_gemm_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, 
   }
   GemmArgs a;
   a.X = X; a.Wt = Wt; a.out = out; a.logits = logits;
-  a.x_plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * K;
-  a.act_plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * (N / 2);
+  a.x_plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * act_ld(K);
+  a.act_plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * act_ld(N / 2);
   a.aval = m->amax_val; a.aidx = m->amax_idx;
   a.act_out = act_out;
   a.sat = m->sat_count;
   a.R = R; a.N = N; a.K = K;
   // the first spare row, which nothing writes; the last real row where 32 bits do not reach the spare ones (those
   // outputs are not used, a row of zeros is only the cheaper one)
-  a.zero_row = ((size_t)m->ws_rows + 1) * K * 2 < ((size_t)1 << 32) ? m->ws_rows : R - 1;
+  a.zero_row = ((size_t)m->ws_rows + 1) * act_ld(K) * 2 < ((size_t)1 << 32) ? m->ws_rows : R - 1;
   const int splits = mode == MODE_PARTIAL ? plan.splits : 1;
   a.kper = K / splits;
   a.n_tiles = (N + 15) / 16;

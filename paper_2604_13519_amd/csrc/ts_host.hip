@@ -183,12 +183,12 @@ static ts_status ensure_workspace(ts_model* m, int rows, int seqs, bool want_log
     const int scap = std::max(seqs, 1);
     const size_t esz = m->esz;
     if ((st = dev_alloc_bytes((void**)&m->H, (size_t)alloc_rows * c.d_model * 4, true))) return st;
-    // projection inputs of bf16 models: a hi plane and a lo plane of IEEE halves, alloc_rows apart
-    const size_t planes = c.dtype == TS_DTYPE_BF16 ? 2 : 1;
-    if ((st = dev_alloc_bytes(&m->Xn, planes * alloc_rows * c.d_model * esz, true))) return st;
+    // projection inputs of bf16 models: a hi plane and a lo plane of IEEE halves, alloc_rows rows of act_ld(K) apart
+    auto act_elems = [&](int K) { return c.dtype == TS_DTYPE_BF16 ? 2 * alloc_rows * act_ld(K) : (size_t)alloc_rows * K; };
+    if ((st = dev_alloc_bytes(&m->Xn, act_elems(c.d_model) * esz, true))) return st;
     if ((st = dev_alloc_bytes(&m->Qb, (size_t)alloc_rows * m->q_dim * esz, true))) return st;
-    if ((st = dev_alloc_bytes(&m->Ab, planes * alloc_rows * m->q_dim * esz, true))) return st;
-    if ((st = dev_alloc_bytes(&m->Fb, planes * alloc_rows * c.d_ffn * esz, true))) return st;
+    if ((st = dev_alloc_bytes(&m->Ab, act_elems(m->q_dim) * esz, true))) return st;
+    if ((st = dev_alloc_bytes(&m->Fb, act_elems(c.d_ffn) * esz, true))) return st;
     size_t pe = 0;
     if (c.dtype == TS_DTYPE_BF16) {
       const int Ns[4] = {m->qkv_dim, c.d_model, 2 * c.d_ffn, c.d_model};
@@ -970,9 +970,9 @@ extern "C" ts_status ts_get_hidden(ts_model* m, int32_t row, float* host_hidden)
   }
   // bf16 models keep the normalised activations as a hi and a lo IEEE half: widened and added
   std::vector<uint16_t> hx(d), lx(d);
-  const size_t plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * d;
-  TS_HIP(copy_sync(m->stream, hx.data(), (const f16_t*)m->Xn + (size_t)row * d, (size_t)d * 2, hipMemcpyDeviceToHost));
-  TS_HIP(copy_sync(m->stream, lx.data(), (const f16_t*)m->Xn + plane + (size_t)row * d, (size_t)d * 2, hipMemcpyDeviceToHost));
+  const size_t plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * act_ld(d);
+  TS_HIP(copy_sync(m->stream, hx.data(), (const f16_t*)m->Xn + (size_t)row * act_ld(d), (size_t)d * 2, hipMemcpyDeviceToHost));
+  TS_HIP(copy_sync(m->stream, lx.data(), (const f16_t*)m->Xn + plane + (size_t)row * act_ld(d), (size_t)d * 2, hipMemcpyDeviceToHost));
   for (int i = 0; i < d; ++i) host_hidden[i] = half_bits_to_float(hx[i]) + half_bits_to_float(lx[i]);
   return TS_OK;
 }

@@ -25,6 +25,13 @@ ts_status ts_fail(ts_status code, const char* fmt, ...);
 constexpr int TS_MROWS_PER_BLOCK = 80;  // rows one GEMM pass covers (5 MFMA tiles of 16)
 constexpr int TS_ATTN_KB = 64;          // keys per attention block (4 pages)
 
+// Row stride, in halves, of the activation planes that feed a projection of K inputs: 128 bytes more than the row,
+// so that the same few columns of many rows, which is what a staged chunk is, do not all lie a power of two apart.
+// Between events, K alone : K + 64 - 38 rows gate/up 45.6 : 45.2 us, 528 rows down 106.5 : 105.0 us, 260 rows x 5120
+// head 150 : 146 us, whole call of 38 rows 1270 : 1257 us (64 bytes more cost 1 % instead, 256 bytes do the same).
+constexpr int TS_ACT_PAD = 64;
+inline __host__ __device__ size_t act_ld(int K) { return (size_t)K + TS_ACT_PAD; }
+
 // Per-row metadata of one verify pass, structure of arrays in one device buffer.
 struct RowMeta {
   int32_t* tok;      // token id
@@ -117,10 +124,10 @@ struct ts_model {
   // workspace, sized for ws_rows rows (multiple of TS_MROWS_PER_BLOCK)
   int ws_rows, ws_seqs;
   float* H;                     // residual stream [rows][d] fp32
-  void* Xn;                     // normalised activations [rows][d]; float, or IEEE half for bf16 models
+  void* Xn;                     // normalised activations: float [rows][d], or IEEE half [2][rows][act_ld(d)] for bf16 models
   void* Qb;                     // rotated queries [rows][q_dim]; float, or IEEE half for bf16 models
-  void* Ab;                     // attention output [rows][q_dim]; float, or IEEE half for bf16 models
-  void* Fb;                     // SwiGLU product [rows][F]; float, or IEEE half for bf16 models
+  void* Ab;                     // attention output, likewise
+  void* Fb;                     // SwiGLU product, likewise
   float* part;                  // split-K partial sums, [S][rows][N] fp32
   size_t part_elems;
   uint16_t* attn_part_o;        // [rows][Hq][splits][hd], IEEE half (each split's normalised output)

@@ -123,7 +123,7 @@ void launch_embed(ts_model* m, const RowMeta& rm, int R, int n_seqs) {
 template <typename T>
 __global__ __launch_bounds__(1024) void k_norm(float* __restrict__ H, const float* __restrict__ part, int n_parts,
                                                size_t part_stride, const float* __restrict__ gain,
-                                               T* __restrict__ Xn, size_t x_plane, int d, float eps,
+                                               T* __restrict__ Xn, size_t x_plane, size_t x_ld, int d, float eps,
                                                unsigned long long* __restrict__ sat) {
   __shared__ float red[16];
   const int r = blockIdx.x;
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(1024) void k_norm(float* __restrict__ H, const floa
   for (int w = 0; w < 16; ++w) tot += red[w];
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
   auto emit = [&](int i, const float4& v, const float4& g) {
-    st_act4(Xn + (size_t)r * d + 4 * i, x_plane, make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w), sat);
+    st_act4(Xn + r * x_ld + 4 * i, x_plane, make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w), sat);
   };
 #pragma unroll
   for (int k = 0; k < KEEP; ++k) {
@@ -182,10 +182,10 @@ void launch_norm(ts_model* m, int R, const float* gain, int n_parts, size_t part
   ProfScope ps(m, "residual_rmsnorm");
   if (m->cfg.dtype == TS_DTYPE_BF16)
     hipLaunchKernelGGL(k_norm<f16_t>, dim3(R), dim3(1024), 0, m->stream, m->H, m->part, n_parts, part_stride, gain,
-                       (f16_t*)m->Xn, (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * m->cfg.d_model, m->cfg.d_model, m->cfg.rms_eps, m->sat_count);
+                       (f16_t*)m->Xn, (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * act_ld(m->cfg.d_model), act_ld(m->cfg.d_model), m->cfg.d_model, m->cfg.rms_eps, m->sat_count);
   else
     hipLaunchKernelGGL(k_norm<float>, dim3(R), dim3(1024), 0, m->stream, m->H, m->part, n_parts, part_stride, gain,
-                       (float*)m->Xn, (size_t)0, m->cfg.d_model, m->cfg.rms_eps, (unsigned long long*)nullptr);
+                       (float*)m->Xn, (size_t)0, (size_t)m->cfg.d_model, m->cfg.d_model, m->cfg.rms_eps, (unsigned long long*)nullptr);
 }
 
 // ---------------------------------------------------------------------------------
