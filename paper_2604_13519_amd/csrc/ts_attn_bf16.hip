@@ -6,7 +6,7 @@
 // 64-bit ancestor set per row plus "root is always visible"; it only matters for the key
 // blocks that overlap [P, P+M).
 //
-// Work split: grid = (key splits, KV head x head group, sequence).  A workgroup streams
+// Work split: grid = (unit of key blocks, KV head x head group), see attn_bf16_units.  A workgroup streams
 // its key range once in blocks of 64 keys (4 pages) through double-buffered LDS and serves
 // up to 4 query heads of the same KV head, one wave per head, all M rows of that head per
 // wave - so each K/V byte is read from HBM once per KV head.
@@ -28,7 +28,8 @@
 // rescale is an exact power of two;
 // probabilities 2^(s - ref) are rounded to half for the second product and the row sum
 // accumulates those rounded values (an extra MFMA against an all-ones operand, fp32 exact).
-// Partial (max, sum, O) per split are combined by k_attn_merge.
+// Partial (max, sum, O) per split (unit of its sequence) are combined by k_attn_merge.
+#include <algorithm>
 #include <type_traits>
 
 #include "ts_internal.h"
@@ -47,10 +48,10 @@ constexpr int KB = TS_ATTN_KB;   // keys per block
 struct AttnArgs {
   const bf16_t* Qb;          // [rows][Hq*HD], IEEE half bit patterns
   const uint64_t* row_anc;   // [rows]
-  const SeqDesc* seqs;
+  const AttnUnit* units;
   uint16_t* part_o;          // [R][Hq][splits][HD], IEEE half: the split's output divided by its row sum
   float* part_ml;            // [R][Hq][splits][2]
-  int layer, Hq, Hkv, R, splits, n_seqs;
+  int layer, Hq, Hkv, splits, n_units;   // splits: slots per (row, head) in the partial buffers
   float scale;               // 1/sqrt(head_dim) * log2(e): scores are kept in log2 units
 };
 
@@ -90,38 +91,38 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
   constexpr int DT = HD / 16;             // 16-dim tiles of the output
   constexpr int NTHR = 64 * HB * RS;
   constexpr int VPP = 2 * HD;             // 16-byte vectors per K page (and per V page)
-  constexpr int VTS = 40;                 // LDS row stride of the V^T of a 32-key half block, in tokens
+  constexpr int VTS = 32;                 // LDS row stride of the V^T of a 32-key half block, in tokens
   constexpr int VPG = 2 * VPP;            // 16-byte vectors per page, K then V
   constexpr int JP = (VPG + NTHR - 1) / NTHR;   // staged vectors per thread and page
   constexpr int NV = 4 * JP;              // staged vectors per thread and key block
-  __shared__ __attribute__((aligned(16))) bf16_t ks_[2][KB][HD + 8];
+  // Both arrays are read without bank conflicts: a 16-byte read is served in groups of 16 lanes that hold rows 0-3 and
+  // 12-15 of one lane group and rows 4-11 of the next, which suits rows 32 bytes apart (K) and 64-byte rows of which
+  // the second half of every 8 has its four vectors reversed (V^T).  Rows 16 bytes apart left half of the LDS cycles
+  // to conflicts (counters, 65 rows x 4 sequences: 80 -> 46 M cycles; time 397 -> 395 us).
+  __shared__ __attribute__((aligned(16))) bf16_t ks_[2][KB][HD + 16];
   // V^T of a half block (2 pages = 32 keys): per head-dim row, the keys in the order the second
   // MFMA wants them - lane group g holds tokens 4g..4g+3 of the first page, then of the second -
-  // so that a lane's operand is one 16-byte read.  Rows are padded to 40 tokens (80 B): 16 lanes
-  // reading 16 B from 16 consecutive rows then fall into 16 distinct groups of 4 banks.
+  // so that a lane's operand is one 16-byte read, and a thread that stages 8 tokens of both pages writes two.
   __shared__ __attribute__((aligned(16))) bf16_t vs_[2][2][HD][VTS];
 
+  auto v_col = [](int d, int grp) { return (grp ^ (d >> 2 & 1) * 3) * 8; };   // where lane group grp's 8 tokens of row d are
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l15 = lane & 15, g4 = lane >> 4;
   const int G = a.Hq / a.Hkv;
   const int subs = G / HB;
   // Workgroups are dealt to the 8 XCDs round-robin by linear id.  The `subs` workgroups that
-  // share one (sequence, KV head, key split) read the same K/V, so they are given ids that
+  // share one (unit, KV head) read the same K/V, so they are given ids that
   // differ by 8: same XCD, same L2, dispatched back to back.
   const int bid = blockIdx.x;
   const int jj = bid >> 3;
   const int rest = (jj / subs) * 8 + (bid & 7);
-  if (rest >= a.splits * a.Hkv * a.n_seqs) return;
-  const int split = rest % a.splits;
-  const int g = (rest / a.splits) % a.Hkv;
+  if (rest >= a.n_units * a.Hkv) return;
+  const int g = rest % a.Hkv;
   const int h = g * G + (jj % subs) * HB + (wave % HB);
   const int tile0 = (wave / HB) * MT0;    // first 16-row tile of this wave
-  const SeqDesc sd = a.seqs[rest / (a.splits * a.Hkv)];
+  const AttnUnit sd = a.units[rest / a.Hkv];
   const int P = sd.P, M = sd.M, T = P + M;
-  const int n_blk = (T + KB - 1) / KB;
-  const int bps = (n_blk + a.splits - 1) / a.splits;
-  const int b0 = split * bps;
-  const int b1 = min(n_blk, b0 + bps);
+  const int b0 = sd.b0, b1 = sd.b1, split = sd.split;
 
   const size_t page_elems = (size_t)a.Hkv * 16 * HD;
   const TS_GLOBAL bf16_t* kl = (const TS_GLOBAL bf16_t*)sd.k_pool + (size_t)a.layer * sd.n_pages * page_elems + (size_t)g * 16 * HD;
@@ -160,20 +161,21 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
   // 8192 keys, 16 KV heads of one query head: 64 us, 115 us with the unrolled halves around the call, 25 us inline.
   auto store_block = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
+    for (int p = 0; p < 4; p += 2)
 #pragma unroll
       for (int j = 0; j < JP; ++j) {
         const int w = tid + j * NTHR;
         if (VPG % NTHR != 0 && w >= VPG) continue;
+        const u32x4 v0 = to_half8(stage[p * JP + j]), v1 = to_half8(stage[(p + 1) * JP + j]);
         if (w < VPP) {
           const int t = w / (HD / 8), dv = w % (HD / 8);
-          *reinterpret_cast<u32x4*>(&ks_[buf][p * 16 + t][dv * 8]) = to_half8(stage[p * JP + j]);
+          *reinterpret_cast<u32x4*>(&ks_[buf][p * 16 + t][dv * 8]) = v0;
+          *reinterpret_cast<u32x4*>(&ks_[buf][p * 16 + 16 + t][dv * 8]) = v1;
         } else {
-          const int w2 = w - VPP;
-          const u32x4 v = to_half8(stage[p * JP + j]);     // 8 tokens of one head-dim row
-          // tokens 8 (w2 & 1) .. +8 of page p: two groups of 4, lane groups 2 (w2 & 1) and 2 (w2 & 1) + 1
-          *reinterpret_cast<u32x2*>(&vs_[buf][p >> 1][w2 >> 1][(w2 & 1) * 16 + (p & 1) * 4]) = u32x2{v.x, v.y};
-          *reinterpret_cast<u32x2*>(&vs_[buf][p >> 1][w2 >> 1][(w2 & 1) * 16 + 8 + (p & 1) * 4]) = u32x2{v.z, v.w};
+          // 8 tokens of one head-dim row from either page of the half block: two lane groups' operands
+          const int d = (w - VPP) >> 1, g0 = (w - VPP) & 1;
+          *reinterpret_cast<u32x4*>(&vs_[buf][p >> 1][d][v_col(d, 2 * g0)]) = u32x4{v0.x, v0.y, v1.x, v1.y};
+          *reinterpret_cast<u32x4*>(&vs_[buf][p >> 1][d][v_col(d, 2 * g0 + 1)]) = u32x4{v0.z, v0.w, v1.z, v1.w};
         }
       }
   };
@@ -265,7 +267,7 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
       auto k_frag = [&](int i) {
         return *reinterpret_cast<const f16x8*>(&ks_[cur][(2 * k2 + i / KSQ) * 16 + l15][(i % KSQ) * 32 + g4 * 8]);
       };
-      auto v_frag = [&](int dt) { return *reinterpret_cast<const f16x8*>(&vs_[cur][k2][dt * 16 + l15][g4 * 8]); };
+      auto v_frag = [&](int dt) { return *reinterpret_cast<const f16x8*>(&vs_[cur][k2][dt * 16 + l15][v_col(l15, g4)]); };
       f16x8 kf[NKF];
 #pragma unroll
       for (int i = 0; i < FD; ++i) kf[i] = k_frag(i);
@@ -403,13 +405,15 @@ constexpr int kMergeFew = 16;
 bool merge_few(int slots, int splits) { return splits <= kMergeFew && slots >= (splits <= 8 ? 4096 : 5120); }
 
 __global__ __launch_bounds__(256) void k_attn_merge_few(const uint16_t* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                        f16_t* __restrict__ Ab, size_t a_plane, int slots, int Hq, int HD, int splits,
+                                                        f16_t* __restrict__ Ab, size_t a_plane, int slots, int Hq, int HD, int stride,
+                                                        const int32_t* __restrict__ row_splits,
                                                         unsigned long long* __restrict__ sat) {
   const int tps = HD / 8;                  // threads per slot
   const int slot = blockIdx.x * (256 / tps) + threadIdx.x / tps, d8 = threadIdx.x % tps;
   if (slot >= slots) return;
-  const float2* ml = reinterpret_cast<const float2*>(part_ml) + (size_t)slot * splits;
-  const uint4* po = reinterpret_cast<const uint4*>(part_o) + (size_t)slot * splits * tps + d8;
+  const float2* ml = reinterpret_cast<const float2*>(part_ml) + (size_t)slot * stride;
+  const uint4* po = reinterpret_cast<const uint4*>(part_o) + (size_t)slot * stride * tps + d8;
+  const int splits = row_splits ? row_splits[slot / Hq] : stride;
   float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, den = 0.f, mstar = -INFINITY;
   float2 w[kMergeFew];
 #pragma unroll
@@ -447,7 +451,8 @@ __global__ __launch_bounds__(256) void k_attn_merge_few(const uint16_t* __restri
 constexpr int kMergeMaxSplits = 512;
 
 __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                    f16_t* __restrict__ Ab, size_t a_plane, int R, int Hq, int HD, int splits,
+                                                    f16_t* __restrict__ Ab, size_t a_plane, int Hq, int HD, int stride,
+                                                    const int32_t* __restrict__ row_splits,
                                                     unsigned long long* __restrict__ sat) {
   __shared__ float s_m[kMergeMaxSplits], s_l[kMergeMaxSplits];
   __shared__ float4 r_num[256];
@@ -456,11 +461,13 @@ __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__
   const int tpp = HD / 4;                  // threads per group: four dims of the head each
   const int groups = 256 / tpp;
   const int grp = tid / tpp, d4 = tid % tpp;
-  const size_t slot = blockIdx.x;
+  const int row = blockIdx.y, head = blockIdx.x;
+  const size_t slot = (size_t)row * Hq + head;
+  const int splits = row_splits ? row_splits[row] : stride;
   const float2* ml = reinterpret_cast<const float2*>(part_ml);
   const uint2* po = reinterpret_cast<const uint2*>(part_o);     // 4 halves
   for (int sp = tid; sp < splits; sp += 256) {
-    const float2 v = ml[slot * splits + sp];
+    const float2 v = ml[slot * stride + sp];
     s_m[sp] = v.x;
     s_l[sp] = v.y;
   }
@@ -468,7 +475,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int sp = grp + u * groups;
-    o4[u] = sp < splits ? po[(slot * splits + sp) * tpp + d4] : make_uint2(0u, 0u);
+    o4[u] = sp < splits ? po[(slot * stride + sp) * tpp + d4] : make_uint2(0u, 0u);
   }
   __syncthreads();
   float mstar = -INFINITY;
@@ -480,7 +487,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int sp = s0 + grp + u * groups;
-        o4[u] = sp < splits ? po[(slot * splits + sp) * tpp + d4] : make_uint2(0u, 0u);
+        o4[u] = sp < splits ? po[(slot * stride + sp) * tpp + d4] : make_uint2(0u, 0u);
       }
     }
 #pragma unroll
@@ -504,7 +511,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__
     den += r_den[k * tpp + d4];
   }
   // the attention output feeds the O projection as a hi and a lo half
-  st_act_planes4(Ab + slot / Hq * act_ld(Hq * HD) + slot % Hq * HD + d4 * 4, a_plane, num.x / den, num.y / den, num.z / den, num.w / den, sat);
+  st_act_planes4(Ab + row * act_ld(Hq * HD) + head * HD + d4 * 4, a_plane, num.x / den, num.y / den, num.z / den, num.w / den, sat);
 }
 
 // Rows are covered by RS waves per head, MT tiles of 16 rows each: (tiles -> RS x MT)
@@ -533,49 +540,93 @@ int heads_per_block(int G) { return G >= 4 ? 4 : (G >= 2 ? 2 : 1); }
 
 }  // namespace
 
-// Number of key splits (every sequence is cut into the same number of splits, each covering
-// ceil(blocks / splits) of ITS key blocks).  One sequence: enough workgroups to cover the CUs
-// once.  Several sequences of different lengths: one round would be as slow as the longest
-// sequence's share, so the splits are made fine enough that the longest workgroup carries at
-// most half of a CU's average load and the dispatcher can even the rest out over a few rounds.
-int attn_bf16_splits(const ts_model* m, int max_keys, int n_seqs, long sum_keys) {
-  const int G = m->cfg.n_q_heads / m->cfg.n_kv_heads;
-  const int subs = G / heads_per_block(G);
-  const int per_split = m->cfg.n_kv_heads * subs * n_seqs;
-  const int n_blk = (max_keys + KB - 1) / KB;
-  const int wg_per_cu = heads_per_block(G) <= 2 ? 2 : 1;
-  int want = (wg_per_cu * m->n_cu + per_split - 1) / per_split;
-  if (n_seqs > 1) {
-    const double avg_per_cu = (double)((sum_keys + KB - 1) / KB) * m->cfg.n_kv_heads * subs / m->n_cu;
-    const int fine = (int)((double)n_blk / (avg_per_cu > 2.0 ? avg_per_cu / 2.0 : 1.0) + 0.999);
-    if (fine > want) want = fine < 16 ? fine : 16;          // partial sums grow with the split count
+// How the key blocks of a pass are dealt to workgroups.  A unit is a run of key blocks of one sequence; every
+// KV head (times the head groups that share its K/V) makes one workgroup of each unit.
+// One sequence: as many equal units as cover the CUs once.
+// Several: no unit is longer than L blocks, and L is the smallest with which the units make r workgroups a CU; r is
+// the one with the least modelled time: r full rounds of units or, where lengths leave the rounds ragged, the mean
+// load of a CU and half a unit; two workgroups that share a CU take one and a half times as long as one.  A sequence
+// gets units in proportion to its length, so that every workgroup has nearly the same share and the last round is
+// full.  Against one number of splits for all sequences, chosen so that the longest share is half of a CU's average
+// load (8B shape unless noted; us a launch): 4 x 32768 keys of 65 rows, 8 heads 397 -> 306 (576 workgroups were 2.25
+// rounds), 6 blocks of ingestion at 2000 39.0 -> 29.0, 8 x 4096 .. 2048 keys of 33 rows 49.5 -> 39.1, 16 x 8192 .. 2048
+// 104 -> 96, 8 x 8192 .. 2700 of 65 rows, 64 dims 68.5 -> 45.5, 16 x 17 rows 57 -> 48.5, 4 x 33 rows 29.1 -> 27.0 (two
+// workgroups a CU counted as one: 30.9).  The merge pays 0.5 us for reading a row's split count and gets it back
+// from fewer partials (16.5 -> 11.3, 11.0 -> 8.8, 14.0 -> 12.1 us in the first, second and fourth of these).
+// kUnitFixed: a workgroup's start and finish cost about as much as three blocks.
+constexpr int kUnitFixed = 3, kBatchSplits = 16;
+int attn_bf16_units(const ts_model* m, int n_seqs, const int* n_keys, int max_M, AttnUnit* units, int* seq_splits) {
+  const int G = m->cfg.n_q_heads / m->cfg.n_kv_heads, hb = heads_per_block(G);
+  const int per_unit = m->cfg.n_kv_heads * (G / hb);
+  int n_units = 0;
+  auto cut = [&](int s, int want) {
+    const int n_blk = (n_keys[s] + KB - 1) / KB, len = (n_blk + want - 1) / want;
+    seq_splits[s] = (n_blk + len - 1) / len;
+    for (int i = 0; i < seq_splits[s]; ++i, ++n_units) {
+      units[n_units].seq = s;
+      units[n_units].split = i;
+      units[n_units].b0 = i * len;
+      units[n_units].b1 = std::min(n_blk, (i + 1) * len);
+    }
+  };
+  if (n_seqs == 1) {
+    const int n_blk = (n_keys[0] + KB - 1) / KB, wg_per_cu = hb <= 2 ? 2 : 1;
+    cut(0, std::min(std::min((wg_per_cu * m->n_cu + per_unit - 1) / per_unit, n_blk), kMergeMaxSplits));
+    return n_units;
   }
-  if (want < 1) want = 1;
-  if (want > n_blk) want = n_blk;
-  if (want > kMergeMaxSplits) want = kMergeMaxSplits;      // the merge kernel keeps (max, sum) of every split in LDS
-  const int bps = (n_blk + want - 1) / want;
-  return (n_blk + bps - 1) / bps;
+  int longest = 0;
+  long total = 0;
+  for (int s = 0; s < n_seqs; ++s) {
+    longest = std::max(longest, (n_keys[s] + KB - 1) / KB);
+    total += (n_keys[s] + KB - 1) / KB;
+  }
+  const bool pairs = hb * (max_M > 48 ? 2 : 1) <= 4;     // up to four waves: two workgroups share a CU
+  const int per_round = std::max(1, m->n_cu / per_unit);
+  auto count = [&](int len) {
+    long u = 0;
+    for (int s = 0; s < n_seqs; ++s) u += ((n_keys[s] + KB - 1) / KB + len - 1) / len;
+    return u;
+  };
+  // partial sums grow with the split count: 16 of a sequence at most, more only if those leave CUs empty
+  const int cap = std::min(std::max(kBatchSplits, (per_round + n_seqs - 1) / n_seqs), kMergeMaxSplits);
+  const int r0 = (n_seqs + per_round - 1) / per_round, least = (longest + cap - 1) / cap;
+  double best = 1e300;
+  int best_len = longest;
+  for (int r = r0; r < r0 + 4; ++r) {
+    int lo = least, hi = longest;                        // count(hi) = n_seqs <= r * per_round
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      if (count(mid) <= (long)r * per_round) hi = mid;
+      else lo = mid + 1;
+    }
+    const double unit = lo + kUnitFixed, rounds = pairs ? r / 2 * 1.5 + r % 2 : r;
+    const double mean = (double)(total + kUnitFixed * count(lo)) / per_round * (pairs && r > 1 ? 0.75 : 1.0);
+    const double cost = std::min(rounds * unit, mean + 0.5 * unit);
+    if (cost < best) { best = cost; best_len = lo; }
+  }
+  for (int s = 0; s < n_seqs; ++s) cut(s, ((n_keys[s] + KB - 1) / KB + best_len - 1) / best_len);
+  return n_units;
 }
+int attn_bf16_max_units(const ts_model* m, int n_seqs) { return std::max(std::max(kMergeMaxSplits, kBatchSplits * n_seqs), m->n_cu + n_seqs); }
 
-void launch_attn_bf16(ts_model* m, const RowMeta& rm, int R, int n_seqs, int layer, int splits, int max_M) {
+void launch_attn_bf16(ts_model* m, const RowMeta& rm, int n_units, int layer, int splits, int max_M) {
   ProfScope ps(m, "attn_bf16");
   const ts_model_config& c = m->cfg;
   AttnArgs a;
-  a.Qb = (const bf16_t*)m->Qb; a.row_anc = rm.anc; a.seqs = m->seq_dev;
+  a.Qb = (const bf16_t*)m->Qb; a.row_anc = rm.anc; a.units = m->unit_dev;
   a.part_o = m->attn_part_o; a.part_ml = m->attn_part_ml;
-  a.layer = layer; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.R = R; a.splits = splits;
+  a.layer = layer; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.splits = splits; a.n_units = n_units;
   a.scale = (float)(1.4426950408889634 / sqrt((double)c.head_dim));   // 1/sqrt(hd) * log2(e)
   const int G = c.n_q_heads / c.n_kv_heads;
   const int hb = heads_per_block(G);
-  a.n_seqs = n_seqs;
-  const int units = splits * c.n_kv_heads * n_seqs;        // (sequence, KV head, key split) triples
-  dim3 grid(((units + 7) / 8) * 8 * (G / hb));
+  dim3 grid((n_units * c.n_kv_heads + 7) / 8 * 8 * (G / hb));
   const int mt = (max_M + 15) / 16;
   if (c.head_dim == 128) launch_hd<128>(hb, mt, grid, m->stream, a);
   else launch_hd<64>(hb, mt, grid, m->stream, a);
 }
 
-void launch_attn_merge(ts_model* m, int R, int splits) {
+// row_splits: splits of each row's sequence (nullptr: all have `splits`, the stride of the partial buffers)
+void launch_attn_merge(ts_model* m, int R, int splits, const int32_t* row_splits) {
   ProfScope ps(m, "attn_merge");
   const ts_model_config& c = m->cfg;
   const size_t plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * act_ld(m->q_dim);
@@ -583,9 +634,10 @@ void launch_attn_merge(ts_model* m, int R, int splits) {
   if (merge_few(slots, splits)) {
     const int per_wg = 256 / (c.head_dim / 8);
     hipLaunchKernelGGL(k_attn_merge_few, dim3((slots + per_wg - 1) / per_wg), dim3(256), 0, m->stream, m->attn_part_o, m->attn_part_ml,
-                       (f16_t*)m->Ab, plane, slots, c.n_q_heads, c.head_dim, splits, m->sat_count);
+                       (f16_t*)m->Ab, plane, slots, c.n_q_heads, c.head_dim, splits, row_splits, m->sat_count);
     return;
   }
-  hipLaunchKernelGGL(k_attn_merge, dim3(R * c.n_q_heads), dim3(256), 0, m->stream, m->attn_part_o, m->attn_part_ml,
-                     (f16_t*)m->Ab, plane, R, c.n_q_heads, c.head_dim, splits, m->sat_count);
+  // R fits the second grid dimension: beyond 65535 rows there are more slots than merge_few leaves to this kernel
+  hipLaunchKernelGGL(k_attn_merge, dim3(c.n_q_heads, R), dim3(256), 0, m->stream, m->attn_part_o, m->attn_part_ml,
+                     (f16_t*)m->Ab, plane, c.n_q_heads, c.head_dim, splits, row_splits, m->sat_count);
 }

@@ -155,19 +155,20 @@ static ts_status check_config(const ts_model_config& c) {
 static void free_workspace(ts_model* m) {
   dev_free(m->H); dev_free(m->Xn); dev_free(m->Qb); dev_free(m->Ab); dev_free(m->Fb); dev_free(m->part);
   dev_free(m->attn_part_o); dev_free(m->attn_part_ml); dev_free(m->rope_cs); dev_free(m->row_dst); dev_free(m->amax_val);
-  dev_free(m->amax_idx); dev_free(m->logits); dev_free(m->meta_dev); dev_free(m->seq_dev);
+  dev_free(m->amax_idx); dev_free(m->logits); dev_free(m->meta_dev); dev_free(m->seq_dev); dev_free(m->unit_dev);
   dev_free(m->samp_part); dev_free(m->samp_tok);
   if (m->rec_host) (void)hipHostFree(m->rec_host);
   if (m->seq_host) (void)hipHostFree(m->seq_host);
+  if (m->unit_host) (void)hipHostFree(m->unit_host);
   if (m->res_host) (void)hipHostFree(m->res_host);
   m->H = nullptr; m->Xn = m->Qb = m->Ab = m->Fb = nullptr; m->part = nullptr;
   m->attn_part_o = nullptr; m->attn_part_ml = nullptr; m->rope_cs = nullptr; m->row_dst = nullptr; m->amax_val = nullptr; m->amax_idx = nullptr;
-  m->logits = nullptr; m->meta_dev = nullptr; m->seq_dev = nullptr; m->rec_host = nullptr; m->seq_host = nullptr; m->res_host = nullptr;
+  m->logits = nullptr; m->meta_dev = nullptr; m->seq_dev = nullptr; m->unit_dev = nullptr; m->rec_host = nullptr; m->seq_host = nullptr; m->unit_host = nullptr; m->res_host = nullptr;
   m->samp_part = nullptr; m->samp_tok = nullptr;
   m->ws_rows = 0; m->ws_seqs = 0; m->logits_rows = 0; m->attn_max_splits = 0; m->part_elems = 0;
 }
 
-static size_t meta_bytes_for(int rows) { return (size_t)rows * (5 * sizeof(int32_t) + sizeof(uint64_t) + sizeof(float)); }
+static size_t meta_bytes_for(int rows) { return (size_t)rows * (6 * sizeof(int32_t) + sizeof(uint64_t) + sizeof(float)); }
 
 // Row buffers carry TS_MROWS_PER_BLOCK spare rows: tile-granular kernels read (never use)
 // rows past the last real one.
@@ -218,6 +219,11 @@ static ts_status ensure_workspace(ts_model* m, int rows, int seqs, bool want_log
     // pinned and device-visible: the row set-up kernel reads the first two, the walk writes the third
     TS_HIP(hipHostMalloc((void**)&m->rec_host, (size_t)alloc_rows * sizeof(RowRec), hipHostMallocDefault));
     TS_HIP(hipHostMalloc((void**)&m->seq_host, (size_t)scap * sizeof(SeqDesc), hipHostMallocDefault));
+    if (c.dtype == TS_DTYPE_BF16) {
+      const size_t units = attn_bf16_max_units(m, scap);
+      if ((st = dev_alloc_bytes((void**)&m->unit_dev, units * sizeof(AttnUnit), true))) return st;
+      TS_HIP(hipHostMalloc((void**)&m->unit_host, units * sizeof(AttnUnit), hipHostMallocDefault));
+    }
     TS_HIP(hipHostMalloc((void**)&m->res_host, (size_t)scap * TS_RESULT_INTS * sizeof(int32_t), hipHostMallocDefault));
     m->ws_rows = cap;
     m->ws_seqs = scap;
@@ -390,7 +396,7 @@ extern "C" ts_status ts_model_load(const ts_model_config* cfg, const ts_weights*
   m->attn_part_o = nullptr; m->attn_part_ml = nullptr; m->attn_max_splits = 0;
   m->rope_cs = nullptr; m->row_dst = nullptr; m->amax_val = nullptr; m->amax_idx = nullptr; m->logits = nullptr;
   m->keep_logits = false; m->logits_rows = 0; m->meta_dev = nullptr; m->rec_host = nullptr; m->seq_host = nullptr;
-  m->seq_dev = nullptr; m->res_host = nullptr; m->ws_rows = 0; m->ws_seqs = 0;
+  m->seq_dev = nullptr; m->unit_dev = nullptr; m->unit_host = nullptr; m->res_host = nullptr; m->ws_rows = 0; m->ws_seqs = 0;
   m->samp_part = nullptr; m->samp_tok = nullptr;
   m->prof_on = false; m->ev_used = 0; m->last_rows = 0;
   hipError_t e = hipGetDevice(&m->device);
@@ -733,7 +739,8 @@ static RowMeta carve_meta(void* base, int rows) {
   rm.lrow = (int32_t*)p; p += (size_t)rows * 4;
   rm.par = (int32_t*)p;  p += (size_t)rows * 4;
   rm.depth = (int32_t*)p; p += (size_t)rows * 4;
-  rm.u = (float*)p;
+  rm.u = (float*)p;      p += (size_t)rows * 4;
+  rm.splits = (int32_t*)p;
   return rm;
 }
 
@@ -754,7 +761,7 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
   const bool bf = c.dtype == TS_DTYPE_BF16;
   // ---- validation (nothing is modified before it passes) ---------------------------
   int R = 0, max_M = 0, max_keys = 0;
-  long sum_keys = 0;
+  int n_keys[TS_MAX_SEQS], seq_splits[TS_MAX_SEQS];
   for (int s = 0; s < n_seqs; ++s) {
     ts_kv* kv = kvs[s];
     if (!kv) return ts_fail(TS_ERR_INVALID_ARG, "null cache handle (sequence %d)", s);
@@ -776,7 +783,7 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
     R += n + 1;
     max_M = std::max(max_M, n + 1);
     max_keys = std::max(max_keys, P_s + n + 1);
-    sum_keys += P_s + n + 1;
+    n_keys[s] = P_s + n + 1;
   }
   if (!bf && (size_t)max_keys > attn_f32_max_keys())
     return ts_fail(TS_ERR_KV_CAPACITY, "fp32 path supports at most %zu keys per sequence", attn_f32_max_keys());
@@ -784,8 +791,10 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
   (void)hipSetDevice(m->device);
   ts_status st = ensure_workspace(m, R, n_seqs, sample != nullptr);
   if (st) return st;
-  const int splits = bf ? attn_bf16_splits(m, max_keys, n_seqs, sum_keys) : 1;
+  const int n_units = bf ? attn_bf16_units(m, n_seqs, n_keys, max_M, m->unit_host, seq_splits) : 0;
+  const int splits = bf ? *std::max_element(seq_splits, seq_splits + n_seqs) : 1;
   if ((st = ensure_attn_partials(m, splits, R))) return st;
+  const bool ragged = bf && *std::min_element(seq_splits, seq_splits + n_seqs) != splits;
 
   // ---- per-row bookkeeping (Alg. 1: flattened sequence + tree mask) ------------------
   const RowMeta dm = carve_meta(m->meta_dev, m->ws_rows + TS_MROWS_PER_BLOCK);
@@ -803,7 +812,7 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
       q.depth = i ? up.depth + 1 : 0;
       q.tok = i ? toks[node] : blocks ? blocks->root[s] : kv->pending;
       q.pos = P_s + q.depth;
-      q.seq = s; q.lrow = i; q.par = prow;
+      q.seq = s; q.lrow = i; q.par = prow; q.splits = bf ? seq_splits[s] : 1;
       q.u = sample && i ? sample->node_uniform[node] : 0.f;
       // the row's slot in layer 0; a layer adds layer_stride elements, a KV head 16 * head_dim
       const int slot = P_s + i;
@@ -819,6 +828,12 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
     kv->have_result = false;
     r0 += n + 1;
   }
+  for (int i = 0; i < n_units; ++i) {
+    AttnUnit& u = m->unit_host[i];
+    const SeqDesc& sd = m->seq_host[u.seq];
+    u.P = sd.P; u.M = sd.M; u.row0 = sd.row0; u.n_pages = sd.n_pages;
+    u.page_table = sd.page_table; u.k_pool = sd.k_pool; u.v_pool = sd.v_pool;
+  }
 
   // ---- the pass ---------------------------------------------------------------------
   m->prof.clear();
@@ -828,7 +843,7 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
   const bool time_pass = m->prof_on && m->prof_filter == "verify_pass";
   if (time_pass) prof_begin(m, "verify_pass");
   const size_t pass_rec = m->prof.size();
-  launch_embed(m, dm, R, n_seqs);       // + row metadata to the device, rotary table
+  launch_embed(m, dm, R, n_seqs, n_units);       // + row metadata to the device, rotary table
   int pending_parts = 0;          // split-K partials of the previous projection still to be added to H
   size_t pending_stride = 0;
   auto project = [&](const char* name, const void* X, const void* W, int N, int K, int* n_parts, size_t* stride) {
@@ -852,8 +867,8 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
     project("gemm_qkv", m->Xn, L.wqkv, m->qkv_dim, d, &np, &ps);
     launch_rope_kv(m, dm, R, l, np, ps);
     if (bf) {
-      launch_attn_bf16(m, dm, R, n_seqs, l, splits, max_M);
-      launch_attn_merge(m, R, splits);
+      launch_attn_bf16(m, dm, n_units, l, splits, max_M);
+      launch_attn_merge(m, R, splits, ragged ? dm.splits : nullptr);
     } else {
       launch_attn_f32(m, dm, R, n_seqs, l, max_keys);
     }
@@ -948,7 +963,7 @@ extern "C" ts_status ts_verify_batch(ts_model* m, ts_kv* const* kvs, int32_t n_s
                                      const int32_t* parent_idx, const int32_t* node_offsets, int32_t* accept_len,
                                      int32_t* accepted_tokens, int32_t* accepted_nodes, int32_t* bonus_token) {
   if (!m || !kvs || !node_offsets || !accept_len || !bonus_token) return ts_fail(TS_ERR_INVALID_ARG, "ts_verify_batch: null argument");
-  if (n_seqs < 1 || n_seqs > 4096) return ts_fail(TS_ERR_INVALID_ARG, "n_seqs %d outside [1,4096]", n_seqs);
+  if (n_seqs < 1 || n_seqs > TS_MAX_SEQS) return ts_fail(TS_ERR_INVALID_ARG, "n_seqs %d outside [1,%d]", n_seqs, TS_MAX_SEQS);
   if (node_offsets[0] != 0) return ts_fail(TS_ERR_INVALID_ARG, "node_offsets[0] must be 0");
   for (int s = 0; s < n_seqs; ++s)
     if (node_offsets[s + 1] < node_offsets[s]) return ts_fail(TS_ERR_INVALID_ARG, "node_offsets must be non-decreasing");

@@ -23,6 +23,7 @@ ts_status ts_fail(ts_status code, const char* fmt, ...);
 
 // ---- geometry constants ---------------------------------------------------------
 constexpr int TS_MROWS_PER_BLOCK = 80;  // rows one GEMM pass covers (5 MFMA tiles of 16)
+constexpr int TS_MAX_SEQS = 4096;       // sequences of one batch
 constexpr int TS_ATTN_KB = 64;          // keys per attention block (4 pages)
 
 // Row stride, in halves, of the activation planes that feed a projection of K inputs: 128 bytes more than the row,
@@ -41,6 +42,7 @@ struct RowMeta {
   int32_t* depth;    // depth within its sequence (root 0)
   uint64_t* anc;     // bit i set iff draft node i is this row or one of its ancestors
   float* u;          // stochastic acceptance: the caller's uniform of this row's draft node
+  int32_t* splits;   // key splits of the row's sequence (attention merge)
 };
 
 // Per-sequence descriptor, device-visible.
@@ -57,6 +59,18 @@ struct SeqDesc {
 };
 constexpr int TS_RESULT_INTS = 4 + 2 * TS_MAX_NODES;
 
+// A run of key blocks of one sequence: the share of one attention workgroup (of every KV head and head group).
+struct AttnUnit {
+  int32_t P, M, row0, n_pages;         // as in SeqDesc
+  const int32_t* page_table;
+  void* k_pool;
+  void* v_pool;
+  int32_t b0, b1;                      // key blocks [b0, b1)
+  int32_t split;                       // which partial of its rows it writes
+  int32_t seq;                         // host only
+  int32_t pad[2];
+};
+
 // Where a row's new K and V go (layer 0, KV head 0): written once per pass, read by every layer's QKV epilogue.
 struct RowDst {
   void* k;                 // K page row of the slot: + layer * layer_stride + g * 16 * hd + dim
@@ -71,9 +85,10 @@ struct RowRec {
   RowDst dst;
   int32_t tok, pos, seq, lrow, par, depth;
   float u;
-  int32_t pad;
+  int32_t splits;
 };
 static_assert(sizeof(RowRec) == 64, "one line per row");
+static_assert(sizeof(AttnUnit) % 16 == 0, "copied in 16-byte vectors");
 
 struct ProfRec { const char* name; hipEvent_t a, b; };
 
@@ -145,6 +160,7 @@ struct ts_model {
   void* meta_dev;               // carved into RowMeta
   RowRec* rec_host; SeqDesc* seq_host;      // pinned, [rows], [ws_seqs]
   SeqDesc* seq_dev;
+  AttnUnit* unit_host; AttnUnit* unit_dev;  // pinned and device, [attn_bf16_max_units(ws_seqs)] (bf16 models)
   int32_t* res_host;            // pinned, ws_seqs * TS_RESULT_INTS
   // profiling
   bool prof_on;
@@ -159,7 +175,7 @@ struct ts_model {
 // misc kernels (ts_kernels_misc.hip)
 void launch_repack_tiles(hipStream_t s, const bf16_t* src, f16_t* dst, int N, int K, int n_tile0, int n_tile_stride,
                          int* range_flag);
-void launch_embed(ts_model* m, const RowMeta& rm, int R, int n_seqs);
+void launch_embed(ts_model* m, const RowMeta& rm, int R, int n_seqs, int n_units);
 void launch_norm(ts_model* m, int R, const float* gain, int n_parts, size_t part_stride, bool first);
 void launch_rope_kv(ts_model* m, const RowMeta& rm, int R, int layer, int n_parts, size_t part_stride);
 void launch_plain_read(ts_model* m, const void* src, size_t bytes, uint32_t* sink);
@@ -187,9 +203,10 @@ void gemm_rows_plan(const ts_model* m, int R, int N, int K, int mode, size_t max
 int gemm_rows_chunk(int cfg);
 void launch_gemm_rows_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* out, int R, int N, int K, int mt, int cfg,
                            int splits, int mode, f16_t* act_out, float* logits);
-int attn_bf16_splits(const ts_model* m, int max_keys, int n_seqs, long sum_keys);
-void launch_attn_bf16(ts_model* m, const RowMeta& rm, int R, int n_seqs, int layer, int splits, int max_M);
-void launch_attn_merge(ts_model* m, int R, int splits);
+int attn_bf16_units(const ts_model* m, int n_seqs, const int* n_keys, int max_M, AttnUnit* units, int* seq_splits);
+int attn_bf16_max_units(const ts_model* m, int n_seqs);
+void launch_attn_bf16(ts_model* m, const RowMeta& rm, int n_units, int layer, int splits, int max_M);
+void launch_attn_merge(ts_model* m, int R, int splits, const int32_t* row_splits);
 
 // profiling bracket
 void prof_begin(ts_model* m, const char* name);

@@ -62,9 +62,10 @@ void launch_repack_tiles(hipStream_t s, const bf16_t* src, f16_t* dst, int N, in
 
 // ---------------------------------------------------------------------------------
 // Per-row set-up of a pass, one workgroup per row:
-//  * the row's record (and, for the first n_seqs rows, one sequence descriptor each) comes straight
-//    out of the pinned memory the host wrote it to: one line over the bus per row, in place of copies
-//    around the pass (two copies down and one up per sequence: 8 - 14 us of a pass);
+//  * the row's record (and, for the first n_seqs rows, one sequence descriptor each, and a share of
+//    the attention units) comes straight out of the pinned memory the host wrote it to: one line over
+//    the bus per row, in place of copies around the pass (two copies down and one up per sequence:
+//    8 - 14 us of a pass);
 //  * embedding gather H[r][:] = E[tok[r]][:]  (the residual stream is fp32);
 //  * rotary table (cos, sin)(pos[r] * theta^(-2j/hd)) for j < hd/2, evaluated in double so that
 //    large positions lose no phase accuracy, stored as float.
@@ -79,6 +80,7 @@ __device__ __forceinline__ void widen_store(float* h, const bf16_t* e) {
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed_rope(const RowRec* __restrict__ rec, const SeqDesc* __restrict__ seq_src, int n_seqs,
                                                     RowMeta rm, RowDst* __restrict__ dst, SeqDesc* __restrict__ seq_dst,
+                                                    const AttnUnit* __restrict__ unit_src, AttnUnit* __restrict__ unit_dst, int n_units,
                                                     const T* __restrict__ E, float* __restrict__ H, int d,
                                                     float2* __restrict__ cs, int half, double theta) {
   __shared__ __attribute__((aligned(16))) RowRec s_rec;
@@ -88,6 +90,9 @@ __global__ __launch_bounds__(256) void k_embed_rope(const RowRec* __restrict__ r
   const int s = (int)threadIdx.x - 64;                            // the second wave
   if (r < n_seqs && s >= 0 && s < (int)(sizeof(SeqDesc) / 8))
     reinterpret_cast<uint64_t*>(seq_dst + r)[s] = reinterpret_cast<const uint64_t*>(seq_src + r)[s];
+  if (threadIdx.x >= 128)                                         // the other two: each wave waits for the bus once
+    for (int i = r * 128 + threadIdx.x - 128; i < n_units * (int)(sizeof(AttnUnit) / 16); i += gridDim.x * 128)
+      reinterpret_cast<uint4*>(unit_dst)[i] = reinterpret_cast<const uint4*>(unit_src)[i];
   __syncthreads();
   const T* e = E + (size_t)s_rec.tok * d;
   for (int i = threadIdx.x * 4; i < d; i += blockDim.x * 4) widen_store(H + (size_t)r * d + i, e + i);       // d is a multiple of 4
@@ -98,20 +103,20 @@ __global__ __launch_bounds__(256) void k_embed_rope(const RowRec* __restrict__ r
   }
   if (threadIdx.x == blockDim.x - 1) {
     rm.anc[r] = s_rec.anc; rm.tok[r] = s_rec.tok; rm.seq[r] = s_rec.seq; rm.lrow[r] = s_rec.lrow;
-    rm.par[r] = s_rec.par; rm.depth[r] = s_rec.depth; rm.u[r] = s_rec.u;
+    rm.par[r] = s_rec.par; rm.depth[r] = s_rec.depth; rm.u[r] = s_rec.u; rm.splits[r] = s_rec.splits;
     dst[r] = s_rec.dst;
   }
 }
 
-void launch_embed(ts_model* m, const RowMeta& rm, int R, int n_seqs) {
+void launch_embed(ts_model* m, const RowMeta& rm, int R, int n_seqs, int n_units) {
   ProfScope ps(m, "embed_rope_table");
   const ts_model_config& c = m->cfg;
   if (c.dtype == TS_DTYPE_BF16)
     hipLaunchKernelGGL(k_embed_rope<bf16_t>, dim3(R), dim3(256), 0, m->stream, m->rec_host, m->seq_host, n_seqs, rm, m->row_dst, m->seq_dev,
-                       (const bf16_t*)m->embed, m->H, c.d_model, m->rope_cs, c.head_dim / 2, (double)c.rope_theta);
+                       m->unit_host, m->unit_dev, n_units, (const bf16_t*)m->embed, m->H, c.d_model, m->rope_cs, c.head_dim / 2, (double)c.rope_theta);
   else
     hipLaunchKernelGGL(k_embed_rope<float>, dim3(R), dim3(256), 0, m->stream, m->rec_host, m->seq_host, n_seqs, rm, m->row_dst, m->seq_dev,
-                       (const float*)m->embed, m->H, c.d_model, m->rope_cs, c.head_dim / 2, (double)c.rope_theta);
+                       m->unit_host, m->unit_dev, n_units, (const float*)m->embed, m->H, c.d_model, m->rope_cs, c.head_dim / 2, (double)c.rope_theta);
 }
 
 // ---------------------------------------------------------------------------------

@@ -110,6 +110,33 @@ def test_merge_of_a_batch(n_seqs, P):
     B.ts_model_free(model)
 
 
+@pytest.mark.parametrize("contexts,n_nodes,hq", [
+    ((2600, 150), 20, 8),                          # two sequences, few KV heads: more than 16 splits, and three
+    ((0, 63, 64, 1900, 700), 64, 16),              # one block, exactly one and two, and the longest 31: ragged splits, many slots
+    (tuple(40 + 9 * i for i in range(130)), 2, 8)  # more sequences than one round of workgroups holds
+])
+def test_units_of_a_ragged_batch(contexts, n_nodes, hq):
+    """Key blocks dealt to workgroups in proportion to the lengths of a batch.  Against single passes."""
+    cfg, w, model, om = _load(n_layers=1, d_model=256, n_q_heads=hq, n_kv_heads=2, head_dim=128, d_ffn=256, vocab=97)
+    rng = np.random.default_rng(len(contexts))
+    trees, kvs = [wl.random_tree(n_nodes, cfg.vocab, rng) for _ in contexts], []
+    for i, P in enumerate(contexts):
+        kvs.append(B.ts_kv_alloc(model, P + n_nodes + 1))
+        if P:
+            K, V = wl.gen_context_kv(cfg, P, seed=900 + i)
+            B.ts_kv_import(kvs[i], K, V)
+        B.ts_set_pending(kvs[i], i % cfg.vocab)
+    rows = n_nodes + 1
+    B.ts_verify_batch(model, kvs, trees)
+    both = B.ts_get_logits(model, 0, rows * len(contexts), cfg.vocab).reshape(len(contexts), rows, cfg.vocab)
+    for i, kv in enumerate(kvs):
+        B.ts_verify(model, kv, *trees[i])
+        one = B.ts_get_logits(model, 0, rows, cfg.vocab)
+        assert max(U.rel_l2(a, b) for a, b in zip(both[i], one)) <= U.TOL_BF16_R, "sequence %d" % i
+        B.ts_kv_free(kv)
+    B.ts_model_free(model)
+
+
 @pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (8, 2)])
 def test_row_tiles_of_one_wave(hq, hkv):
     """One, two and three 16-row tiles in a wave (more rows take two waves) with one, two and four query heads per
