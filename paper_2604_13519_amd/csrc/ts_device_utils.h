@@ -10,6 +10,7 @@ typedef uint16_t f16_t;    // IEEE half bit pattern in memory
 // would be accessed with FLAT instructions, whose completion is tied to the LDS counter; casting
 // them to the global address space keeps vector memory and LDS waits independent.
 #define TS_GLOBAL __attribute__((address_space(1)))
+#define TS_LDS __attribute__((address_space(3)))
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t u) { return __uint_as_float((uint32_t)u << 16); }
 

@@ -5,7 +5,7 @@
 // every weight fragment is multiplied with R / 16 activation fragments.  The kernel keeps the
 // arithmetic (IEEE half x half -> fp32) and the data path of the skinny kernel - weights
 // pre-tiled in MFMA operand order and loaded straight from global memory into registers,
-// activations shared through a double-buffered LDS chunk - and changes the tile a wave owns:
+// activations shared through LDS chunks - and changes the tile a wave owns:
 //  * 4 tiles of 16 output features per wave (the skinny kernel has 2).  One 1 KiB activation
 //    fragment read from LDS then feeds 4 MFMAs, 64 matrix-pipe cycles against 8 LDS-pipe
 //    cycles; with 8 waves the LDS pipe is half as busy as the four matrix pipes.
@@ -13,14 +13,23 @@
 //    row blocks; the row blocks of one weight slab get consecutive places on the same XCD, so that
 //    the slab comes from HBM once and from that XCD's L2 for the other blocks.
 //  * 8 waves as CS column sets x KW k-waves (8x1: 512 columns, 4x2: 256, 2x4: 128) plus K
-//    splits across workgroups; the planner takes the combination with the fewest rounds of
-//    workgroups over the CUs.  The k-waves of a column set add their accumulators through LDS,
+//    splits across workgroups; the planner takes the combination with the least modelled time.
+//    The k-waves of a column set add their accumulators through LDS,
 //    one row tile at a time, in the order kq = 0, 1, ...; K splits write fp32 partial sums
 //    [split][row][col] for the next row-wise kernel (deterministic, no atomics).
+//  * Activations go from memory into the LDS directly (no registers on the way), two to four chunks
+//    deep, requested together with the weights of the same chunk and waited for by count; the first
+//    LDS read of a chunk is issued before the barrier that ends the one before, and the requests go
+//    out between the first products of a chunk, so that the matrix pipes do not stand still at a chunk's
+//    edge.  Through registers (one chunk ahead with k-waves, two without) against this, us:
+//    132 rows gate/up 108 -> 78, down 57 -> 44; 2048 rows gate/up 765 -> 710 (1.27 -> 1.36 PFLOP/s, both planes
+//    counted), down 345 -> 327, QKV 173 -> 159; 528 rows gate/up 224 -> 193.  What is left is power: register operands
+//    alone sustain 1.55 - 1.75 PFLOP/s here.
 //  * gate/up variant (SWIGLU): gate and up tiles alternate, a wave holds two (gate, up) pairs
 //    and the epilogue stores SiLU(gate) * up as half.
-//  * lm_head variant (ARGMAX, 8x1 only, no K split): the epilogue reduces each row's maximum over
-//    the workgroup's 512 columns and emits one (value, index) partial per row and column group.
+//  * lm_head variant (ARGMAX, no K split): the epilogue reduces each row's maximum over the workgroup's
+//    columns and emits one (value, index) partial per row and column group.  A small head takes the shapes of
+//    256 or 128 columns like any other projection (8192 columns, 528 rows 119 -> 70 us, 260 rows x 5120 146 -> 59 us).
 #include "ts_internal.h"
 #include "ts_device_utils.h"
 #include <algorithm>
@@ -59,31 +68,46 @@ enum { MODE_PARTIAL = 0, MODE_ARGMAX = 1, MODE_SWIGLU = 2 };
 constexpr int NT = 4;        // tiles of 16 output features per wave
 constexpr int WAVES = 8;
 
+// Ring slots: the activations of a chunk take MT * KW * 2 KiB of LDS each, its weights 16 registers.  The 4-row-tile
+// kernels with one or two k-waves run two workgroups per CU and have half the registers and LDS.
+constexpr int ring_depth(int MT, int KW) { return KW <= 2 ? (MT <= 4 ? 3 : 4) : MT <= 4 ? 4 : MT <= 6 ? 3 : 2; }
+
+// Waits until at most N of the wave's vector-memory loads are in flight (and its LDS accesses are done), then for the
+// other waves of the workgroup.
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  static_assert(N < 64, "the counter has six bits");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt((N & 15) | 7 << 4 | (N >> 4) << 14);      // vmcnt(N) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 template <int MT, int CS, int KW, int MODE>
-__global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
+__global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm_rows_bf16(RowsArgs a) {
   static_assert(CS * KW == WAVES, "8 waves");
-  static_assert(MODE != MODE_ARGMAX || KW == 1, "the arg-max epilogue expects one wave per column set");
   constexpr int KC = KW * 32;             // k elements per staged chunk: one k-step per wave
-  constexpr int KSTEPS = KC / 32;
-  constexpr int KSW = KSTEPS / KW;          // k-steps of a chunk this wave multiplies
-  static_assert(KSW >= 1 && KSW * KW == KSTEPS, "k-steps of a chunk divide among the k-waves");
-  // LDS rows without bank conflicts: a 16-byte read is served in groups of 16 lanes that hold rows 0-3 and 12-15 of
-  // one lane group and rows 4-11 of the next.  64-byte rows stand without padding, the second half of every 8 rows
-  // with its four vectors reversed; longer rows are 32 bytes apart.  (Rows 16 bytes apart: half of the LDS cycles were
-  // conflicts; 2048 rows gate/up 724 -> 719 us, down 338 -> 334 us.)
-  constexpr int XS = KC == 32 ? 32 : KC + 16;
-  auto xcol = [](int row, int k) { return KC == 32 ? k ^ ((row >> 2 & 1) * 24) : k; };
-  constexpr int NTHR = 64 * WAVES;
-  constexpr int PL = TS_ACT_PLANES;         // an activation is the sum of a hi and a lo half
-  constexpr int XVP = MT * 16 * KC / 8;     // 16-byte vectors per plane of a chunk
-  constexpr int XV = PL * XVP;
-  constexpr int XPT = (XV + NTHR - 1) / NTHR;
-  constexpr size_t XS_BYTES = sizeof(f16_t) * 2 * PL * MT * 16 * XS;
-  constexpr size_t RED_BYTES = KW > 1 ? sizeof(float) * WAVES * 4 * NT * 64 : 0;   // the reduction reuses the activation buffers
-  constexpr size_t AMAX_BYTES = MODE == MODE_ARGMAX ? (size_t)8 * WAVES * MT * 16 : 0;
-  constexpr size_t SMEM_BYTES = XS_BYTES > RED_BYTES ? (XS_BYTES > AMAX_BYTES ? XS_BYTES : AMAX_BYTES) : (RED_BYTES > AMAX_BYTES ? RED_BYTES : AMAX_BYTES);
-  __shared__ __attribute__((aligned(16))) char smem[SMEM_BYTES];
-  f16_t (*xs)[PL][MT * 16][XS] = reinterpret_cast<f16_t (*)[PL][MT * 16][XS]>(smem);
+  constexpr int PL = TS_ACT_PLANES;       // an activation is the sum of a hi and a lo half
+  constexpr int UPR = KC / 8;             // 16-byte vectors per row of a chunk
+  constexpr int PPP = MT * 16 * UPR / 64; // 1 KiB pieces per plane of a chunk: one direct-to-LDS load of a wave each
+  constexpr int XN = (PL * PPP + WAVES - 1) / WAVES;      // pieces a wave stages; the surplus repeats its last one
+  constexpr size_t XBYTES = (size_t)PL * PPP * 1024;
+  constexpr int RD = ring_depth(MT, KW);
+  constexpr bool AHEAD = RD >= 4;
+  constexpr int FD = 1, RQ = 2;           // fragments read ahead; the fragment behind whose products the requests go out
+  static_assert(RD * XBYTES <= 160 * 1024, "the activation chunks fit the LDS");
+  // One array per ring slot: the compiler then knows which loads a read of LDS has to wait for (all of them, if the
+  // slots were parts of one array).  The first two later serve the k-wave reduction and the arg-max.
+  __shared__ __attribute__((aligned(1024))) char xs0[XBYTES], xs1[XBYTES], xs2[RD > 2 ? XBYTES : 16], xs3[RD > 3 ? XBYTES : 16];
+  auto slot = [&](auto i_c) -> char* {
+    constexpr int I = decltype(i_c)::value;
+    if constexpr (I == 0) return xs0;
+    else if constexpr (I == 1) return xs1;
+    else if constexpr (I == 2) return xs2;
+    else return xs3;
+  };
 
   // place: XCD = blockIdx.x % 8; each takes an equal, contiguous run of the (weight slab, row block)
   // pairs, so that the row blocks of a slab follow each other on one XCD (two at a run's ends).  Whole
@@ -110,23 +134,26 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
   for (int t = 0; t < NT; ++t) {
     nt_idx[t] = (group * CS + cs_u) * NT + t;
     const int c = nt_idx[t] < a.n_tiles ? nt_idx[t] : a.n_tiles - 1;   // idle waves re-read a valid tile
-    wbase[t] = reinterpret_cast<const char*>(a.Wt) + ((size_t)c * a.kt_count + kbase0 / 32 + kq_u * KSW) * 1024;
+    wbase[t] = reinterpret_cast<const char*>(a.Wt) + ((size_t)c * a.kt_count + kbase0 / 32 + kq_u) * 1024;
   }
   const uint32_t w_lane = lane * 16;
-  // plane and row block are in the base (a wave's 64 vectors lie in one plane): both can be past 4 GiB in the
-  // workspace of a very large batch; the lane offset covers the 64 to 128 rows of a block
-  static_assert(XVP % 64 == 0, "a wave stages from one plane");
-  constexpr int XPP = XVP % NTHR == 0 ? XVP / NTHR : 0;     // staging rounds per plane; 0: a round holds vectors of both
+  // Staging: lane l of a piece brings the vector that belongs at l x 16 bytes of it.  A row's vectors stand permuted
+  // (swz), so that the 16-byte reads below meet no bank twice: each is served in groups of 16 lanes that hold rows 0-3
+  // and 12-15 of one lane group and rows 4-11 of the next.
+  auto swz = [](int row) { return KC == 128 ? row & 15 : KC == 64 ? row >> 1 & 7 : (row >> 2 & 1) * 3; };
+  // plane and row block are in the base: both can be past 4 GiB in the workspace of a very large batch; the lane
+  // offset covers the 64 to 128 rows of a block
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const char* xbase = reinterpret_cast<const char*>(a.X) + ((size_t)row0 * act_ld(a.K) + kbase0) * 2;
   const size_t plane_bytes = a.x_plane * 2;
-  bool x_lo[XPT];                           // which plane (uniform in a wave)
-  uint32_t x_off[XPT];                      // byte offset of each staged vector within its plane and chunk
+  int piece[XN];
+  uint32_t x_off[XN];
 #pragma unroll
-  for (int p = 0; p < XPT; ++p) {
-    const int v = XPP ? tid + (p < XPP ? p : p - XPP) * NTHR : min(tid + p * NTHR, XV - 1);
-    const int row = min((v % XVP) / (KC / 8), a.x_rows - 1 - row0), cv = v % (KC / 8);
-    x_lo[p] = XPP ? p >= XPP : __builtin_amdgcn_readfirstlane(v / XVP) != 0;
-    x_off[p] = ((uint32_t)row * (uint32_t)act_ld(a.K) + cv * 8) * 2;
+  for (int p = 0; p < XN; ++p) {
+    piece[p] = p * WAVES + wave_u;
+    if (piece[p] >= PL * PPP) piece[p] -= WAVES;
+    const int rl = piece[p] % PPP * (64 / UPR) + lane / UPR;
+    x_off[p] = ((uint32_t)min(rl, a.x_rows - 1 - row0) * (uint32_t)act_ld(a.K) + ((lane % UPR) ^ swz(rl)) * 8) * 2;
   }
 
   f32x4 acc[MT][NT];
@@ -135,141 +162,113 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Pipeline depth.  With one workgroup per CU (2 waves per SIMD) the loads need more than one
-  // chunk of matrix-core time to arrive: weights travel RD - 1 chunks ahead in a register ring,
-  // activations XD chunks ahead in registers and one chunk ahead in LDS.  The 4-row-tile kernels
-  // that run two workgroups per CU keep the short pipeline (their register budget is half).
-  constexpr int RD = (MT <= 4 && KW <= 2) ? 2 : 4;
-  constexpr int XD = (RD == 4 && KW == 1) ? 2 : 1;
-  f16x8 w[RD][NT][KSW];
-  u32x4 xr[XD][XPT];
-  const int last_chunk = n_chunks - 1;
-
-  // loads are never predicated (a load under an `if` would make every later wait a wait for
-  // everything): past the end they re-request the last chunk.
+  // Pipeline.  Group c = activations and weights of chunk c, requested RD - 1 steps ahead.  A step waits until its
+  // group - with four slots the next one too, so that its first fragment can be read early - has arrived, meets the
+  // other waves (all have their pieces in LDS, and none still reads the slot of the chunk before), and between its
+  // products requests group c + RD - 1 into that slot.  Loads are never predicated (the counts rely on it): past the
+  // end they re-request the last chunk.
+  // Measured: fragments 1, 2, 3 ahead 528 rows gate/up 193, 208, 208 us; requests after the third fragment against
+  // right after the barrier 330 rows gate/up 132 : 134 us; the next group waited for with three slots too: 193 -> 285 us.
   // The empty asm statements keep the lane offsets 32 bits wide up to the load, which then adds them to the
   // uniform base itself; left alone the compiler hoists 64-bit lane addresses, a register pair per load, out of
-  // the loop, and with the planes in the base the largest tiles spill around them.  8 tiles x 4 k-waves: 37 -> 1
-  // registers spilled, 2000 rows x 2048 columns x K 2048 78 -> 47 us; the 8B shape at 264 rows: gate/up 133 -> 127 us,
-  // down 68.5 -> 64.0 us, QKV of 130 rows 29.8 -> 26.1 us.
-  auto load_w = [&](f16x8 (&dst)[NT][KSW], int chunk) {
-    const size_t off = (size_t)min(chunk, last_chunk) * (KSTEPS * 1024);
+  // the loop, and the largest tiles spill around them.
+  f16x8 w[RD][NT];
+  const int last_chunk = n_chunks - 1;
+  auto request = [&](auto i_c, int chunk) {
+    constexpr int I = decltype(i_c)::value;
+    const int ch = min(chunk, last_chunk);
+    const char* xc = xbase + (size_t)ch * (KC * 2);
+#pragma unroll
+    for (int p = 0; p < XN; ++p) {
+      uint32_t o = x_off[p];
+      asm("" : "+v"(o));
+      __builtin_amdgcn_global_load_lds((const TS_GLOBAL void*)(xc + (piece[p] >= PPP ? plane_bytes : 0) + o),
+                                       (TS_LDS void*)(slot(i_c) + piece[p] * 1024), 16, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     uint32_t wl = w_lane;
     asm("" : "+v"(wl));
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int j = 0; j < KSW; ++j)
-        dst[t][j] = *reinterpret_cast<const f16x8*>(wbase[t] + off + wl + j * 1024);
+    for (int t = 0; t < NT; ++t) w[I][t] = *reinterpret_cast<const f16x8*>(wbase[t] + (size_t)ch * (KW * 1024) + wl);
+    __builtin_amdgcn_sched_barrier(0);
   };
-  auto load_x = [&](u32x4 (&dst)[XPT], int chunk) {
-    const char* hi = xbase + (size_t)min(chunk, last_chunk) * (KC * 2);
-    const char* lo = hi + plane_bytes;
-#pragma unroll
-    for (int p = 0; p < XPT; ++p) {
-      uint32_t o = x_off[p];
-      asm("" : "+v"(o));
-      dst[p] = *reinterpret_cast<const u32x4*>((x_lo[p] ? lo : hi) + o);
-    }
+  const uint32_t x_read = l15 * (KC * 2) + ((kq * 4 + g) ^ swz(l15)) * 16;
+  auto frag = [&](auto i_c, int f) {        // fragment f of a slot: row tile f / PL, plane f % PL
+    return *reinterpret_cast<const f16x8*>(slot(i_c) + f % PL * (PPP * 1024) + f / PL * (16 * KC * 2) + x_read);
   };
-  auto store_x = [&](const u32x4 (&src)[XPT], int buf) {
-#pragma unroll
-    for (int p = 0; p < XPT; ++p) {
-      const int v = tid + p * NTHR;
-      if (XV % NTHR == 0 || v < XV)
-        *reinterpret_cast<u32x4*>(&xs[buf][v / XVP][(v % XVP) / (KC / 8)][xcol((v % XVP) / (KC / 8), (v % (KC / 8)) * 8)]) = src[p];
-    }
-  };
-  auto mma_chunk = [&](const f16x8 (&wc)[NT][KSW], int buf) {
-#pragma unroll
-    for (int ks = 0; ks < KSW; ++ks) {
-      const int kk = xcol(l15, (kq * KSW + ks) * 32 + g * 8);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-        for (int pl = 0; pl < PL; ++pl) {
-          const f16x8 xa = *reinterpret_cast<const f16x8*>(&xs[buf][pl][mt * 16 + l15][kk]);
-#pragma unroll
-          for (int t = 0; t < NT; ++t) acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa, wc[t][ks], acc[mt][t], 0, 0, 0);
-        }
-      }
-    }
-  };
-  // Step c (I = c % RD at compile time).  On entry: weights of chunks c .. c+RD-2 requested,
-  // activations of chunk c in LDS buffer c % 2, of chunks c+1 .. c+XD-1 requested into registers.
+  f16x8 xa[FD + 1];
   auto step = [&](auto i_c, int c) {
     constexpr int I = decltype(i_c)::value;
-    load_x(xr[I % XD], c + XD);
-    load_w(w[(I + RD - 1) % RD], c + RD - 1);
-    mma_chunk(w[I], I & 1);
-    store_x(xr[(I + 1) % XD], (I + 1) & 1);
-    __syncthreads();
+    constexpr int NF = MT * PL;
+    wait_loads<(RD - 2 - AHEAD) * (XN + NT)>();
+    if constexpr (!AHEAD) {
+#pragma unroll
+      for (int f = 0; f < FD; ++f) xa[f] = frag(i_c, f);
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      if (f + FD < NF) xa[(f + FD) % (FD + 1)] = frag(i_c, f + FD);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[f / PL][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f % (FD + 1)], w[I][t], acc[f / PL][t], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (f == RQ) request(std::integral_constant<int, (I + RD - 1) % RD>{}, c + RD - 1);
+    }
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int f = 0; f < FD; ++f) xa[f] = frag(std::integral_constant<int, (I + 1) % RD>{}, f);
+    }
   };
-
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2 % RD>;
+  using I3 = std::integral_constant<int, 3 % RD>;
+  request(I0{}, 0);
+  if constexpr (RD > 2) request(I1{}, 1);
+  if constexpr (RD > 3) request(I2{}, 2);
+  if constexpr (AHEAD) {
+    wait_loads<(RD - 2) * (XN + NT)>();
 #pragma unroll
-  for (int i = 0; i < XD; ++i) load_x(xr[i], i);
-#pragma unroll
-  for (int i = 0; i < RD - 1; ++i) load_w(w[i], i);
-  store_x(xr[0], 0);
-  __syncthreads();
+    for (int f = 0; f < FD; ++f) xa[f] = frag(I0{}, f);
+  }
   int c0 = 0;
   for (; c0 + RD <= n_chunks; c0 += RD) {
-    step(std::integral_constant<int, 0>{}, c0);
-    step(std::integral_constant<int, 1>{}, c0 + 1);
-    if (RD == 4) {
-      step(std::integral_constant<int, 2 % RD>{}, c0 + 2);
-      step(std::integral_constant<int, 3 % RD>{}, c0 + 3);
-    }
+    step(I0{}, c0);
+    step(I1{}, c0 + 1);
+    if constexpr (RD > 2) step(I2{}, c0 + 2);
+    if constexpr (RD > 3) step(I3{}, c0 + 3);
   }
-  if (c0 < n_chunks) step(std::integral_constant<int, 0>{}, c0);
-  if (RD == 4) {
-    if (c0 + 1 < n_chunks) step(std::integral_constant<int, 1>{}, c0 + 1);
-    if (c0 + 2 < n_chunks) step(std::integral_constant<int, 2 % RD>{}, c0 + 2);
-  }
+  if (c0 < n_chunks) step(I0{}, c0);
+  if constexpr (RD > 2) if (c0 + 1 < n_chunks) step(I1{}, c0 + 1);
+  if constexpr (RD > 3) if (c0 + 2 < n_chunks) step(I2{}, c0 + 2);
+  // nothing may still be on its way into the LDS when it is used otherwise or given back
+  wait_loads<0>();
 
-  if (MODE == MODE_ARGMAX) {
-    // per row: maximum over the wave's 64 columns (in-lane over the 4 tiles, then over the 16
-    // lanes of the row), then over the 8 waves through LDS (free after the loop's last barrier)
-    float* rv = reinterpret_cast<float*>(smem);                    // [WAVES][MT * 16]
-    int* ri = reinterpret_cast<int*>(smem) + WAVES * MT * 16;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = row0 + mt * 16 + g * 4 + r;
-        float bv = -INFINITY;
-        int bi = 0x7fffffff;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const int col = nt_idx[t] * 16 + l15;
-          if (nt_idx[t] < a.n_tiles && col < a.N) {
-            const float v = acc[mt][t][r];
-            if (a.logits != nullptr && row < a.R) a.logits[(size_t)row * a.N + col] = v;
-            amax_take(bv, bi, v, col);
-          }
-        }
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
-          const float ov = __shfl_xor(bv, o, 64);
-          const int oi = __shfl_xor(bi, o, 64);
-          amax_take(bv, bi, ov, oi);
-        }
-        if (l15 == 0) { rv[wave * (MT * 16) + mt * 16 + g * 4 + r] = bv; ri[wave * (MT * 16) + mt * 16 + g * 4 + r] = bi; }
-      }
-    __syncthreads();
-    if (tid < MT * 16 && row0 + tid < a.R) {
-      float bv = rv[tid];
-      int bi = ri[tid];
-      for (int wv = 1; wv < WAVES; ++wv) amax_take(bv, bi, rv[wv * (MT * 16) + tid], ri[wv * (MT * 16) + tid]);
-      a.aval[(size_t)(row0 + tid) * a.amax_stride + group] = bv;
-      a.aidx[(size_t)(row0 + tid) * a.amax_stride + group] = bi;
-    }
-    return;
-  }
-
+  // ARGMAX: best (value, column) of every row over the 64 columns of each column set
+  __shared__ float rv[MODE == MODE_ARGMAX ? CS : 1][MODE == MODE_ARGMAX ? MT * 16 : 1];
+  __shared__ int ri[MODE == MODE_ARGMAX ? CS : 1][MODE == MODE_ARGMAX ? MT * 16 : 1];
   // value of output (row tile mt, row r of the lane group, tile t) goes to memory
   auto emit = [&](int mt, int r, const float (&v)[NT]) {
     const int row = row0 + mt * 16 + g * 4 + r;
+    if (MODE == MODE_ARGMAX) {                // in-lane over the 4 tiles, then over the 16 lanes of the row
+      float bv = -INFINITY;
+      int bi = 0x7fffffff;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int col = nt_idx[t] * 16 + l15;
+        if (nt_idx[t] < a.n_tiles && col < a.N) {
+          if (a.logits != nullptr && row < a.R) a.logits[(size_t)row * a.N + col] = v[t];
+          amax_take(bv, bi, v[t], col);
+        }
+      }
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) {
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        amax_take(bv, bi, ov, oi);
+      }
+      if (l15 == 0) { rv[cs][row - row0] = bv; ri[cs][row - row0] = bi; }
+      return;
+    }
     if (row >= a.R) return;
     if (MODE == MODE_SWIGLU) {
 #pragma unroll
@@ -300,16 +299,17 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
         emit(mt, r, v);
       }
   } else {
-    // one row tile at a time through LDS (the activation buffers are free after the loop's last
-    // barrier): every wave stores its 16 values per lane, then k-wave kq finishes the rows
+    // one row tile at a time through LDS (the activation slots are free now; the first four waves use one, the others
+    // the next, and a column set's k-waves are all in one half): every wave stores its 16 values per lane, then k-wave kq finishes the rows
     // r = kq, kq + KW, .. of the tile, adding in the order kq = 0, 1, ...
-    float* red = reinterpret_cast<float*>(smem);
+    static_assert(KW == 1 || XBYTES >= sizeof(float) * 16 * NT * 64, "the sums of four waves fit a slot");
+    float* red = reinterpret_cast<float*>(wave < 4 ? xs0 : xs1);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) red[((wave * 4 + r) * NT + t) * 64 + lane] = acc[mt][t][r];
+        for (int t = 0; t < NT; ++t) red[(((wave & 3) * 4 + r) * NT + t) * 64 + lane] = acc[mt][t][r];
       __syncthreads();
       for (int r = kq; r < 4; r += KW) {
         float v[NT];
@@ -317,12 +317,21 @@ __global__ __launch_bounds__(64 * WAVES) void k_gemm_rows_bf16(RowsArgs a) {
         for (int t = 0; t < NT; ++t) {
           float sum = 0.f;
 #pragma unroll
-          for (int k = 0; k < KW; ++k) sum += red[(((cs * KW + k) * 4 + r) * NT + t) * 64 + lane];
+          for (int k = 0; k < KW; ++k) sum += red[((((cs * KW + k) & 3) * 4 + r) * NT + t) * 64 + lane];
           v[t] = sum;
         }
         emit(mt, r, v);
       }
       __syncthreads();
+    }
+  }  if (MODE == MODE_ARGMAX) {
+    __syncthreads();
+    if (tid < MT * 16 && row0 + tid < a.R) {
+      float bv = rv[0][tid];
+      int bi = ri[0][tid];
+      for (int c = 1; c < CS; ++c) amax_take(bv, bi, rv[c][tid], ri[c][tid]);
+      a.aval[(size_t)(row0 + tid) * a.amax_stride + group] = bv;
+      a.aidx[(size_t)(row0 + tid) * a.amax_stride + group] = bi;
     }
   }
 }
@@ -337,14 +346,10 @@ const int kCfgKC[kNumCfg] = {32, 64, 128};
 template <int MT, int MODE>
 void launch_cfg(int cfg, dim3 grid, hipStream_t s, const RowsArgs& a) {
   const dim3 block(64 * WAVES);
-  if (MODE == MODE_ARGMAX) {                      // 8x1 only
-    hipLaunchKernelGGL((k_gemm_rows_bf16<MT, 8, 1, MODE>), grid, block, 0, s, a);
-    return;
-  }
   switch (cfg) {
     case 0: hipLaunchKernelGGL((k_gemm_rows_bf16<MT, 8, 1, MODE>), grid, block, 0, s, a); break;
-    case 1: hipLaunchKernelGGL((k_gemm_rows_bf16<MT, 4, 2, MODE == MODE_ARGMAX ? MODE_PARTIAL : MODE>), grid, block, 0, s, a); break;
-    default: hipLaunchKernelGGL((k_gemm_rows_bf16<MT, 2, 4, MODE == MODE_ARGMAX ? MODE_PARTIAL : MODE>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((k_gemm_rows_bf16<MT, 4, 2, MODE>), grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL((k_gemm_rows_bf16<MT, 2, 4, MODE>), grid, block, 0, s, a); break;
   }
 }
 
@@ -363,39 +368,41 @@ void launch_mt(int mt, int cfg, dim3 grid, hipStream_t s, const RowsArgs& a) {
 
 int gemm_rows_chunk(int cfg) { return kCfgKC[cfg]; }
 
-// Row tiles per workgroup (4..8: the rows are cut into equal blocks), configuration and K
-// splits with the least modelled time: rounds of workgroups over the CUs x (matrix-core time of
-// a workgroup + a fixed start/finish cost) + traffic of the partial sums.  max_part_elems
-// bounds splits x R x N.  K is a multiple of 128 (check_config), so every chunk length fits.
+// Row tiles per workgroup (4..8: the rows are cut into equal blocks), configuration and K splits with the least
+// modelled time.  max_part_elems bounds splits x R x N.  K is a multiple of 128 (check_config), so every chunk length fits.
+//   workgroup = k-steps of a wave x (kStepTile x row tiles + kStep) + kFix + kFixTile x row tiles   (start, finish, joining k-waves)
+//   launch    = rounds over the CUs x workgroup, 8 % less where half the CUs stay empty (clock), + 0.6 us per million partial sums
+// where the 4-row-tile kernels with one or two k-waves need half the registers and LDS of a CU: two workgroups share
+// one and take 1.75 times as long as one.  The constants (ns, us) are fitted to a sweep of every (row tiles, configuration,
+// splits) of the 8B and 32B-class projections at 18 and 8 row counts of 96 to 2048, each with the change of the
+// kernels that read the sums: the chosen ones together take 0.5 % more than the best ones, at most 7 %
+// (400 rows x 8192 columns of the head).  The model before, one efficiency per configuration: 3.9 %, at most 25 %.
 void gemm_rows_plan(const ts_model* m, int R, int N, int K, int mode, size_t max_part_elems, int* mt_out, int* cfg_out,
                     int* splits_out) {
+  static const double kStepTile[kNumCfg] = {0.125, 0.113, 0.160}, kStep[kNumCfg] = {0.200, 0.300, 0.400};
+  static const double kPairStep[kNumCfg] = {0.768, 0.820, 0.0};          // four row tiles, two workgroups a CU
+  static const double kFix[kNumCfg] = {11.0, 2.0, 4.0}, kFixTile[kNumCfg] = {0.0, 1.6, 0.7};
   const int tiles = (R + 15) / 16;
   double best = 1e300;
   for (int mt = kMinMT; mt <= kMaxMT; ++mt) {
     const int n_rblocks = (tiles + mt - 1) / mt;
     if (mt > kMinMT && n_rblocks == (tiles + mt - 2) / (mt - 1)) continue;   // same blocks, more idle rows
     for (int cfg = 0; cfg < kNumCfg; ++cfg) {
-      if (mode == MODE_ARGMAX && cfg != 0) break;
       const int chunks = K / kCfgKC[cfg];
       const int cols = kCfgCS[cfg] * NT * 16;
       const int groups = (N + cols - 1) / cols;
+      if (mode == MODE_ARGMAX && groups > m->amax_parts) continue;       // room for the partial maxima of a row
       for (int s = 1; s <= chunks && s <= 8; ++s) {
         if (chunks % s) continue;
         if (mode != MODE_PARTIAL && s > 1) break;
         if (s > 1 && (size_t)s * R * N > max_part_elems) break;
-        const long wgs = (long)groups * s * n_rblocks;
-        // the 4-row-tile kernels with one or two k-waves need half the registers and LDS of a CU:
-        // two workgroups share one
-        const int wg_per_cu = (cfg <= 1 && mt <= 4) ? 2 : 1;
-        const long rounds = (wgs + (long)m->n_cu * wg_per_cu - 1) / ((long)m->n_cu * wg_per_cu);
-        // MFMAs a SIMD issues for one workgroup (2 waves per SIMD), 16 cycles each at 2.4 GHz;
-        // measured issue efficiency (one activation plane's worth): about 0.36 with four waves per
-        // SIMD and the short pipeline, 0.40 with two waves and the deep one, a tenth less with k-waves
-        // (their deeper activation registers leave no room for two chunks ahead)
-        const double eff = wg_per_cu == 2 ? 0.36 : (cfg == 0 ? 0.40 : 0.36 * (cfg == 2 ? 0.9 : 1.0));
-        const double mfma_us = 2.0 * (K / s / 32 / kCfgKW[cfg]) * mt * NT * 16 / 2400.0;
-        double cost = rounds * (wg_per_cu * mfma_us / eff + 6.0);
-        if (s > 1) cost += s * R * (double)N * 4.0 / 12.0e6;        // partial sums, mostly overlapped with the products
+        const long wgs = (long)groups * s * n_rblocks, rounds = (wgs + m->n_cu - 1) / m->n_cu;
+        const bool pairs = mt <= 4 && cfg <= 1;
+        const double steps = (double)(K / s / kCfgKC[cfg]);
+        const double wg = steps * (pairs ? kPairStep[cfg] : kStepTile[cfg] * mt + kStep[cfg]) + kFix[cfg] + kFixTile[cfg] * mt;
+        double cost = wg * (pairs ? rounds / 2 * 1.75 + rounds % 2 : rounds);
+        cost *= 1.0 - 0.08 * (1.0 - (double)wgs / (double)(rounds * m->n_cu));
+        if (s > 1) cost += 0.6e-6 * s * R * (double)N;
         if (cost < best) { best = cost; *mt_out = mt; *cfg_out = cfg; *splits_out = s; }
       }
     }

@@ -110,6 +110,36 @@ def test_merge_of_a_batch(n_seqs, P):
     B.ts_model_free(model)
 
 
+@pytest.mark.parametrize("d_model,hq,d_ffn,vocab,n_seqs,n_nodes", [
+    (128, 1, 128, 97, 2, 40),        # 82 rows; one to four chunks of K: fewer than the ring holds
+    (384, 3, 640, 1500, 3, 32),      # 99 rows; chunk counts that are no multiple of the ring's
+    (256, 2, 1152, 5000, 2, 64),     # 130 rows, nine row tiles
+    (640, 5, 384, 8209, 4, 64),      # 260 rows, ragged head
+    (512, 4, 1536, 700, 7, 64),      # 455 rows
+])
+def test_many_rows_rings_and_small_heads(d_model, hq, d_ffn, vocab, n_seqs, n_nodes):
+    """Passes of more than 80 rows over short and odd K ranges, and heads of few column groups (arg-max joined over
+    k-waves).  Logits against single passes; the fused arg-max against the stored logits, lowest token on ties."""
+    cfg, w, model, om = _load(n_layers=1, d_model=d_model, n_q_heads=hq, n_kv_heads=hq, head_dim=128, d_ffn=d_ffn, vocab=vocab)
+    rng = np.random.default_rng(d_model)
+    trees, kvs = [wl.random_tree(n_nodes, cfg.vocab, rng) for _ in range(n_seqs)], []
+    for i in range(n_seqs):
+        K, V = wl.gen_context_kv(cfg, 30 + i, seed=800 + i)
+        kvs.append(B.ts_kv_alloc(model, 31 + i + n_nodes))
+        B.ts_kv_import(kvs[i], K, V)
+        B.ts_set_pending(kvs[i], i)
+    rows = n_nodes + 1
+    B.ts_verify_batch(model, kvs, trees)
+    both = B.ts_get_logits(model, 0, rows * n_seqs, cfg.vocab)
+    assert np.array_equal(B.ts_get_row_tokens(model, 0, rows * n_seqs), both.argmax(1))
+    for i, kv in enumerate(kvs):
+        B.ts_verify(model, kv, *trees[i])
+        one = B.ts_get_logits(model, 0, rows, cfg.vocab)
+        assert max(U.rel_l2(a, b) for a, b in zip(both[i * rows:(i + 1) * rows], one)) <= U.TOL_BF16_R, "sequence %d" % i
+        B.ts_kv_free(kv)
+    B.ts_model_free(model)
+
+
 @pytest.mark.parametrize("contexts,n_nodes,hq", [
     ((2600, 150), 20, 8),                          # two sequences, few KV heads: more than 16 splits, and three
     ((0, 63, 64, 1900, 700), 64, 16),              # one block, exactly one and two, and the longest 31: ragged splits, many slots
