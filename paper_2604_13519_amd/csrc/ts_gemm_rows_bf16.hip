@@ -165,8 +165,8 @@ __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm
   // Pipeline.  Group c = activations and weights of chunk c, requested RD - 1 steps ahead.  A step waits until its
   // group - with four slots the next one too, so that its first fragment can be read early - has arrived, meets the
   // other waves (all have their pieces in LDS, and none still reads the slot of the chunk before), and between its
-  // products requests group c + RD - 1 into that slot.  Loads are never predicated (the counts rely on it): past the
-  // end they re-request the last chunk.
+  // products requests group c + RD - 1 into that slot.  Loads in the loop are never predicated (the counts rely on
+  // it): past the end they re-request the last chunk.
   // Measured: fragments 1, 2, 3 ahead 528 rows gate/up 193, 208, 208 us; requests after the third fragment against
   // right after the barrier 330 rows gate/up 132 : 134 us; the next group waited for with three slots too: 193 -> 285 us.
   // The empty asm statements keep the lane offsets 32 bits wide up to the load, which then adds them to the
@@ -197,10 +197,13 @@ __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm
     return *reinterpret_cast<const f16x8*>(slot(i_c) + f % PL * (PPP * 1024) + f / PL * (16 * KC * 2) + x_read);
   };
   f16x8 xa[FD + 1];
-  auto step = [&](auto i_c, int c) {
-    constexpr int I = decltype(i_c)::value;
-    constexpr int NF = MT * PL;
-    wait_loads<(RD - 2 - AHEAD) * (XN + NT)>();
+  // T < 0: a step of the loop.  T >= 0: step T of the rest, behind which no chunk is left to request: the groups in
+  // flight get fewer, and no request may be made for nothing (its weights, which nothing uses, would be left out by the
+  // compiler, and the counts would be wrong).
+  auto step = [&](auto i_c, auto t_c, int c) {
+    constexpr int I = decltype(i_c)::value, T = decltype(t_c)::value;
+    constexpr int NF = MT * PL, LEFT = RD - 2 - AHEAD - (T < 0 ? 0 : T);     // later groups that may stay in flight
+    wait_loads<(LEFT > 0 ? LEFT : 0) * (XN + NT)>();
     if constexpr (!AHEAD) {
 #pragma unroll
       for (int f = 0; f < FD; ++f) xa[f] = frag(i_c, f);
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[f / PL][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f % (FD + 1)], w[I][t], acc[f / PL][t], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
-      if (f == RQ) request(std::integral_constant<int, (I + RD - 1) % RD>{}, c + RD - 1);
+      if (T < 0 && f == RQ) request(std::integral_constant<int, (I + RD - 1) % RD>{}, c + RD - 1);
     }
     if constexpr (AHEAD) {
 #pragma unroll
@@ -222,6 +225,7 @@ __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2 % RD>;
   using I3 = std::integral_constant<int, 3 % RD>;
+  using Loop = std::integral_constant<int, -1>;
   request(I0{}, 0);
   if constexpr (RD > 2) request(I1{}, 1);
   if constexpr (RD > 3) request(I2{}, 2);
@@ -232,14 +236,14 @@ __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm
   }
   int c0 = 0;
   for (; c0 + RD <= n_chunks; c0 += RD) {
-    step(I0{}, c0);
-    step(I1{}, c0 + 1);
-    if constexpr (RD > 2) step(I2{}, c0 + 2);
-    if constexpr (RD > 3) step(I3{}, c0 + 3);
+    step(I0{}, Loop{}, c0);
+    step(I1{}, Loop{}, c0 + 1);
+    if constexpr (RD > 2) step(I2{}, Loop{}, c0 + 2);
+    if constexpr (RD > 3) step(I3{}, Loop{}, c0 + 3);
   }
-  if (c0 < n_chunks) step(I0{}, c0);
-  if constexpr (RD > 2) if (c0 + 1 < n_chunks) step(I1{}, c0 + 1);
-  if constexpr (RD > 3) if (c0 + 2 < n_chunks) step(I2{}, c0 + 2);
+  if (c0 < n_chunks) step(I0{}, I0{}, c0);
+  if constexpr (RD > 2) if (c0 + 1 < n_chunks) step(I1{}, I1{}, c0 + 1);
+  if constexpr (RD > 3) if (c0 + 2 < n_chunks) step(I2{}, I2{}, c0 + 2);
   // nothing may still be on its way into the LDS when it is used otherwise or given back
   wait_loads<0>();
 
