@@ -30,6 +30,7 @@
 #include "ts_internal.h"
 #include "ts_device_utils.h"
 #include <algorithm>
+#include <type_traits>
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -61,10 +62,104 @@ struct GemmArgs {
 
 enum { MODE_PARTIAL = 0, MODE_ARGMAX = 1, MODE_SWIGLU = 2 };
 
+// The finish of both kernels below: joins the k-waves, applies the mode's epilogue and stores.  acc[mt][t] holds rows
+// 4 (lane / 16) .. +4 of row tile mt and column lane % 16 of tile t; red: room for the sums of all waves, free to use.
+template <int MT, int NT, int CS, int KW, int MODE>
+__device__ __forceinline__ void finish(const GemmArgs& a, const f32x4 (&acc)[MT][NT], const int (&nt_idx)[NT], float* red, int group, int split) {
+  constexpr bool ARGMAX = MODE == MODE_ARGMAX;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, g = lane >> 4;
+  const int cs = wave / KW, kq = wave % KW;
+  // ARGMAX: best (value, column) of every row over the columns of each column set
+  __shared__ float rv[ARGMAX ? CS : 1][ARGMAX ? MT * 16 : 1];
+  __shared__ int ri[ARGMAX ? CS : 1][ARGMAX ? MT * 16 : 1];
+  // value of output (row tile mt, row r of the lane group, tile t) goes to memory
+  auto emit = [&](int mt, int r, const float (&v)[NT]) {
+    const int row = mt * 16 + g * 4 + r;
+    if (ARGMAX) {
+      float bv = -INFINITY;
+      int bi = 0x7fffffff;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int col = nt_idx[t] * 16 + l15;
+        if (nt_idx[t] < a.n_tiles && col < a.N) {
+          if (a.logits != nullptr && row < a.R) a.logits[(size_t)row * a.N + col] = v[t];
+          amax_take(bv, bi, v[t], col);
+        }
+      }
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) {       // reduce over the 16 lanes that hold this row
+        const float ov = __shfl_xor(bv, o, 64);
+        const int oi = __shfl_xor(bi, o, 64);
+        amax_take(bv, bi, ov, oi);
+      }
+      if (l15 == 0) { rv[cs][row] = bv; ri[cs][row] = bi; }
+      return;
+    }
+    if (row >= a.R) return;
+    if (MODE == MODE_SWIGLU) {
+      const int f = (nt_idx[0] >> 1) * 16 + l15;           // tiles 2j / 2j+1 = gate / up of features 16j..
+      if (nt_idx[NT - 1] < a.n_tiles) {
+        const float gv = v[0], uv = v[NT - 1];
+        st_act_planes(a.act_out + (size_t)row * act_ld(a.N / 2) + f, a.act_plane, gv / (1.0f + expf(-gv)) * uv, a.sat);
+      }
+    } else {
+      float* o = a.out + (size_t)split * a.split_stride;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int col = nt_idx[t] * 16 + l15;
+        if (nt_idx[t] < a.n_tiles && col < a.N) o[(size_t)row * a.N + col] = v[t];
+      }
+    }
+  };
+  if (KW == 1) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float v[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) v[t] = acc[mt][t][r];
+        emit(mt, r, v);
+      }
+  } else {
+    // add the KW accumulators of a column set through LDS, one row tile at a time, always in the order kq = 0, 1, ...
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) red[((wave * 4 + r) * NT + t) * 64 + lane] = acc[mt][t][r];
+      __syncthreads();
+      for (int r = kq; r < 4; r += KW) {                 // this wave finishes rows r of the tile
+        float v[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          float sum = 0.f;
+#pragma unroll
+          for (int k = 0; k < KW; ++k) sum += red[(((cs * KW + k) * 4 + r) * NT + t) * 64 + lane];
+          v[t] = sum;
+        }
+        emit(mt, r, v);
+      }
+      __syncthreads();
+    }
+  }
+  if (ARGMAX) {
+    __syncthreads();
+    if (tid < MT * 16 && tid < a.R) {
+      float bv = rv[0][tid];
+      int bi = ri[0][tid];
+      for (int c = 1; c < CS; ++c) amax_take(bv, bi, rv[c][tid], ri[c][tid]);
+      a.aval[(size_t)tid * a.amax_parts + group] = bv;
+      a.aidx[(size_t)tid * a.amax_parts + group] = bi;
+    }
+  }
+}
+
 template <int MT, int NT, int CS, int KW, int KC, int PF, int MODE, int XPAD = 16>
 __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   constexpr int WAVES = CS * KW;            // CS column sets x KW k-step owners
-  constexpr bool ARGMAX = MODE == MODE_ARGMAX;
   constexpr int KSTEPS = KC / 32;           // MFMA k-steps per chunk
   constexpr int KSW = KSTEPS / KW;          // ... of which this wave multiplies KSW
   static_assert(KSTEPS % KW == 0 && KSW >= 1, "k-steps of a chunk must divide among the k-waves");
@@ -219,101 +314,173 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   for (int b = 0; b < NBUF - 1; ++b)
     if (c0 + b < n_chunks) step(w[b], w[(b + PF) % NBUF], xr[(b + PF) % NBUF], xr[(b + 1) % NBUF], c0 + b);
 
-  // ARGMAX: best (value, column) of every row over the columns of each column set
-  __shared__ float rv[ARGMAX ? CS : 1][ARGMAX ? MT * 16 : 1];
-  __shared__ int ri[ARGMAX ? CS : 1][ARGMAX ? MT * 16 : 1];
-  // value of output (row tile mt, row r of the lane group, tile t) goes to memory
-  auto emit = [&](int mt, int r, const float (&v)[NT]) {
-    const int row = mt * 16 + g * 4 + r;
-    if (ARGMAX) {
-      float bv = -INFINITY;
-      int bi = 0x7fffffff;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int col = nt_idx[t] * 16 + l15;
-        if (nt_idx[t] < a.n_tiles && col < a.N) {
-          if (a.logits != nullptr && row < a.R) a.logits[(size_t)row * a.N + col] = v[t];
-          amax_take(bv, bi, v[t], col);
-        }
-      }
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) {       // reduce over the 16 lanes that hold this row
-        const float ov = __shfl_xor(bv, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        amax_take(bv, bi, ov, oi);
-      }
-      if (l15 == 0) { rv[cs][row] = bv; ri[cs][row] = bi; }
-      return;
-    }
-    if (row >= a.R) return;
-    if (MODE == MODE_SWIGLU) {
-      const int f = (nt_idx[0] >> 1) * 16 + l15;           // tiles 2j / 2j+1 = gate / up of features 16j..
-      if (nt_idx[NT - 1] < a.n_tiles) {
-        const float gv = v[0], uv = v[NT - 1];
-        st_act_planes(a.act_out + (size_t)row * act_ld(a.N / 2) + f, a.act_plane, gv / (1.0f + expf(-gv)) * uv, a.sat);
-      }
-    } else {
-      float* o = a.out + (size_t)split * a.split_stride;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const int col = nt_idx[t] * 16 + l15;
-        if (nt_idx[t] < a.n_tiles && col < a.N) o[(size_t)row * a.N + col] = v[t];
-      }
-    }
+  finish<MT, NT, CS, KW, MODE>(a, acc, nt_idx, reinterpret_cast<float*>(smem), group, split);
+}
+
+// One row tile (up to 16 rows), and two where K is not split across workgroups: the same stream with the activations
+// going straight into the LDS, RD chunks deep.  In the kernel above the weights are one or two chunks of 128 k ahead, and
+// the ring cannot be deeper because the activations share its registers; here they are RD - 1 chunks of 64 ahead.
+// A group is the activations and weights of one chunk; a step waits for its own group, meets the other waves (all
+// have their pieces in LDS, and none still reads the slot of the chunk before), requests group c + RD - 1 into that
+// slot and multiplies.  Loads in the loop are never predicated: past the end they re-request the last chunk.
+// Measured (between events, kernel above : this one): 9 rows head of 128256 columns 183 : 172 us (6.1 TB/s); 1 row QKV
+// 12.5 : 12.2, O 9.5 : 9.3, 32B-class O 18.8 : 18.1, QKV 20.8 : 20.2; calls 842 : 832 us (decode), 32B-class layers 415 : 410.
+// 17 rows: gate/up 41.6 : 41.0, head of 8192 18.4 : 17.9, but the short ranges of QKV 13.6 : 14.0 and O 10.9 : 11.3.  From three row
+// tiles on the kernel above is the better one (38 rows down 25.3 : 28.7, 65 rows 28.8 : 32.3, O 14.1 : 15.1 us), with chunks
+// of 128 k and three or four slots too (26.9, 30.6, 15.0; at 1 row 21.6 : 22.2 for down).
+template <int MT, int NT, int CS, int KW, int KC, int RD, int MODE>
+__global__ __launch_bounds__(64 * CS * KW) void k_gemm_few_bf16(GemmArgs a) {
+  constexpr int WAVES = CS * KW;            // CS column sets x KW k-step owners
+  constexpr int KSTEPS = KC / 32;           // MFMA k-steps per chunk
+  constexpr int KSW = KSTEPS / KW;          // ... of which this wave multiplies KSW
+  static_assert(KSTEPS % KW == 0 && KSW >= 1, "k-steps of a chunk must divide among the k-waves");
+  static_assert(MODE != MODE_SWIGLU || NT == 2, "gate and up tiles alternate");
+  constexpr int PL = TS_ACT_PLANES;         // an activation is the sum of a hi and a lo half
+  constexpr int UPR = KC / 8;               // 16-byte vectors per row of a chunk
+  constexpr int PPP = MT * 16 * UPR / 64;   // 1 KiB pieces per plane of a chunk: one direct-to-LDS load of a wave each
+  constexpr int XN = (PL * PPP + WAVES - 1) / WAVES;      // pieces a wave stages; the surplus repeats its last one
+  constexpr size_t XBYTES = (size_t)PL * PPP * 1024;
+  constexpr int GN = XN + NT * KSW;         // loads of a group
+  // one array per ring slot: the compiler then knows which loads a read of LDS has to wait for
+  static_assert(RD * XBYTES <= 160 * 1024, "the activation chunks fit the LDS");
+  __shared__ float red[KW > 1 ? WAVES * 4 * NT * 64 : 1];
+  __shared__ __attribute__((aligned(1024))) char xs0[XBYTES], xs1[XBYTES], xs2[RD > 2 ? XBYTES : 16], xs3[RD > 3 ? XBYTES : 16], xs4[RD > 4 ? XBYTES : 16], xs5[RD > 5 ? XBYTES : 16];
+  auto slot = [&](auto i_c) -> char* {
+    constexpr int I = decltype(i_c)::value;
+    if constexpr (I == 0) return xs0;
+    else if constexpr (I == 1) return xs1;
+    else if constexpr (I == 2) return xs2;
+    else if constexpr (I == 3) return xs3;
+    else if constexpr (I == 4) return xs4;
+    else return xs5;
   };
-  if (KW == 1) {
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, g = lane >> 4;
+  const int cs = wave / KW, kq = wave % KW;
+  // Place: workgroups are dealt to the 8 XCDs round robin by id.  With a.runs each XCD takes a contiguous run of
+  // the (split, column group) pairs in split order, else the pairs go round robin as they come (use_runs).
+  const int units = a.groups * a.splits;
+  const int unit = a.runs ? (int)((blockIdx.x & 7) * ((units + 7) / 8) + (blockIdx.x >> 3)) : (int)blockIdx.x;
+  if (unit >= units) return;
+  const int group = unit % a.groups, split = unit / a.groups;
+  const int kbase0 = split * a.kper;
+  const int n_chunks = a.kper / KC;
+
+  // Addresses are (uniform 64-bit base) + (32-bit per-lane byte offset that never changes).
+  const int cs_u = __builtin_amdgcn_readfirstlane(cs), kq_u = __builtin_amdgcn_readfirstlane(kq), wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const char* wbase[NT];                    // start of this wave's k range in each owned tile row
+  int nt_idx[NT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float v[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) v[t] = acc[mt][t][r];
-        emit(mt, r, v);
-      }
-  } else {
-    // add the KW accumulators of a column set through LDS (the activation buffers are free
-    // after the loop's last barrier), one row tile at a time, always in the order kq = 0, 1, ...
-    float* red = reinterpret_cast<float*>(smem);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) red[((wave * 4 + r) * NT + t) * 64 + lane] = acc[mt][t][r];
-      __syncthreads();
-      for (int r = kq; r < 4; r += KW) {                 // this wave finishes rows r of the tile
-        float v[NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          float sum = 0.f;
-#pragma unroll
-          for (int k = 0; k < KW; ++k) sum += red[(((cs * KW + k) * 4 + r) * NT + t) * 64 + lane];
-          v[t] = sum;
-        }
-        emit(mt, r, v);
-      }
-      __syncthreads();
-    }
+  for (int t = 0; t < NT; ++t) {
+    nt_idx[t] = (group * CS + cs_u) * NT + t;
+    const int c = nt_idx[t] < a.n_tiles ? nt_idx[t] : a.n_tiles - 1;   // idle waves re-read a valid tile
+    wbase[t] = reinterpret_cast<const char*>(a.Wt) + ((size_t)c * a.kt_count + kbase0 / 32 + kq_u * KSW) * 1024;
   }
-  if (ARGMAX) {
-    __syncthreads();
-    if (tid < MT * 16 && tid < a.R) {
-      float bv = rv[0][tid];
-      int bi = ri[0][tid];
-      for (int c = 1; c < CS; ++c) amax_take(bv, bi, rv[c][tid], ri[c][tid]);
-      a.aval[(size_t)tid * a.amax_parts + group] = bv;
-      a.aidx[(size_t)tid * a.amax_parts + group] = bi;
-    }
+  const uint32_t w_lane = lane * 16;
+  // a row's vectors stand permuted, so that the reads meet no bank twice (see XS above)
+  auto swz = [](int row) { return KC == 128 ? row & 15 : row >> 1 & 7; };
+  // The workspace only grows, and a plane of one that held a very large batch passes 4 GiB: the plane is in the
+  // base, the lane offset covers the rows of this pass.
+  const char* xbase = reinterpret_cast<const char*>(a.X) + (size_t)kbase0 * 2;
+  const size_t plane_bytes = a.x_plane * 2;
+  int piece[XN];
+  uint32_t x_off[XN];
+#pragma unroll
+  for (int p = 0; p < XN; ++p) {
+    piece[p] = min(p * WAVES + wave_u, PL * PPP - 1);
+    const int rl = piece[p] % PPP * (64 / UPR) + lane / UPR;
+    // rows past the last come from one spare row, which is zero: their lines are fetched once, and zeros cost the
+    // matrix pipes little power.  17 rows (32 before): head of 8192 columns 19.4 -> 16.3 us, gate/up 40.6 -> 39.7 us,
+    // O 9.2 -> 8.8 us
+    const int row = rl < a.R ? rl : a.zero_row;
+    x_off[p] = ((uint32_t)row * (uint32_t)act_ld(a.K) + ((lane % UPR) ^ swz(rl)) * 8) * 2;
   }
+
+  f32x4 acc[MT][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  f16x8 w[RD][NT][KSW];
+  const int last_chunk = n_chunks - 1;
+  auto request = [&](auto i_c, int chunk) __attribute__((always_inline)) {
+    constexpr int I = decltype(i_c)::value;
+    const int ch = min(chunk, last_chunk);
+    const char* xc = xbase + (size_t)ch * (KC * 2);
+#pragma unroll
+    for (int p = 0; p < XN; ++p) {
+      uint32_t o = x_off[p];
+      asm("" : "+v"(o));
+      __builtin_amdgcn_global_load_lds((const TS_GLOBAL void*)(xc + (piece[p] >= PPP ? plane_bytes : 0) + o),
+                                       (TS_LDS void*)(slot(i_c) + piece[p] * 1024), 16, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t wl = w_lane;
+    asm("" : "+v"(wl));
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int j = 0; j < KSW; ++j)
+        w[I][t][j] = __builtin_nontemporal_load(reinterpret_cast<const f16x8*>(wbase[t] + (size_t)ch * (KSTEPS * 1024) + wl + j * 1024));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  uint32_t x_read[KSW];
+#pragma unroll
+  for (int j = 0; j < KSW; ++j) x_read[j] = l15 * (KC * 2) + (((kq * KSW + j) * 4 + g) ^ swz(l15)) * 16;
+  // T < 0: a step of the loop.  T >= 0: step T of the rest, behind which no chunk is left to request.
+  auto step = [&](auto i_c, auto t_c, int c) __attribute__((always_inline)) {
+    constexpr int I = decltype(i_c)::value, T = decltype(t_c)::value;
+    constexpr int LEFT = RD - 2 - (T < 0 ? 0 : T);           // later groups that may stay in flight
+    wait_loads<(LEFT > 0 ? LEFT : 0) * GN>();
+    if (T < 0) request(std::integral_constant<int, (I + RD - 1) % RD>{}, c + RD - 1);
+#pragma unroll
+    for (int ks = 0; ks < KSW; ++ks)
+#pragma unroll
+      for (int pl = 0; pl < PL; ++pl) {
+        f16x8 xa[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          xa[mt] = *reinterpret_cast<const f16x8*>(slot(i_c) + pl * (PPP * 1024) + mt * (16 * KC * 2) + x_read[ks]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[mt], w[I][t][ks], acc[mt][t], 0, 0, 0);
+      }
+  };
+  auto ring = [&](auto n, auto&& f) __attribute__((always_inline)) {       // f(slot, number) for the first n slots
+    constexpr int N = decltype(n)::value;
+    if constexpr (N > 0) f(std::integral_constant<int, 0>{});
+    if constexpr (N > 1) f(std::integral_constant<int, 1>{});
+    if constexpr (N > 2) f(std::integral_constant<int, 2>{});
+    if constexpr (N > 3) f(std::integral_constant<int, 3>{});
+    if constexpr (N > 4) f(std::integral_constant<int, 4>{});
+    if constexpr (N > 5) f(std::integral_constant<int, 5>{});
+  };
+  using Loop = std::integral_constant<int, -1>;
+  using Rest = std::integral_constant<int, RD - 1>;
+  ring(Rest{}, [&](auto i_c) __attribute__((always_inline)) { request(i_c, decltype(i_c)::value); });
+  int c0 = 0;
+  for (; c0 + RD <= n_chunks; c0 += RD)
+    ring(std::integral_constant<int, RD>{}, [&](auto i_c) __attribute__((always_inline)) { step(i_c, Loop{}, c0 + decltype(i_c)::value); });
+  ring(Rest{}, [&](auto i_c) __attribute__((always_inline)) { if (c0 + decltype(i_c)::value < n_chunks) step(i_c, i_c, c0 + decltype(i_c)::value); });
+  // nothing may still be on its way into the LDS when it is used otherwise or given back
+  wait_loads<0>();
+
+  finish<MT, NT, CS, KW, MODE>(a, acc, nt_idx, red, group, split);
 }
 
 template <int NT, int CS, int KW, int KC, int PF, int MODE>
 void launch_mt(int mt, dim3 grid, hipStream_t s, const GemmArgs& a) {
   const dim3 block(64 * CS * KW);
   switch (mt) {
-    case 1: hipLaunchKernelGGL((k_gemm_bf16<1, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a); break;
-    case 2: hipLaunchKernelGGL((k_gemm_bf16<2, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a); break;
+    case 1: hipLaunchKernelGGL((k_gemm_few_bf16<1, NT, CS, KW, (KW > 2 ? 128 : 64), (KW > 2 ? 4 : 6), MODE>), grid, block, 0, s, a); break;
+    case 2:
+      if constexpr (MODE != MODE_PARTIAL) hipLaunchKernelGGL((k_gemm_few_bf16<2, NT, CS, KW, (KW > 2 ? 128 : 64), (KW > 2 ? 4 : 6), MODE>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((k_gemm_bf16<2, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a);
+      break;
     case 3: hipLaunchKernelGGL((k_gemm_bf16<3, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a); break;
     case 4: hipLaunchKernelGGL((k_gemm_bf16<4, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a); break;
     default: hipLaunchKernelGGL((k_gemm_bf16<5, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a); break;
@@ -416,16 +583,20 @@ GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
       const long rounds = (wgs + m->n_cu - 1) / m->n_cu;
       const double kper = (double)K / s;
       double cost = rounds * cols * kper * 2.0;
-      if (s > 1) cost += std::max(2.3 * s * R * (double)N * 4.0 / m->n_cu, 5.0 * std::min(N, 1024) * s);
-      cost += 0.3 * rounds * rows * kper * 2.0 * TS_ACT_PLANES;
+      // one row tile (the kernel with the deep ring): activations weigh little, splits more than their bytes, and neither
+      // one tile per wave nor the number of waves matters.  One row, before and with its own constants: QKV 12.3 -> 11.8 us,
+      // down 21.5 -> 20.9; 32B-class O 18.0 -> 16.6, down 42.5 -> 40.2 (9 rows 12.8 -> 12.6, 22.0 -> 21.2, 19.2 -> 18.7, 43.0 -> 41.2)
+      const bool one = rows <= 16 && mode == MODE_PARTIAL;
+      if (s > 1) cost += std::max(2.3 * s * R * (double)N * 4.0 / m->n_cu, (one && N >= 1024 ? 8.0 : 5.0) * std::min(N, 1024) * s);
+      cost += (one ? 0.1 : 0.3) * rounds * rows * kper * 2.0 * TS_ACT_PLANES;
       // Measured (8B shape): over a long K range the k-wave shape wins by its deeper prefetch (gate/up, 32
       // chunks, 65 rows: 55.5 us against 57.7 us for the 4-wave shape of the same columns; down, 14 chunks, 1 to
       // 17 rows 21.7 - 22.9 against 22.2 - 23.8 us, from 38 rows on no more); over the short ranges of the split
       // projections its longer prologue and the cross-wave reduction are not amortised (O, 4 chunks, 65 rows:
       // 16.1 against 14.4 us; QKV, 8 chunks: 22.4 against 20.4 us).
       const bool long_k = kper / kc >= 16 || (kper / kc >= 12 && rows <= 32);
-      if (long_k ? kShapeCS[shape] * kShapeKW[shape] < 6 : kShapeKW[shape] > 1) cost *= 1.05;
-      if (kShapeNT[shape] < 2) cost *= 1.05;                     // one tile per wave reads twice the LDS per weight byte
+      if (!one && (long_k ? kShapeCS[shape] * kShapeKW[shape] < 6 : kShapeKW[shape] > 1)) cost *= 1.05;
+      if (!one && kShapeNT[shape] < 2) cost *= 1.05;                     // one tile per wave reads twice the LDS per weight byte
       cost += rounds * 73728.0;
       if (cost < best_cost) { best_cost = cost; best.shape = shape; best.splits = s; }
     }

@@ -72,19 +72,6 @@ constexpr int WAVES = 8;
 // kernels with one or two k-waves run two workgroups per CU and have half the registers and LDS.
 constexpr int ring_depth(int MT, int KW) { return KW <= 2 ? (MT <= 4 ? 3 : 4) : MT <= 4 ? 4 : MT <= 6 ? 3 : 2; }
 
-// Waits until at most N of the wave's vector-memory loads are in flight (and its LDS accesses are done), then for the
-// other waves of the workgroup.
-template <int N>
-__device__ __forceinline__ void wait_loads() {
-  static_assert(N < 64, "the counter has six bits");
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt((N & 15) | 7 << 4 | (N >> 4) << 14);      // vmcnt(N) lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
 template <int MT, int CS, int KW, int MODE>
 __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm_rows_bf16(RowsArgs a) {
   static_assert(CS * KW == WAVES, "8 waves");

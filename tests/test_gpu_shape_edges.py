@@ -110,6 +110,25 @@ def test_merge_of_a_batch(n_seqs, P):
     B.ts_model_free(model)
 
 
+@pytest.mark.parametrize("d_model,hq,d_ffn", [
+    (128, 1, 128),       # K of two chunks: less than the ring of the one-row-tile kernel holds
+    (384, 3, 1152),      # six and eighteen chunks: exactly one round of the ring, and three
+    (640, 5, 896),       # ten and fourteen: rests of four and two
+    (1024, 8, 2944),     # K splits, 46 chunks
+])
+def test_one_and_two_row_tiles(d_model, hq, d_ffn):
+    """Passes of one, fifteen, sixteen, seventeen and thirty-two rows: one row tile, two, and two with a single row."""
+    cfg, w, model, om = _load(n_layers=1, d_model=d_model, n_q_heads=hq, n_kv_heads=hq, head_dim=128, d_ffn=d_ffn, vocab=1003)
+    rng = np.random.default_rng(d_model + 1)
+    K, V = wl.gen_context_kv(cfg, 70, seed=43)
+    for n in (0, 14, 15, 16, 31):
+        kv, okv = U.make_pair(cfg, model, K, V, 9)
+        tok, par = wl.random_tree(n, cfg.vocab, rng)
+        U.check_verify(cfg, model, om, kv, okv, tok, par, label="d%d rows %d" % (d_model, n + 1))
+        B.ts_kv_free(kv)
+    B.ts_model_free(model)
+
+
 @pytest.mark.parametrize("d_model,hq,d_ffn,vocab,n_seqs,n_nodes", [
     (128, 1, 128, 97, 2, 40),        # 82 rows; one to four chunks of K: fewer than the ring holds
     (384, 3, 640, 1500, 3, 32),      # 99 rows; chunk counts that are no multiple of the ring's
