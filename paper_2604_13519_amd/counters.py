@@ -51,8 +51,8 @@ def _short(k):
 
 def _gemm_mode(name):
     """Epilogue of a projection (0 partial sums, 1 arg-max, 2 SwiGLU); None: not a projection of a bf16 model."""
-    m = re.match(r"k_gemm_bf16<(?:\d+, ){6}(\d+), \d+>|k_gemm_rows_bf16<(?:\d+, ){3}(\d+)>", name)
-    return int(m.group(1) or m.group(2)) if m else None
+    m = re.match(r"k_gemm_(?:bf16<(?:\d+, ){6}(\d+), \d+|few_bf16<(?:\d+, ){6}(\d+)|rows_bf16<(?:\d+, ){3}(\d+))>", name)
+    return int(m.group(m.lastindex)) if m else None
 
 
 _KINDS = {"k_embed_rope": "embed_rope_table", "k_norm": "residual_rmsnorm", "k_rope_kv": "rope_kv_write", "k_attn_bf16": "attn_bf16",
@@ -132,8 +132,8 @@ def trace_summary(db, workload, command, bench_json=None):
         f.write("`python -m paper_2604_13519_amd.counters trace <results.db> --workload %s`:\n\n    %s\n\n" % (workload, command))
         f.write("Durations are kernel begin-to-end times from the trace; the run also holds model load (k_repack_tiles, k_kv_xfer)\n"
                 "and bench.py's untimed passes.  Template arguments of `k_gemm_bf16`: row tiles, tiles per wave, column sets, k-waves,\n"
-                "chunk, prefetch depth, mode (0 partial sums, 1 arg-max, 2 SwiGLU), LDS pad; of `k_gemm_rows_bf16`: row tiles, column sets,\n"
-                "k-waves, mode; grids in workgroups.\n\n")
+                "chunk, prefetch depth, mode (0 partial sums, 1 arg-max, 2 SwiGLU), LDS pad; of `k_gemm_few_bf16` the same with the ring's\n"
+                "depth and no pad; of `k_gemm_rows_bf16`: row tiles, column sets, k-waves, mode; grids in workgroups.\n\n")
         f.write("| kind | kernel | calls | total us | avg us | % |\n|---|---|---:|---:|---:|---:|\n")
         for (kind, k), (n, t) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
             if t / total < 0.0005:

@@ -13,7 +13,8 @@
 //    the weights of the next PF chunks are in flight (register ring) while the current one
 //    is multiplied.
 //  * The activations X (R x K, tiny) are shared by the WAVES waves of a workgroup through a
-//    double-buffered LDS chunk and read as A operands with 16-byte LDS loads.
+//    double-buffered LDS chunk and read as A operands with 16-byte LDS loads.  With one row tile, and two
+//    where K is not split, they go straight into a deeper LDS ring (k_gemm_few_bf16).
 //  * K is split two ways.  Inside a workgroup, KW waves share the same output columns and take
 //    alternate k-steps of every chunk; their accumulators are added through LDS in a fixed
 //    order at the end.  Across workgroups, partial sums go to a fp32

@@ -315,7 +315,8 @@ __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm
       }
       __syncthreads();
     }
-  }  if (MODE == MODE_ARGMAX) {
+  }
+  if (MODE == MODE_ARGMAX) {
     __syncthreads();
     if (tid < MT * 16 && row0 + tid < a.R) {
       float bv = rv[0][tid];

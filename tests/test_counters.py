@@ -44,7 +44,7 @@ def test_a_counter_pass_is_grouped_by_kind(tmp_path):
     assert len([k for k in got if k[0] == "gemm_qkv"]) == 2 and sum(len(c["X"]) for c in got.values()) == len(SEQ)
 
 
-@pytest.mark.parametrize("name,mode", [("k_gemm_bf16<1, 2, 4, 1, 128, 1, 0, 8>", 0), ("k_gemm_rows_bf16<8, 2, 4, 2>", 2),
+@pytest.mark.parametrize("name,mode", [("k_gemm_bf16<1, 2, 4, 1, 128, 1, 0, 8>", 0), ("k_gemm_few_bf16<1, 1, 2, 4, 128, 4, 1>", 1), ("k_gemm_rows_bf16<8, 2, 4, 2>", 2),
                                        ("k_gemm_rows_bf16<4, 8, 1, 1>", 1), ("k_gemm_f32<1, 1, false>", None), ("k_norm<float>", None)])
 def test_projection_modes(name, mode):
     assert C._gemm_mode(name) == mode
