@@ -104,7 +104,11 @@ __device__ __forceinline__ float max_over_lane_groups(float x) {
 }
 
 // Waits until at most N of the wave's vector-memory loads are in flight (and its LDS accesses are done), then for the
-// other waves of the workgroup.
+// other waves of the workgroup.  Loads retire in the order of their issue, so a ring of chunks waits for its oldest by
+// the number of loads the later ones issued.  That holds only while every chunk issues exactly that number: no load of
+// a chunk may be predicated, and none may be left out by the compiler, which does so where nothing uses its value - the
+// step would then read, now and then, what has not arrived.  So every register that a chunk loads has to be used on every
+// path, if only by keep_loaded; tests/test_wait_counts.py walks the compiled kernels for it.
 template <int N>
 __device__ __forceinline__ void wait_loads() {
   static_assert(N < 64, "the counter has six bits");
@@ -115,6 +119,10 @@ __device__ __forceinline__ void wait_loads() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
+
+// a use of a loaded value that costs nothing: the load that brings it cannot be left out
+template <typename T>
+__device__ __forceinline__ void keep_loaded(const T& v) { asm volatile("" :: "v"(v)); }
 
 // keep the larger value; among equal values the lower index
 __device__ __forceinline__ void amax_take(float& bv, int& bi, float v, int i) {

@@ -466,7 +466,15 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_few_bf16(GemmArgs a) {
   int c0 = 0;
   for (; c0 + RD <= n_chunks; c0 += RD)
     ring(std::integral_constant<int, RD>{}, [&](auto i_c) __attribute__((always_inline)) { step(i_c, Loop{}, c0 + decltype(i_c)::value); });
-  ring(Rest{}, [&](auto i_c) __attribute__((always_inline)) { if (c0 + decltype(i_c)::value < n_chunks) step(i_c, i_c, c0 + decltype(i_c)::value); });
+  ring(Rest{}, [&](auto i_c) __attribute__((always_inline)) {
+    constexpr int I = decltype(i_c)::value;
+    if (c0 + I < n_chunks) step(i_c, i_c, c0 + I);
+    else                                                 // a request past the end
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int j = 0; j < KSW; ++j) keep_loaded(w[I][t][j]);
+  });
   // nothing may still be on its way into the LDS when it is used otherwise or given back
   wait_loads<0>();
 

@@ -228,9 +228,17 @@ __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm
     if constexpr (RD > 2) step(I2{}, Loop{}, c0 + 2);
     if constexpr (RD > 3) step(I3{}, Loop{}, c0 + 3);
   }
-  if (c0 < n_chunks) step(I0{}, I0{}, c0);
-  if constexpr (RD > 2) if (c0 + 1 < n_chunks) step(I1{}, I1{}, c0 + 1);
-  if constexpr (RD > 3) if (c0 + 2 < n_chunks) step(I2{}, I2{}, c0 + 2);
+  // the rest; a slot that it does not reach holds a request past the end
+  auto rest = [&](auto i_c) {
+    constexpr int I = decltype(i_c)::value;
+    if (c0 + I < n_chunks) step(i_c, i_c, c0 + I);
+    else
+#pragma unroll
+      for (int t = 0; t < NT; ++t) keep_loaded(w[I][t]);
+  };
+  rest(I0{});
+  if constexpr (RD > 2) rest(I1{});
+  if constexpr (RD > 3) rest(I2{});
   // nothing may still be on its way into the LDS when it is used otherwise or given back
   wait_loads<0>();
 
