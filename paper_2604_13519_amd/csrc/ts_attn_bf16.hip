@@ -550,7 +550,9 @@ int heads_per_block(int G) { return G >= 4 ? 4 : (G >= 2 ? 2 : 1); }
 // One sequence: as many equal units as cover the CUs once.
 // Several: no unit is longer than L blocks, and L is the smallest with which the units make r workgroups a CU; r is
 // the one with the least modelled time: r full rounds of units or, where lengths leave the rounds ragged, the mean
-// load of a CU and half a unit; two workgroups that share a CU take one and a half times as long as one.  A sequence
+// load of a CU and half a unit; two workgroups that share a CU take one and a half times as long as one, 1.35 times
+// with one row tile, whose workgroups mostly wait for their keys (with 1.5 there, us a launch, against 1.35: 4 x 4096 keys of 1 row
+// 20.9 : 18.6, of 16 rows 21.9 : 20.2, 6 x 4096 .. 1024 20.1 : 19.1, 6 x 1000 11.8 : 11.2).  A sequence
 // gets units in proportion to its length, so that every workgroup has nearly the same share and the last round is
 // full.  Against one number of splits for all sequences, chosen so that the longest share is half of a CU's average
 // load (8B shape unless noted; us a launch): 4 x 32768 keys of 65 rows, 8 heads 397 -> 306 (576 workgroups were 2.25
@@ -586,6 +588,7 @@ int attn_bf16_units(const ts_model* m, int n_seqs, const int* n_keys, int max_M,
     total += (n_keys[s] + KB - 1) / KB;
   }
   const bool pairs = hb * (max_M > 48 ? 2 : 1) <= 4;     // up to four waves: two workgroups share a CU
+  const double two = max_M <= 16 ? 1.35 : 1.5;           // ... and take so much longer than one
   const int per_round = std::max(1, m->n_cu / per_unit);
   auto count = [&](int len) {
     long u = 0;
@@ -604,8 +607,8 @@ int attn_bf16_units(const ts_model* m, int n_seqs, const int* n_keys, int max_M,
       if (count(mid) <= (long)r * per_round) hi = mid;
       else lo = mid + 1;
     }
-    const double unit = lo + kUnitFixed, rounds = pairs ? r / 2 * 1.5 + r % 2 : r;
-    const double mean = (double)(total + kUnitFixed * count(lo)) / per_round * (pairs && r > 1 ? 0.75 : 1.0);
+    const double unit = lo + kUnitFixed, rounds = pairs ? r / 2 * two + r % 2 : r;
+    const double mean = (double)(total + kUnitFixed * count(lo)) / per_round * (pairs && r > 1 ? two / 2 : 1.0);
     const double cost = std::min(rounds * unit, mean + 0.5 * unit);
     if (cost < best) { best = cost; best_len = lo; }
   }
