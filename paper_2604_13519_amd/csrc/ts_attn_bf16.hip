@@ -49,9 +49,9 @@ struct AttnArgs {
   const bf16_t* Qb;          // [rows][Hq*HD], IEEE half bit patterns
   const uint64_t* row_anc;   // [rows]
   const AttnUnit* units;
-  uint16_t* part_o;          // [R][Hq][splits][HD], IEEE half: the split's output divided by its row sum
-  float* part_ml;            // [R][Hq][splits][2]
-  int layer, Hq, Hkv, splits, n_units;   // splits: slots per (row, head) in the partial buffers
+  uint16_t* part_o;          // per row [Hq][splits][HD], IEEE half: the split's output divided by its row sum
+  float* part_ml;            // per row [Hq][splits][2]
+  int layer, Hq, Hkv, n_units;
   float scale;               // 1/sqrt(head_dim) * log2(e): scores are kept in log2 units
 };
 
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
     const float l = l_run[mt][0];  // already the sum over all keys (MFMA reduces over the lane groups)
     const int lrow = (tile0 + mt) * 16 + l15;
     if (lrow < M) {
-      const size_t base = ((size_t)(sd.row0 + lrow) * a.Hq + h) * a.splits + split;
+      const size_t base = (size_t)(sd.part0 + lrow * sd.splits) * a.Hq + h * sd.splits + split;
       if (g4 == 0) {
         a.part_ml[base * 2 + 0] = m_run[mt] == kNoRef ? -INFINITY : m_run[mt];
         a.part_ml[base * 2 + 1] = l;
@@ -410,15 +410,21 @@ constexpr int kMergeFew = 16;
 bool merge_few(int slots, int splits) { return splits <= kMergeFew && slots >= (splits <= 8 ? 4096 : 5120); }
 
 __global__ __launch_bounds__(256) void k_attn_merge_few(const uint16_t* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                        f16_t* __restrict__ Ab, size_t a_plane, int slots, int Hq, int HD, int stride,
-                                                        const int32_t* __restrict__ row_splits,
+                                                        f16_t* __restrict__ Ab, size_t a_plane, int slots, int Hq, int HD, int all_splits,
+                                                        const int2* __restrict__ row_part,
                                                         unsigned long long* __restrict__ sat) {
   const int tps = HD / 8;                  // threads per slot
   const int slot = blockIdx.x * (256 / tps) + threadIdx.x / tps, d8 = threadIdx.x % tps;
   if (slot >= slots) return;
-  const float2* ml = reinterpret_cast<const float2*>(part_ml) + (size_t)slot * stride;
-  const uint4* po = reinterpret_cast<const uint4*>(part_o) + (size_t)slot * stride * tps + d8;
-  const int splits = row_splits ? row_splits[slot / Hq] : stride;
+  size_t base = (size_t)slot * all_splits;
+  int splits = all_splits;
+  if (row_part) {
+    const int2 p = row_part[slot / Hq];
+    base = (size_t)p.x * Hq + slot % Hq * p.y;
+    splits = p.y;
+  }
+  const float2* ml = reinterpret_cast<const float2*>(part_ml) + base;
+  const uint4* po = reinterpret_cast<const uint4*>(part_o) + base * tps + d8;
   float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, den = 0.f, mstar = -INFINITY;
   float2 w[kMergeFew];
 #pragma unroll
@@ -456,8 +462,8 @@ __global__ __launch_bounds__(256) void k_attn_merge_few(const uint16_t* __restri
 constexpr int kMergeMaxSplits = 512;
 
 __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__ part_o, const float* __restrict__ part_ml,
-                                                    f16_t* __restrict__ Ab, size_t a_plane, int Hq, int HD, int stride,
-                                                    const int32_t* __restrict__ row_splits,
+                                                    f16_t* __restrict__ Ab, size_t a_plane, int Hq, int HD, int all_splits,
+                                                    const int2* __restrict__ row_part,
                                                     unsigned long long* __restrict__ sat) {
   __shared__ float s_m[kMergeMaxSplits], s_l[kMergeMaxSplits];
   __shared__ float4 r_num[256];
@@ -467,12 +473,17 @@ __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__
   const int groups = 256 / tpp;
   const int grp = tid / tpp, d4 = tid % tpp;
   const int row = blockIdx.y, head = blockIdx.x;
-  const size_t slot = (size_t)row * Hq + head;
-  const int splits = row_splits ? row_splits[row] : stride;
+  size_t base = ((size_t)row * Hq + head) * all_splits;
+  int splits = all_splits;
+  if (row_part) {
+    const int2 p = row_part[row];
+    base = (size_t)p.x * Hq + head * p.y;
+    splits = p.y;
+  }
   const float2* ml = reinterpret_cast<const float2*>(part_ml);
   const uint2* po = reinterpret_cast<const uint2*>(part_o);     // 4 halves
   for (int sp = tid; sp < splits; sp += 256) {
-    const float2 v = ml[slot * stride + sp];
+    const float2 v = ml[base + sp];
     s_m[sp] = v.x;
     s_l[sp] = v.y;
   }
@@ -480,7 +491,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int sp = grp + u * groups;
-    o4[u] = sp < splits ? po[(slot * stride + sp) * tpp + d4] : make_uint2(0u, 0u);
+    o4[u] = sp < splits ? po[(base + sp) * tpp + d4] : make_uint2(0u, 0u);
   }
   __syncthreads();
   float mstar = -INFINITY;
@@ -492,7 +503,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const uint16_t* __restrict__
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int sp = s0 + grp + u * groups;
-        o4[u] = sp < splits ? po[(slot * stride + sp) * tpp + d4] : make_uint2(0u, 0u);
+        o4[u] = sp < splits ? po[(base + sp) * tpp + d4] : make_uint2(0u, 0u);
       }
     }
 #pragma unroll
@@ -617,13 +628,13 @@ int attn_bf16_units(const ts_model* m, int n_seqs, const int* n_keys, int max_M,
 }
 int attn_bf16_max_units(const ts_model* m, int n_seqs) { return std::max(std::max(kMergeMaxSplits, kBatchSplits * n_seqs), m->n_cu + n_seqs); }
 
-void launch_attn_bf16(ts_model* m, const RowMeta& rm, int n_units, int layer, int splits, int max_M) {
+void launch_attn_bf16(ts_model* m, const RowMeta& rm, int n_units, int layer, int max_M) {
   ProfScope ps(m, "attn_bf16");
   const ts_model_config& c = m->cfg;
   AttnArgs a;
   a.Qb = (const bf16_t*)m->Qb; a.row_anc = rm.anc; a.units = m->unit_dev;
   a.part_o = m->attn_part_o; a.part_ml = m->attn_part_ml;
-  a.layer = layer; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.splits = splits; a.n_units = n_units;
+  a.layer = layer; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.n_units = n_units;
   a.scale = (float)(1.4426950408889634 / sqrt((double)c.head_dim));   // 1/sqrt(hd) * log2(e)
   const int G = c.n_q_heads / c.n_kv_heads;
   const int hb = heads_per_block(G);
@@ -633,8 +644,8 @@ void launch_attn_bf16(ts_model* m, const RowMeta& rm, int n_units, int layer, in
   else launch_hd<64>(hb, mt, grid, m->stream, a);
 }
 
-// row_splits: splits of each row's sequence (nullptr: all have `splits`, the stride of the partial buffers)
-void launch_attn_merge(ts_model* m, int R, int splits, const int32_t* row_splits) {
+// splits: the most of any row; row_part: where each row's are (nullptr: all rows have `splits`)
+void launch_attn_merge(ts_model* m, int R, int splits, const int2* row_part) {
   ProfScope ps(m, "attn_merge");
   const ts_model_config& c = m->cfg;
   const size_t plane = (size_t)(m->ws_rows + TS_MROWS_PER_BLOCK) * act_ld(m->q_dim);
@@ -642,10 +653,10 @@ void launch_attn_merge(ts_model* m, int R, int splits, const int32_t* row_splits
   if (merge_few(slots, splits)) {
     const int per_wg = 256 / (c.head_dim / 8);
     hipLaunchKernelGGL(k_attn_merge_few, dim3((slots + per_wg - 1) / per_wg), dim3(256), 0, m->stream, m->attn_part_o, m->attn_part_ml,
-                       (f16_t*)m->Ab, plane, slots, c.n_q_heads, c.head_dim, splits, row_splits, m->sat_count);
+                       (f16_t*)m->Ab, plane, slots, c.n_q_heads, c.head_dim, splits, row_part, m->sat_count);
     return;
   }
   // R fits the second grid dimension: beyond 65535 rows there are more slots than merge_few leaves to this kernel
   hipLaunchKernelGGL(k_attn_merge, dim3(c.n_q_heads, R), dim3(256), 0, m->stream, m->attn_part_o, m->attn_part_ml,
-                     (f16_t*)m->Ab, plane, c.n_q_heads, c.head_dim, splits, row_splits, m->sat_count);
+                     (f16_t*)m->Ab, plane, c.n_q_heads, c.head_dim, splits, row_part, m->sat_count);
 }

@@ -165,10 +165,10 @@ static void free_workspace(ts_model* m) {
   m->attn_part_o = nullptr; m->attn_part_ml = nullptr; m->rope_cs = nullptr; m->row_dst = nullptr; m->amax_val = nullptr; m->amax_idx = nullptr;
   m->logits = nullptr; m->meta_dev = nullptr; m->seq_dev = nullptr; m->unit_dev = nullptr; m->rec_host = nullptr; m->seq_host = nullptr; m->unit_host = nullptr; m->res_host = nullptr;
   m->samp_part = nullptr; m->samp_tok = nullptr;
-  m->ws_rows = 0; m->ws_seqs = 0; m->logits_rows = 0; m->attn_max_splits = 0; m->part_elems = 0;
+  m->ws_rows = 0; m->ws_seqs = 0; m->logits_rows = 0; m->attn_part_slots = 0; m->part_elems = 0;
 }
 
-static size_t meta_bytes_for(int rows) { return (size_t)rows * (6 * sizeof(int32_t) + sizeof(uint64_t) + sizeof(float)); }
+static size_t meta_bytes_for(int rows) { return (size_t)rows * (5 * sizeof(int32_t) + sizeof(int2) + sizeof(uint64_t) + sizeof(float)); }
 
 // Row buffers carry TS_MROWS_PER_BLOCK spare rows: tile-granular kernels read (never use)
 // rows past the last real one.
@@ -240,18 +240,16 @@ static ts_status ensure_workspace(ts_model* m, int rows, int seqs, bool want_log
   return TS_OK;
 }
 
-static ts_status ensure_attn_partials(ts_model* m, int splits, int R) {
-  if (m->cfg.dtype != TS_DTYPE_BF16) return TS_OK;
-  const size_t need = (size_t)splits * R;
-  if (need <= (size_t)m->attn_max_splits) return TS_OK;   // attn_max_splits counts split*row slots
+static ts_status ensure_attn_partials(ts_model* m, size_t need) {       // need: (row, split) pairs
+  if (need <= m->attn_part_slots) return TS_OK;
   TS_HIP(hipStreamSynchronize(m->stream));
   dev_free(m->attn_part_o); dev_free(m->attn_part_ml);
   m->attn_part_o = nullptr; m->attn_part_ml = nullptr;
-  m->attn_max_splits = 0;
+  m->attn_part_slots = 0;
   ts_status st;
   if ((st = dev_alloc_bytes((void**)&m->attn_part_o, need * m->q_dim * 2, true))) return st;
   if ((st = dev_alloc_bytes((void**)&m->attn_part_ml, need * m->cfg.n_q_heads * 2 * 4, true))) return st;
-  m->attn_max_splits = (int)need;
+  m->attn_part_slots = need;
   return TS_OK;
 }
 
@@ -393,7 +391,7 @@ extern "C" ts_status ts_model_load(const ts_model_config* cfg, const ts_weights*
   m->stream = nullptr;
   m->embed = m->lm_head = nullptr; m->norm_f = nullptr; m->range_flag = nullptr; m->sat_count = nullptr;
   m->H = nullptr; m->Xn = m->Qb = m->Ab = m->Fb = nullptr; m->part = nullptr; m->part_elems = 0;
-  m->attn_part_o = nullptr; m->attn_part_ml = nullptr; m->attn_max_splits = 0;
+  m->attn_part_o = nullptr; m->attn_part_ml = nullptr; m->attn_part_slots = 0;
   m->rope_cs = nullptr; m->row_dst = nullptr; m->amax_val = nullptr; m->amax_idx = nullptr; m->logits = nullptr;
   m->keep_logits = false; m->logits_rows = 0; m->meta_dev = nullptr; m->rec_host = nullptr; m->seq_host = nullptr;
   m->seq_dev = nullptr; m->unit_dev = nullptr; m->unit_host = nullptr; m->res_host = nullptr; m->ws_rows = 0; m->ws_seqs = 0;
@@ -734,13 +732,13 @@ static RowMeta carve_meta(void* base, int rows) {
   RowMeta rm;
   char* p = (char*)base;
   rm.anc = (uint64_t*)p; p += (size_t)rows * sizeof(uint64_t);
+  rm.part = (int2*)p;    p += (size_t)rows * sizeof(int2);
   rm.tok = (int32_t*)p;  p += (size_t)rows * 4;
   rm.seq = (int32_t*)p;  p += (size_t)rows * 4;
   rm.lrow = (int32_t*)p; p += (size_t)rows * 4;
   rm.par = (int32_t*)p;  p += (size_t)rows * 4;
   rm.depth = (int32_t*)p; p += (size_t)rows * 4;
-  rm.u = (float*)p;      p += (size_t)rows * 4;
-  rm.splits = (int32_t*)p;
+  rm.u = (float*)p;
   return rm;
 }
 
@@ -793,16 +791,18 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
   if (st) return st;
   const int n_units = bf ? attn_bf16_units(m, n_seqs, n_keys, max_M, m->unit_host, seq_splits) : 0;
   const int splits = bf ? *std::max_element(seq_splits, seq_splits + n_seqs) : 1;
-  if ((st = ensure_attn_partials(m, splits, R))) return st;
+  size_t part_slots = 0;
+  for (int s = 0; s < n_seqs && bf; ++s) part_slots += (size_t)(offs[s + 1] - offs[s] + 1) * seq_splits[s];
+  if ((st = ensure_attn_partials(m, part_slots))) return st;
   const bool ragged = bf && *std::min_element(seq_splits, seq_splits + n_seqs) != splits;
 
   // ---- per-row bookkeeping (Alg. 1: flattened sequence + tree mask) ------------------
   const RowMeta dm = carve_meta(m->meta_dev, m->ws_rows + TS_MROWS_PER_BLOCK);
   const size_t page_elems = (size_t)c.n_kv_heads * TS_PAGE_SIZE * c.head_dim;
-  int r0 = 0;
+  int r0 = 0, part0 = 0, unit = 0;
   for (int s = 0; s < n_seqs; ++s) {
     ts_kv* kv = kvs[s];
-    const int n = offs[s + 1] - offs[s];
+    const int n = offs[s + 1] - offs[s], sp = bf ? seq_splits[s] : 1;
     const int P_s = blocks ? blocks->P[s] : kv->P;
     for (int i = 0; i <= n; ++i) {                        // row 0 = root, row i = node i - 1
       RowRec& q = m->rec_host[r0 + i];
@@ -812,7 +812,7 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
       q.depth = i ? up.depth + 1 : 0;
       q.tok = i ? toks[node] : blocks ? blocks->root[s] : kv->pending;
       q.pos = P_s + q.depth;
-      q.seq = s; q.lrow = i; q.par = prow; q.splits = bf ? seq_splits[s] : 1;
+      q.seq = s; q.lrow = i; q.par = prow; q.part0 = part0 + i * sp; q.splits = sp;
       q.u = sample && i ? sample->node_uniform[node] : 0.f;
       // the row's slot in layer 0; a layer adds layer_stride elements, a KV head 16 * head_dim
       const int slot = P_s + i;
@@ -825,14 +825,15 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
     sd.P = P_s; sd.M = n + 1; sd.row0 = r0; sd.n_pages = kv->pool_pages;
     sd.page_table = kv->page_table; sd.k_pool = kv->k_pool; sd.v_pool = kv->v_pool; sd.result = kv->result;
     sd.host_result = m->res_host + (size_t)s * TS_RESULT_INTS;
+    for (; unit < n_units && m->unit_host[unit].seq == s; ++unit) {       // in the order of the sequences
+      AttnUnit& u = m->unit_host[unit];
+      u.P = sd.P; u.M = sd.M; u.row0 = sd.row0; u.n_pages = sd.n_pages;
+      u.page_table = sd.page_table; u.k_pool = sd.k_pool; u.v_pool = sd.v_pool;
+      u.part0 = part0; u.splits = sp;
+    }
     kv->have_result = false;
     r0 += n + 1;
-  }
-  for (int i = 0; i < n_units; ++i) {
-    AttnUnit& u = m->unit_host[i];
-    const SeqDesc& sd = m->seq_host[u.seq];
-    u.P = sd.P; u.M = sd.M; u.row0 = sd.row0; u.n_pages = sd.n_pages;
-    u.page_table = sd.page_table; u.k_pool = sd.k_pool; u.v_pool = sd.v_pool;
+    part0 += (n + 1) * sp;
   }
 
   // ---- the pass ---------------------------------------------------------------------
@@ -867,8 +868,8 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
     project("gemm_qkv", m->Xn, L.wqkv, m->qkv_dim, d, &np, &ps);
     launch_rope_kv(m, dm, R, l, np, ps);
     if (bf) {
-      launch_attn_bf16(m, dm, n_units, l, splits, max_M);
-      launch_attn_merge(m, R, splits, ragged ? dm.splits : nullptr);
+      launch_attn_bf16(m, dm, n_units, l, max_M);
+      launch_attn_merge(m, R, splits, ragged ? dm.part : nullptr);
     } else {
       launch_attn_f32(m, dm, R, n_seqs, l, max_keys);
     }

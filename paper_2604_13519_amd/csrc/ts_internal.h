@@ -42,7 +42,7 @@ struct RowMeta {
   int32_t* depth;    // depth within its sequence (root 0)
   uint64_t* anc;     // bit i set iff draft node i is this row or one of its ancestors
   float* u;          // stochastic acceptance: the caller's uniform of this row's draft node
-  int32_t* splits;   // key splits of the row's sequence (attention merge)
+  int2* part;        // attention partials: splits of the rows before this one, its own splits (see attn_part_o)
 };
 
 // Per-sequence descriptor, device-visible.
@@ -68,7 +68,7 @@ struct AttnUnit {
   int32_t b0, b1;                      // key blocks [b0, b1)
   int32_t split;                       // which partial of its rows it writes
   int32_t seq;                         // host only
-  int32_t pad[2];
+  int32_t part0, splits;               // of the sequence's first row and of each of its rows (RowMeta::part)
 };
 
 // Where a row's new K and V go (layer 0, KV head 0): written once per pass, read by every layer's QKV epilogue.
@@ -83,9 +83,9 @@ struct RowDst {
 struct RowRec {
   uint64_t anc;
   RowDst dst;
-  int32_t tok, pos, seq, lrow, par, depth;
+  int32_t tok, pos, seq, part0;
   float u;
-  int32_t splits;
+  int16_t lrow, par, depth, splits;
 };
 static_assert(sizeof(RowRec) == 64, "one line per row");
 static_assert(sizeof(AttnUnit) % 16 == 0, "copied in 16-byte vectors");
@@ -145,9 +145,12 @@ struct ts_model {
   void* Fb;                     // SwiGLU product, likewise
   float* part;                  // split-K partial sums, [S][rows][N] fp32
   size_t part_elems;
-  uint16_t* attn_part_o;        // [rows][Hq][splits][hd], IEEE half (each split's normalised output)
-  float* attn_part_ml;          // [rows][Hq][splits][2]
-  int attn_max_splits;
+  // Per row [Hq][splits][hd], IEEE half (each split's normalised output), and [Hq][splits][2]; a row has the splits of
+  // its own sequence and starts behind the rows before it: one long request among thousands of short ones has 16, they
+  // one each, and room for the most of any for all rows would be gigabytes
+  uint16_t* attn_part_o;
+  float* attn_part_ml;
+  size_t attn_part_slots;       // room for so many (row, split) pairs
   float2* rope_cs;              // [rows][hd/2] (cos, sin)
   RowDst* row_dst;              // [rows]
   float* amax_val; int32_t* amax_idx; int amax_parts;   // [rows][parts]
@@ -205,8 +208,8 @@ void launch_gemm_rows_bf16(ts_model* m, const f16_t* X, const f16_t* Wt, float* 
                            int splits, int mode, f16_t* act_out, float* logits);
 int attn_bf16_units(const ts_model* m, int n_seqs, const int* n_keys, int max_M, AttnUnit* units, int* seq_splits);
 int attn_bf16_max_units(const ts_model* m, int n_seqs);
-void launch_attn_bf16(ts_model* m, const RowMeta& rm, int n_units, int layer, int splits, int max_M);
-void launch_attn_merge(ts_model* m, int R, int splits, const int32_t* row_splits);
+void launch_attn_bf16(ts_model* m, const RowMeta& rm, int n_units, int layer, int max_M);
+void launch_attn_merge(ts_model* m, int R, int splits, const int2* row_part);
 
 // profiling bracket
 void prof_begin(ts_model* m, const char* name);

@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void k_embed_rope(const RowRec* __restrict__ r
   }
   if (threadIdx.x == blockDim.x - 1) {
     rm.anc[r] = s_rec.anc; rm.tok[r] = s_rec.tok; rm.seq[r] = s_rec.seq; rm.lrow[r] = s_rec.lrow;
-    rm.par[r] = s_rec.par; rm.depth[r] = s_rec.depth; rm.u[r] = s_rec.u; rm.splits[r] = s_rec.splits;
+    rm.par[r] = s_rec.par; rm.depth[r] = s_rec.depth; rm.u[r] = s_rec.u; rm.part[r] = make_int2(s_rec.part0, s_rec.splits);
     dst[r] = s_rec.dst;
   }
 }

@@ -186,6 +186,38 @@ def test_units_of_a_ragged_batch(contexts, n_nodes, hq):
     B.ts_model_free(model)
 
 
+def test_partials_of_one_long_request_among_many():
+    """Key splits of one long request cost room for its own rows, not for those of the 400 short ones beside it:
+    13 splits for all 6817 rows would be 374 MB, for its 17 rows they are 29 MB.  Rows against single passes."""
+    import torch
+    cfg, w, model, om = _load(n_layers=1, d_model=256, n_q_heads=16, n_kv_heads=2, head_dim=128, d_ffn=256, vocab=97)
+    rng = np.random.default_rng(5)
+    n_seqs, nodes, long_one = 401, 16, 200
+    trees = [wl.random_tree(nodes, cfg.vocab, rng) for _ in range(n_seqs)]
+    kvs = []
+    for i in range(n_seqs):
+        K, V = wl.gen_context_kv(cfg, 20 + i % 7, seed=1000 + i)
+        kvs.append(B.ts_kv_alloc(model, 4200 if i == long_one else 60))
+        B.ts_kv_import(kvs[i], K, V)
+        B.ts_set_pending(kvs[i], i % cfg.vocab)
+    B.ts_verify_batch(model, kvs, trees)                   # the workspace of as many rows, short contexts only
+    K, V = wl.gen_context_kv(cfg, 4160, seed=77)
+    B.ts_kv_import(kvs[long_one], K, V)
+    before = torch.cuda.mem_get_info()[0]
+    B.ts_verify_batch(model, kvs, trees)
+    grown = before - torch.cuda.mem_get_info()[0]
+    assert grown <= 32 << 20, "the pass took %.0f MB more" % (grown / 1e6)
+    rows = nodes + 1
+    both = B.ts_get_logits(model, 0, rows * n_seqs, cfg.vocab).reshape(n_seqs, rows, cfg.vocab)
+    for i in (0, 1, long_one - 1, long_one, long_one + 1, n_seqs - 1):
+        B.ts_verify(model, kvs[i], *trees[i])
+        one = B.ts_get_logits(model, 0, rows, cfg.vocab)
+        assert max(U.rel_l2(a, b) for a, b in zip(both[i], one)) <= U.TOL_BF16_R, "sequence %d" % i
+    for kv in kvs:
+        B.ts_kv_free(kv)
+    B.ts_model_free(model)
+
+
 @pytest.mark.parametrize("hq,hkv", [(2, 2), (4, 2), (8, 2)])
 def test_row_tiles_of_one_wave(hq, hkv):
     """One, two and three 16-row tiles in a wave (more rows take two waves) with one, two and four query heads per
