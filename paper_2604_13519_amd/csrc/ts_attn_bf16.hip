@@ -51,7 +51,7 @@ struct AttnArgs {
   const AttnUnit* units;
   uint16_t* part_o;          // per row [Hq][splits][HD], IEEE half: the split's output divided by its row sum
   float* part_ml;            // per row [Hq][splits][2]
-  int layer, Hq, Hkv, n_units;
+  int layer, Hq, Hkv, n_units, n_cu;
   float scale;               // 1/sqrt(head_dim) * log2(e): scores are kept in log2 units
 };
 
@@ -241,10 +241,13 @@ __global__ __launch_bounds__(64 * HB * (MT1 > 0 ? 2 : 1), (HB * (MT1 > 0 ? 2 : 1
   __syncthreads();
 
   // One of the two waves of a SIMD goes first wherever both could issue, so that they do not run their matrix and
-  // their soft-max phases at the same time: the one with more row tiles, or, where two workgroups share a CU (the
-  // dispatcher puts one on every CU before any second one), the later one.  33 rows x 16 sequences 89.0 -> 86.1 us, x 8
-  // 69.8 -> 69.0, 65 rows x 4 sequences x 32768 keys 299 -> 295.6 us; single sequences the same.
-  if (RS == 2 ? wave < HB : (bid >> 8 & 1) != 0) __builtin_amdgcn_s_setprio(1);
+  // their soft-max phases at the same time.  With eight waves a workgroup fills a CU, and waves w and w + 4 share a SIMD:
+  // the first row split goes first (it has as many row tiles as the second or one more).  With up to four waves two
+  // workgroups share a CU (the dispatcher puts one on every CU before any second one), and the later one goes first.
+  // 33 rows x 16 sequences 89.0 -> 86.1 us, x 8 69.8 -> 69.0, 65 rows x 4 sequences x 32768 keys 299 -> 295.6 us; single
+  // sequences the same.  Two query heads per KV head, 65 rows (four waves), by the row split as with eight : by the
+  // workgroup: one sequence of 16384 keys 29.8 : 28.2, x 16 96.0 : 92.0 us.
+  if (HB * RS == 8 ? wave < HB : ((uint32_t)bid / (uint32_t)a.n_cu & 1) != 0) __builtin_amdgcn_s_setprio(1);
   for (int blk = b0; blk < b1; ++blk) {
     const int cur = (blk - b0) & 1;
     const bool more = blk + 1 < b1;
@@ -639,7 +642,7 @@ void launch_attn_bf16(ts_model* m, const RowMeta& rm, int n_units, int layer, in
   AttnArgs a;
   a.Qb = (const bf16_t*)m->Qb; a.row_anc = rm.anc; a.units = m->unit_dev;
   a.part_o = m->attn_part_o; a.part_ml = m->attn_part_ml;
-  a.layer = layer; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.n_units = n_units;
+  a.layer = layer; a.Hq = c.n_q_heads; a.Hkv = c.n_kv_heads; a.n_units = n_units; a.n_cu = m->n_cu;
   a.scale = (float)(1.4426950408889634 / sqrt((double)c.head_dim));   // 1/sqrt(hd) * log2(e)
   const int G = c.n_q_heads / c.n_kv_heads;
   const int hb = heads_per_block(G);
