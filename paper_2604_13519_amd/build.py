@@ -14,6 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libtoolspec_hip.so")
+HOOKS_PATH = os.path.join(OBJ_DIR, "libts_kernel_hooks.so")
 SOURCES = ["ts_host.hip", "ts_kernels_misc.hip", "ts_gemm_bf16.hip", "ts_gemm_rows_bf16.hip", "ts_attn_bf16.hip", "ts_f32.hip", "ts_draft.cpp", "ts_generate.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # keep hipcc from forming packed-fp32 instructions
@@ -34,6 +35,17 @@ def _run(cmd):
     if p.returncode != 0:
         raise RuntimeError("command failed: %s\n%s" % (" ".join(cmd), out))
     return out
+
+
+def build_test_hooks(verbose=True):
+    """The small host library through which tests reach planners and single projection launches (no kernels of its own)."""
+    src = os.path.join(os.path.dirname(HERE), "tests", "native", "kernel_hooks.cpp")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    _run([_hipcc(), "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(rocm, "include"), "-O2", "-std=c++17", "-fPIC", "-shared", src, "-x", "none", "-o", HOOKS_PATH,
+          "-L" + HERE, "-l:" + os.path.basename(LIB_PATH), "-Wl,-rpath,$ORIGIN/.."])
+    if verbose:
+        print("built", HOOKS_PATH)
+    return HOOKS_PATH
 
 
 def build_library(verbose=True):
