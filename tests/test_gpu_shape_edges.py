@@ -130,15 +130,17 @@ def test_one_and_two_row_tiles(d_model, hq, d_ffn):
 
 
 @pytest.mark.parametrize("d_model,hq,d_ffn,vocab,n_seqs,n_nodes", [
-    (128, 1, 128, 97, 2, 40),        # 82 rows; one to four chunks of K: fewer than the ring holds
-    (384, 3, 640, 1500, 3, 32),      # 99 rows; chunk counts that are no multiple of the ring's
-    (256, 2, 1152, 5000, 2, 64),     # 130 rows, nine row tiles
-    (640, 5, 384, 8209, 4, 64),      # 260 rows, ragged head
-    (512, 4, 1536, 700, 7, 64),      # 455 rows
+    (128, 1, 128, 97, 2, 40),        # 82 rows; every projection one chunk of 128
+    (384, 3, 640, 1500, 3, 32),      # 99 rows; one chunk a split, gate/up and head three
+    (256, 2, 1152, 5000, 2, 64),     # 130 rows, nine row tiles; one to three chunks
+    (640, 5, 384, 8209, 4, 64),      # 260 rows, six row tiles in the head, which ends inside a tile
+    (512, 4, 1536, 700, 7, 64),      # 455 rows; one to four chunks
+    (1152, 9, 8064, 20011, 16, 64),  # 1040 rows; one k-wave (gate/up, head) and two (QKV, O, down), long ranges with rests
 ])
 def test_many_rows_rings_and_small_heads(d_model, hq, d_ffn, vocab, n_seqs, n_nodes):
-    """Passes of more than 80 rows over short and odd K ranges, and heads of few column groups (arg-max joined over
-    k-waves).  Logits against single passes; the fused arg-max against the stored logits, lowest token on ties."""
+    """Passes of more than 80 rows over short and odd K ranges, and heads of few column groups.  Logits against single
+    passes; the fused arg-max against the stored logits.  (Every variant of the kernel by itself, and ties between equal
+    columns: test_gpu_projection_variants.py.)"""
     cfg, w, model, om = _load(n_layers=1, d_model=d_model, n_q_heads=hq, n_kv_heads=hq, head_dim=128, d_ffn=d_ffn, vocab=vocab)
     rng = np.random.default_rng(d_model)
     trees, kvs = [wl.random_tree(n_nodes, cfg.vocab, rng) for _ in range(n_seqs)], []
@@ -159,14 +161,17 @@ def test_many_rows_rings_and_small_heads(d_model, hq, d_ffn, vocab, n_seqs, n_no
     B.ts_model_free(model)
 
 
-@pytest.mark.parametrize("contexts,n_nodes,hq", [
-    ((2600, 150), 20, 8),                          # two sequences, few KV heads: more than 16 splits, and three
-    ((0, 63, 64, 1900, 700), 64, 16),              # one block, exactly one and two, and the longest 31: ragged splits, many slots
-    (tuple(40 + 9 * i for i in range(130)), 2, 8)  # more sequences than one round of workgroups holds
+@pytest.mark.parametrize("contexts,n_nodes,hq,hd", [
+    ((2600, 150), 20, 8, 128),                          # two sequences, few KV heads: more than 16 splits, and three
+    ((0, 63, 64, 1900, 700), 64, 16, 128),              # two blocks, two and three, and the longest 31: ragged splits, many slots
+    ((0, 61, 62, 2600), 2, 8, 128),                     # three keys, exactly one block and one key more beside 41 blocks
+    (tuple(40 + 9 * i for i in range(130)), 2, 8, 128),  # more sequences than one round of workgroups holds
+    ((0, 61, 62, 2600), 2, 8, 64),                      # heads of 64: merged by a workgroup per slot
+    ((0, 63, 64, 1900, 700, 1200), 64, 16, 64),         # ... and by a thread per 8 dims
 ])
-def test_units_of_a_ragged_batch(contexts, n_nodes, hq):
+def test_units_of_a_ragged_batch(contexts, n_nodes, hq, hd):
     """Key blocks dealt to workgroups in proportion to the lengths of a batch.  Against single passes."""
-    cfg, w, model, om = _load(n_layers=1, d_model=256, n_q_heads=hq, n_kv_heads=2, head_dim=128, d_ffn=256, vocab=97)
+    cfg, w, model, om = _load(n_layers=1, d_model=256, n_q_heads=hq, n_kv_heads=2, head_dim=hd, d_ffn=256, vocab=97)
     rng = np.random.default_rng(len(contexts))
     trees, kvs = [wl.random_tree(n_nodes, cfg.vocab, rng) for _ in contexts], []
     for i, P in enumerate(contexts):
