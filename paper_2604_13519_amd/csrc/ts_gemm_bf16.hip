@@ -14,7 +14,7 @@
 //    is multiplied.
 //  * The activations X (R x K, tiny) are shared by the WAVES waves of a workgroup through a
 //    double-buffered LDS chunk and read as A operands with 16-byte LDS loads.  With one row tile, and two
-//    where K is not split, they go straight into a deeper LDS ring (k_gemm_few_bf16).
+//    where K is not split, they mostly go straight into a deeper LDS ring (k_gemm_few_bf16, see launch_mt).
 //  * K is split two ways.  Inside a workgroup, KW waves share the same output columns and take
 //    alternate k-steps of every chunk; their accumulators are added through LDS in a fixed
 //    order at the end.  Across workgroups, partial sums go to a fp32
@@ -481,13 +481,24 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_few_bf16(GemmArgs a) {
   finish<MT, NT, CS, KW, MODE>(a, acc, nt_idx, red, group, split);
 }
 
+// One row tile, and two where K is not split: k_gemm_few_bf16, with chunks of 64 k and six slots, or, with four k-waves (one
+// k-step of a chunk each), of 128 and four.  The four k-waves of a small model's gate/up are the exception, on short ranges (4 to
+// 16 chunks) the ring does not pay for its longer prologue.  Us between events, k_gemm_bf16 : k_gemm_few_bf16 -
+// gate/up of 1, 16 and 26 rows, K 512 x 3072 columns 6.1 : 6.1, 6.2 : 6.2, 7.0 : 7.1, K 1024 x 5632 6.7 : 7.1, 7.3 : 7.6, 8.7 : 8.7,
+// K 2048 x 11264 12.9 : 13.1, 14.8 : 15.1, 18.1 : 18.0; arg-max, K 512 x 2048 6.5 : 6.5, 6.9 : 6.8, 8.2 : 7.8, K 1024 x 8192
+// 8.5 : 8.4, 8.9 : 8.7, 10.4 : 9.9.
 template <int NT, int CS, int KW, int KC, int PF, int MODE>
 void launch_mt(int mt, dim3 grid, hipStream_t s, const GemmArgs& a) {
   const dim3 block(64 * CS * KW);
+  constexpr bool FEW = KW <= 2 || MODE == MODE_ARGMAX;
+  constexpr int FKC = KW > 2 ? 128 : 64, FRD = KW > 2 ? 4 : 6;
   switch (mt) {
-    case 1: hipLaunchKernelGGL((k_gemm_few_bf16<1, NT, CS, KW, (KW > 2 ? 128 : 64), (KW > 2 ? 4 : 6), MODE>), grid, block, 0, s, a); break;
+    case 1:
+      if constexpr (FEW) hipLaunchKernelGGL((k_gemm_few_bf16<1, NT, CS, KW, FKC, FRD, MODE>), grid, block, 0, s, a);
+      else hipLaunchKernelGGL((k_gemm_bf16<1, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a);
+      break;
     case 2:
-      if constexpr (MODE != MODE_PARTIAL) hipLaunchKernelGGL((k_gemm_few_bf16<2, NT, CS, KW, (KW > 2 ? 128 : 64), (KW > 2 ? 4 : 6), MODE>), grid, block, 0, s, a);
+      if constexpr (FEW && MODE != MODE_PARTIAL) hipLaunchKernelGGL((k_gemm_few_bf16<2, NT, CS, KW, FKC, FRD, MODE>), grid, block, 0, s, a);
       else hipLaunchKernelGGL((k_gemm_bf16<2, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a);
       break;
     case 3: hipLaunchKernelGGL((k_gemm_bf16<3, NT, CS, KW, KC, PF, MODE>), grid, block, 0, s, a); break;
@@ -497,9 +508,10 @@ void launch_mt(int mt, dim3 grid, hipStream_t s, const GemmArgs& a) {
 }
 
 // The compiled tile shapes.  shape id -> (NT, CS, KW): tiles per wave, column sets and
-// k-waves per workgroup.  All use chunks of 128 k (the LDS holds two buffers of the
-// activation chunk in both planes, 90 KiB for 80 rows).  The k-wave shapes hold fewer weight registers
-// per chunk and prefetch two to four chunks ahead instead of one.
+// k-waves per workgroup.  In k_gemm_bf16 all use chunks of 128 k (the LDS holds two buffers of the activation chunk in
+// both planes, 90 KiB for 80 rows); the k-wave shapes hold fewer weight registers per chunk and prefetch two to
+// four chunks ahead instead of one.  launch_mt has the chunks and the ring of k_gemm_few_bf16.  A plan's K split is a whole
+// number of 128 k (kShapeKC) for either.
 constexpr int kNumShapes = 7;
 const int kShapeNT[kNumShapes] = {1, 2, 1, 2, 2, 1, 2};
 const int kShapeCS[kNumShapes] = {4, 4, 8, 8, 4, 2, 1};
