@@ -51,7 +51,7 @@ def _short(k):
 
 def _gemm_mode(name):
     """Epilogue of a projection (0 partial sums, 1 arg-max, 2 SwiGLU); None: not a projection of a bf16 model."""
-    m = re.match(r"k_gemm_(?:bf16<(?:\d+, ){6}(\d+), \d+|few_bf16<(?:\d+, ){6}(\d+)|rows_bf16<(?:\d+, ){3}(\d+))>", name)
+    m = re.match(r"k_gemm_(?:(?:few_)?bf16<(?:\d+, ){6}(\d+)(?:, \d+)?|rows_bf16<(?:\d+, ){3}(\d+))>", name)     # older traces: and the LDS pad
     return int(m.group(m.lastindex)) if m else None
 
 
@@ -132,8 +132,8 @@ def trace_summary(db, workload, command, bench_json=None):
         f.write("`python -m paper_2604_13519_amd.counters trace <results.db> --workload %s`:\n\n    %s\n\n" % (workload, command))
         f.write("Durations are kernel begin-to-end times from the trace; the run also holds model load (k_repack_tiles, k_kv_xfer)\n"
                 "and bench.py's untimed passes.  Template arguments of `k_gemm_bf16`: row tiles, tiles per wave, column sets, k-waves,\n"
-                "chunk, prefetch depth, mode (0 partial sums, 1 arg-max, 2 SwiGLU), LDS pad; of `k_gemm_few_bf16` the same with the ring's\n"
-                "depth and no pad; of `k_gemm_rows_bf16`: row tiles, column sets, k-waves, mode; grids in workgroups.\n\n")
+                "chunk, prefetch depth, mode (0 partial sums, 1 arg-max, 2 SwiGLU); of `k_gemm_few_bf16` the same with the ring's depth;\n"
+                "of `k_gemm_rows_bf16`: row tiles, column sets, k-waves, mode; grids in workgroups.\n\n")
         f.write("| kind | kernel | calls | total us | avg us | % |\n|---|---|---:|---:|---:|---:|\n")
         for (kind, k), (n, t) in sorted(agg.items(), key=lambda kv: -kv[1][1]):
             if t / total < 0.0005:

@@ -72,9 +72,13 @@ __device__ __forceinline__ u32x4 to_half8(u32x4 v) {
 // which makes any visible score overflow to +inf and any masked one 0.
 // Measured (with the two 32-key halves unrolled): 65 rows x 8 heads per KV head x 32768 keys x 4
 // sequences 514 -> 416 us, 33 rows x 16 sequences 114 -> 106 us, 38 rows x 23011 keys 43.3 -> 40.0 us,
-// 65 rows x 8192 keys 27.0 -> 25.3 us.  What bounds the loop now is the LDS: with the K and V^T fragment
-// reads compiled out the first of these takes 287 us, without the staging 341 us, without the
-// exponentials 398 us.
+// 65 rows x 8192 keys 27.0 -> 25.3 us.
+// What the kernel waits for, as it is now, by leaving parts out (us in a trace: all, without the K and V^T fragment reads
+// out of LDS, without staging the next block, without the exponentials, without all three): the first of these 324, 241,
+// 261, 283, 217; 33 rows x 16 sequences 94, 57, 68, 81, 46; 38 rows x 23011 keys 36, 23, 28, 34, 21; 65 rows x 8192 keys 23.8,
+// 20.7, 22.0, 22.0, 18.2.  Two thirds (half with three tiles in one wave) are the matrix instructions and what
+// surrounds them; of the rest the reads cost most, by the time products wait for them and not by the LDS's rate, which is
+// 15 - 22 % busy (counters).
 constexpr float kRefSlack = 8.f, kRefLimit = 256.f, kNoRef = -1e30f;
 
 union Pack8 {
@@ -577,7 +581,7 @@ int heads_per_block(int G) { return G >= 4 ? 4 : (G >= 2 ? 2 : 1); }
 // load (8B shape unless noted; us a launch): 4 x 32768 keys of 65 rows, 8 heads 397 -> 306 (576 workgroups were 2.25
 // rounds), 6 blocks of ingestion at 2000 39.0 -> 29.0, 8 x 4096 .. 2048 keys of 33 rows 49.5 -> 39.1, 16 x 8192 .. 2048
 // 104 -> 96, 8 x 8192 .. 2700 of 65 rows, 64 dims 68.5 -> 45.5, 16 x 17 rows 57 -> 48.5, 4 x 33 rows 29.1 -> 27.0 (two
-// workgroups a CU counted as one: 30.9).  The merge pays 0.5 us for reading a row's split count and gets it back
+// workgroups a CU counted as one: 30.9).  A merge of differing split counts reads them first and gets that back
 // from fewer partials (16.5 -> 11.3, 11.0 -> 8.8, 14.0 -> 12.1 us in the first, second and fourth of these).
 // kUnitFixed: a workgroup's start and finish cost about as much as three blocks.
 constexpr int kUnitFixed = 3, kBatchSplits = 16;

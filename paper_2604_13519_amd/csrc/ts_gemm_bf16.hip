@@ -158,7 +158,7 @@ __device__ __forceinline__ void finish(const GemmArgs& a, const f32x4 (&acc)[MT]
   }
 }
 
-template <int MT, int NT, int CS, int KW, int KC, int PF, int MODE, int XPAD = 16>
+template <int MT, int NT, int CS, int KW, int KC, int PF, int MODE>
 __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   constexpr int WAVES = CS * KW;            // CS column sets x KW k-step owners
   constexpr int KSTEPS = KC / 32;           // MFMA k-steps per chunk
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
   // 0-3, 12-15, 20-27 make the first): with rows 16 (2 mod 4) bytes apart, as with 32 more than KC, their 16-byte
   // vectors fall into 16 different bank groups.  16 bytes more left a conflict in every read, half of the LDS cycles
   // (counters: gate/up 65 rows 11.8 -> 7.2 M cycles).
-  constexpr int XS = KC + XPAD;
+  constexpr int XS = KC + 16;
   constexpr int NTHR = 64 * WAVES;
   constexpr int NBUF = PF + 1;              // weight register ring
   constexpr int PL = TS_ACT_PLANES;         // an activation is the sum of a hi and a lo half
@@ -328,7 +328,8 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_bf16(GemmArgs a) {
 // 12.5 : 12.2, O 9.5 : 9.3, 32B-class O 18.8 : 18.1, QKV 20.8 : 20.2; calls 842 : 832 us (decode), 32B-class layers 415 : 410.
 // 17 rows: gate/up 41.6 : 41.0, head of 8192 18.4 : 17.9, but the short ranges of QKV 13.6 : 14.0 and O 10.9 : 11.3.  From three row
 // tiles on the kernel above is the better one (38 rows down 25.3 : 28.7, 65 rows 28.8 : 32.3, O 14.1 : 15.1 us), with chunks
-// of 128 k and three or four slots too (26.9, 30.6, 15.0; at 1 row 21.6 : 22.2 for down).
+// of 128 k and three or four slots too (26.9, 30.6, 15.0; at 1 row 21.6 : 22.2 for down).  Nor is the step of the many-row
+// kernel, which reads ahead and requests between products, any faster there (gemm_bf16_plan).
 template <int MT, int NT, int CS, int KW, int KC, int RD, int MODE>
 __global__ __launch_bounds__(64 * CS * KW) void k_gemm_few_bf16(GemmArgs a) {
   constexpr int WAVES = CS * KW;            // CS column sets x KW k-step owners
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(64 * CS * KW) void k_gemm_few_bf16(GemmArgs a) {
   constexpr int PL = TS_ACT_PLANES;         // an activation is the sum of a hi and a lo half
   constexpr int UPR = KC / 8;               // 16-byte vectors per row of a chunk
   constexpr int PPP = MT * 16 * UPR / 64;   // 1 KiB pieces per plane of a chunk: one direct-to-LDS load of a wave each
-  constexpr int XN = (PL * PPP + WAVES - 1) / WAVES;      // pieces a wave stages; the surplus repeats its last one
+  constexpr int XN = (PL * PPP + WAVES - 1) / WAVES;      // pieces a wave stages; the surplus repeats the chunk's last one
   constexpr size_t XBYTES = (size_t)PL * PPP * 1024;
   constexpr int GN = XN + NT * KSW;         // loads of a group
   // one array per ring slot: the compiler then knows which loads a read of LDS has to wait for
@@ -581,7 +582,12 @@ int gemm_bf16_chunk(int shape) { return shape >= kRowsShape0 ? gemm_rows_chunk((
 // a split 7.9 -> 7.0 us; 65 rows O 33.0 -> 27.5 us, head of 151936 columns 363 -> 316 us, the rest alike.  Two layers and a
 // head of 8192 columns, 1 / 9 / 17 / 38 / 65 rows: 445 -> 418, 453 -> 427, 501 -> 450, 546 -> 509, 659 -> 603 us a call.
 GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
-  if (R > TS_MROWS_PER_BLOCK) {   // batches: the many-row kernel
+  // Batches: the many-row kernel.  Up to 80 rows the kernels of this file are the faster ones.  8B shape, us between events,
+  // these : the many-row kernel by its best plan - 38, 65 and 80 rows QKV 15.1 : 20.3, 18.8 : 21.0, 19.5 : 21.2, O 12.0 : 14.8,
+  // 14.2 : 15.8, 15.0 : 16.2, gate/up 43.8 : 50.7, 50.0 : 53.4, 52.2 : 53.4, down 23.9 : 28.4, 27.3 : 30.0, 29.7 : 30.5, head of
+  // 8192 columns 24 : 45, 32 : 48, 34 : 48 - except for the head of 128256 columns from 64 rows on: 49 rows 186 : 188, 64 193 : 189,
+  // 65 211 : 192, 80 213 : 193.
+  if (R > TS_MROWS_PER_BLOCK) {
     int mt, cfg, splits;
     const size_t max_part = m->part_elems ? m->part_elems : kRowsPartCap;
     gemm_rows_plan(m, R, N, K, mode, max_part, &mt, &cfg, &splits);
@@ -607,6 +613,9 @@ GemmPlan gemm_bf16_plan(const ts_model* m, int R, int N, int K, int mode) {
       // one row tile (the kernel with the deep ring): activations weigh little, splits more than their bytes, and neither
       // one tile per wave nor the number of waves matters.  One row, before and with its own constants: QKV 12.3 -> 11.8 us,
       // down 21.5 -> 20.9; 32B-class O 18.0 -> 16.6, down 42.5 -> 40.2 (9 rows 12.8 -> 12.6, 22.0 -> 21.2, 19.2 -> 18.7, 43.0 -> 41.2)
+      // Gate/up and the arg-max keep the constants of the other rows.  Gate/up (28672 columns) and a head of 8192 get the best
+      // shape with them at 1 - 32 rows; the one plan of a head is made for 80 rows (amax_parts is sized by it), and
+      // for 128256 columns that is 6 - 9 % from the best one at 1 - 16 rows (153 : 166, 157 : 166, 158 : 165 us at 1, 9, 16 rows).
       const bool one = rows <= 16 && mode == MODE_PARTIAL;
       if (s > 1) cost += std::max(2.3 * s * R * (double)N * 4.0 / m->n_cu, (one && N >= 1024 ? 8.0 : 5.0) * std::min(N, 1024) * s);
       cost += (one ? 0.1 : 0.3) * rounds * rows * kper * 2.0 * TS_ACT_PLANES;

@@ -37,7 +37,6 @@
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -128,7 +127,9 @@ __global__ __launch_bounds__(64 * WAVES, MT <= 4 && KW <= 2 ? 4 : 2) void k_gemm
   // (swz), so that the 16-byte reads below meet no bank twice: each is served in groups of 16 lanes that hold rows 0-3
   // and 12-15 of one lane group and rows 4-11 of the next.
   auto swz = [](int row) { return KC == 128 ? row & 15 : KC == 64 ? row >> 1 & 7 : (row >> 2 & 1) * 3; };
-  // plane and row block are in the base: both can be past 4 GiB in the workspace of a very large batch; the lane
+  // Rows past the last hold what an earlier pass left, or zeros: their outputs are not stored.  (The kernels of few rows
+  // read one spare row of zeros in their place, which costs the matrix pipes less power; not tried here.)
+  // Plane and row block are in the base: both can be past 4 GiB in the workspace of a very large batch; the lane
   // offset covers the 64 to 128 rows of a block
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const char* xbase = reinterpret_cast<const char*>(a.X) + ((size_t)row0 * act_ld(a.K) + kbase0) * 2;
@@ -371,9 +372,9 @@ int gemm_rows_chunk(int cfg) { return kCfgKC[cfg]; }
 // Row tiles per workgroup (4..8: the rows are cut into equal blocks), configuration and K splits with the least
 // modelled time.  max_part_elems bounds splits x R x N.  K is a multiple of 128 (check_config), so every chunk length fits.
 //   workgroup = k-steps of a wave x (kStepTile x row tiles + kStep) + kFix + kFixTile x row tiles   (start, finish, joining k-waves)
-//   launch    = rounds over the CUs x workgroup, 8 % less where half the CUs stay empty (clock), + 0.6 us per million partial sums
+//   launch    = rounds over the CUs x workgroup, less 8 % of the share of CUs that stay empty (clock), + 0.6 us per million partial sums
 // where the 4-row-tile kernels with one or two k-waves need half the registers and LDS of a CU: two workgroups share
-// one and take 1.75 times as long as one.  The constants (ns, us) are fitted to a sweep of every (row tiles, configuration,
+// one and take 1.75 times as long as one.  The constants (all in us) are fitted to a sweep of every (row tiles, configuration,
 // splits) of the 8B and 32B-class projections at 18 and 8 row counts of 96 to 2048, each with the change of the
 // kernels that read the sums: the chosen ones together take 0.5 % more than the best ones, at most 7 %
 // (400 rows x 8192 columns of the head).  The model before, one efficiency per configuration: 3.9 %, at most 25 %.

@@ -892,8 +892,8 @@ static ts_status verify_impl(ts_model* m, ts_kv* const* kvs, int n_seqs, const i
   }
   launch_norm(m, R, m->norm_f, pending_parts, pending_stride, false);
   if (bf) {
-    // one row block: the plan made at load (it sized the partial buffers); batches: the many-row kernel,
-    // whose 512-column groups need fewer partials
+    // one row block: the plan made at load for the most rows of a block, which sized amax_parts; batches: the many-row
+    // kernel, whose planner takes only configurations with so many column groups at most (its widest always is one)
     const GemmPlan p = gemm_bf16_plan(m, std::max(R, TS_MROWS_PER_BLOCK), c.vocab, d, 1);
     ProfScope ps(m, "gemm_lm_head_argmax");
     launch_gemm_bf16(m, (const f16_t*)m->Xn, (const f16_t*)m->lm_head, nullptr, R, c.vocab, d, p, 1,
