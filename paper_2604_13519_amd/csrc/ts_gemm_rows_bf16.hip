@@ -23,8 +23,9 @@
 //    out between the first products of a chunk, so that the matrix pipes do not stand still at a chunk's
 //    edge.  Through registers (one chunk ahead with k-waves, two without) against this, us:
 //    132 rows gate/up 108 -> 78, down 57 -> 44; 2048 rows gate/up 765 -> 710 (1.27 -> 1.36 PFLOP/s, both planes
-//    counted), down 345 -> 327, QKV 173 -> 159; 528 rows gate/up 224 -> 193.  What is left is power: register operands
-//    alone sustain 1.55 - 1.75 PFLOP/s here.
+//    counted), down 345 -> 327, QKV 173 -> 159; 528 rows gate/up 224 -> 193.  What is left: the matrix pipes are
+//    busy 76 % of the cycles (528 rows gate/up, counters) of a clock that the power holds down: random operands that stay in
+//    registers sustain 1.88 PFLOP/s here, zeros 2.37.
 //  * gate/up variant (SWIGLU): gate and up tiles alternate, a wave holds two (gate, up) pairs
 //    and the epilogue stores SiLU(gate) * up as half.
 //  * lm_head variant (ARGMAX, no K split): the epilogue reduces each row's maximum over the workgroup's
