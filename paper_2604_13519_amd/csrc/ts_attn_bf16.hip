@@ -574,8 +574,9 @@ int heads_per_block(int G) { return G >= 4 ? 4 : (G >= 2 ? 2 : 1); }
 // Several: no unit is longer than L blocks, and L is the smallest with which the units make r workgroups a CU; r is
 // the one with the least modelled time: r full rounds of units or, where lengths leave the rounds ragged, the mean
 // load of a CU and half a unit; two workgroups that share a CU take one and a half times as long as one, 1.35 times
-// with one row tile, whose workgroups mostly wait for their keys (with 1.5 there, us a launch, against 1.35: 4 x 4096 keys of 1 row
-// 20.9 : 18.6, of 16 rows 21.9 : 20.2, 6 x 4096 .. 1024 20.1 : 19.1, 6 x 1000 11.8 : 11.2).  A sequence
+// with one row tile, whose workgroups mostly wait for their keys (us a launch with 1.5 there, with 1.35, and with the same number of
+// splits for all: 4 x 4096 keys of 1 row 21.8, 17.8, 19.3, of 16 rows 22.7, 20.3, 21.0, 6 x 4096 .. 1024 of 1 row 21.2, 17.5, 19.9,
+// 6 x 1000 12.5, 11.2, 11.8).  A sequence
 // gets units in proportion to its length, so that every workgroup has nearly the same share and the last round is
 // full.  Against one number of splits for all sequences, chosen so that the longest share is half of a CU's average
 // load (8B shape unless noted; us a launch): 4 x 32768 keys of 65 rows, 8 heads 397 -> 306 (576 workgroups were 2.25
